@@ -234,3 +234,70 @@ _TOLERANCE = {
 
 def tolerance(case):
     return dict(_TOLERANCE[case["op"]])
+
+
+# ---------------------------------------------------------------------------------------------------------------
+# the same results in 64 bits
+# ---------------------------------------------------------------------------------------------------------------
+def _exact_attn(c, s):
+    B, Hq, Hkv, Sq, Sk, D = (c[k] for k in ("B", "Hq", "Hkv", "Sq", "Sk", "D"))
+    o = torch.empty((B, Hq, Sq, D), dtype=torch.float64, device="cuda")
+    lse = torch.empty((B, Hq, Sq), dtype=torch.float64, device="cuda")
+    rows = max(1, min(Sq, (1 << 28) // Sk))                 # 2 GiB of scores at a time
+    keys = torch.arange(Sk, device="cuda")
+    for b in range(B):
+        for hk in range(Hkv):
+            kt, v = s["k"][b, hk].double().t().contiguous(), s["v"][b, hk].double()
+            for h in range(hk * (Hq // Hkv), (hk + 1) * (Hq // Hkv)):
+                for i in range(0, Sq, rows):
+                    scores = (s["q"][b, h, i:i + rows].double() * float(D) ** -0.5) @ kt
+                    if c["causal"]:
+                        last = torch.arange(i, i + scores.shape[0], device="cuda") + (Sk - Sq)
+                        scores.masked_fill_(keys[None, :] > last[:, None], -math.inf)
+                    lse[b, h, i:i + rows] = total = torch.logsumexp(scores, dim=1)
+                    o[b, h, i:i + rows] = scores.sub_(total[:, None]).exp_() @ v
+    return o, lse
+
+
+def _exact_gemm(c, s):
+    b = s["b"].double()
+    return s["a"].double() @ (b.t().contiguous() if c["b_is_nk"] else b)
+
+
+def _groups_of_128(v):
+    """e4m3 codes and a scale per 128 values, both decided in 32 bits as the format is defined, widened again."""
+    g = v.float().reshape(v.shape[0], -1, 128)
+    scale = g.abs().amax(dim=2, keepdim=True) * torch.tensor(1.0 / 448.0, device=v.device)
+    scale = torch.where(scale > 0, scale, torch.ones_like(scale))
+    codes = (g * (1.0 / scale)).clamp_(-448.0, 448.0).to(torch.float8_e4m3fn)
+    return (codes.double() * scale.double()).reshape(v.shape)
+
+
+def _widened(codes, scales):
+    w = codes.view(torch.float8_e4m3fn).double()
+    return w * scales.double().repeat_interleave(128, 0).repeat_interleave(128, 1)
+
+
+def _exact_moe(c, s):
+    T, H, I, E = c["T"], c["H"], c["I"], c["E"]
+    y = torch.zeros((T, H), dtype=torch.float64, device="cuda")
+    for e in range(E):
+        tok, slot = (s["ids"] == e).nonzero(as_tuple=True)
+        if tok.numel() == 0:
+            continue
+        xq = _groups_of_128(s["x"][tok])
+        gu = xq @ _widened(s["w13"][e], s["s13"][e]).t().contiguous()
+        gate, up = gu[:, :I], gu[:, I:]
+        a = _groups_of_128(gate / (1.0 + torch.exp(-gate)) * up)
+        rows = a @ _widened(s["w2"][e], s["s2"][e]).t().contiguous()
+        y.index_add_(0, tok, rows * s["wts"][tok, slot].double()[:, None])
+    return y
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in 64 bits; for the expert layer with the codes of its two quantizations,
+    which are part of its definition.  None where that takes too long."""
+    if case["op"] == "attn" and work(case)["flops"] > 1.2e13:
+        return None
+    op, s = prepare(case, seed)
+    return {"attn": _exact_attn, "gemm": _exact_gemm, "moe": _exact_moe}[op](case, s)
