@@ -31,6 +31,8 @@
  * Supported: D in {64, 128}; any B, Hq, Hkv, Sq, Sk >= 1 with Hq % Hkv == 0 and
  * B*Hq*ceil(Sq/128) < 2^31; scale finite and > 0.
  *
+ * Calls with few query rows against many keys can be given memory to spread over the whole GPU: attn_workspace.h.
+ *
  * `stream` is a hipStream_t passed as void* (NULL = the default stream).  The
  * call enqueues the kernel on that stream and returns; the result is ready
  * when the stream reaches that point.  Thread-safe, no global state.
@@ -91,7 +93,7 @@ int attn_fwd_strided(const void *q, const void *k, const void *v, void *o, float
  *                  other's start-up, drain and causal diagonal; what short sequences and small grids get);
  *   wg_rows = 0:   the library's own choice, i.e. exactly attn_fwd.
  * Any other value: ATTN_ERR_UNSUPPORTED.  Calls the 128-row kernel with 64-bit addressing serves (Sq <= 64, or a
- * head of K/V spanning 4 GiB or more) ignore wg_rows.  Everything else as for attn_fwd.
+ * head of K/V spanning 4 GiB or more) run it for either value.  Everything else as for attn_fwd.
  */
 int attn_fwd_tile(const void *q, const void *k, const void *v, void *o, float *lse,
                   int B, int Hq, int Hkv, int Sq, int Sk, int D,

@@ -41,6 +41,10 @@ def load_library(build_if_missing: bool = True):
         lib.attn_fwd_tile.argtypes = [p, p, p, p, p, i, i, i, i, i, i, i, f, i, p]
         lib.attn_fwd_strided.restype = i
         lib.attn_fwd_strided.argtypes = [p, p, p, p, p, i, i, i, i, i, i, p, p, p, p, i, f, p]
+        lib.attn_fwd_workspace_bytes.restype = ctypes.c_size_t
+        lib.attn_fwd_workspace_bytes.argtypes = [i, i, i, i, i, i]
+        lib.attn_fwd_workspace.restype = i
+        lib.attn_fwd_workspace.argtypes = [p, p, p, p, p, i, i, i, i, i, i, p, p, p, p, i, f, p, ctypes.c_size_t, i, p]
         ll = ctypes.c_longlong
         lib.gemm_bf16.restype = i
         lib.gemm_bf16.argtypes = [p, p, p, i, i, i, ll, ll, ll, i, p]
@@ -146,10 +150,20 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
         raise ValueError("q, k, v, o, lse must live on one CUDA device")
     if scale is None:
         scale = float(D) ** -0.5
+    current = torch.cuda.current_stream(q.device)
     if stream is None:
-        stream = torch.cuda.current_stream(q.device)
+        stream = current
     lib = load_library()
-    if all(t.is_contiguous() for t in (q, k, v, o)):
+    # few query rows: cut the keys over workgroups too, with torch's memory for the parts (only on the stream torch
+    # will reuse that memory on; elsewhere the call does without it)
+    need = lib.attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) if Sq <= 64 and stream.cuda_stream == current.cuda_stream else 0
+    if need:
+        ws = torch.empty(need, dtype=torch.uint8, device=q.device)
+        rc = lib.attn_fwd_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
+                                    B, Hq, Hkv, Sq, Sk, D, _strides3(q), _strides3(k), _strides3(v), _strides3(o),
+                                    int(bool(causal)), float(scale), ws.data_ptr(), need,
+                                    need // (4 * B * Hq * Sq * (D + 2)), stream.cuda_stream)
+    elif all(t.is_contiguous() for t in (q, k, v, o)):
         rc = lib.attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
                           B, Hq, Hkv, Sq, Sk, D, int(bool(causal)), float(scale), stream.cuda_stream)
     else:

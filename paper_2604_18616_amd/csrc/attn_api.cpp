@@ -4,7 +4,7 @@
 #include <math.h>
 #include <stdint.h>
 
-#include "../../include/attn.h"
+#include "../../include/attn_workspace.h"
 #include "attn_launch.h"
 
 #define ATTN_VERSION 100   /* 0.1.0 */
@@ -19,7 +19,7 @@ static int check_dims(int B, int Hq, int Hkv, int Sq, int Sk, int D) {
 static int attn_fwd_impl(const void* q, const void* k, const void* v, void* o, float* lse,
                          int B, int Hq, int Hkv, int Sq, int Sk, int D,
                          const long long* qs, const long long* ks, const long long* vs, const long long* os,
-                         int causal, float scale, int wg_rows, void* stream) {
+                         int causal, float scale, int wg_rows, void* workspace, size_t workspace_bytes, int splits, void* stream) {
     if (!q || !k || !v || !o) return ATTN_ERR_NULL_PTR;
     if (wg_rows != 0 && wg_rows != 128 && wg_rows != 256) return ATTN_ERR_UNSUPPORTED;
     if (int rc = check_dims(B, Hq, Hkv, Sq, Sk, D)) return rc;
@@ -48,6 +48,12 @@ static int attn_fwd_impl(const void* q, const void* k, const void* v, void* o, f
     p.nQt = 0; p.nblocks = 0; p.hpw = 1; p.hpw_log2 = 0;   // set by the launcher
     p.scale = scale;
     p.scale_log2 = (float)((double)scale * 1.4426950408889634074);
+    if (wg_rows == 0 && attn_split_fits(p)) {
+        AttnSplit sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, splits);
+        if (!workspace || workspace_bytes < attn_split_bytes(B, Hq, Sq, D, sp.splits)) sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 1);
+        const int src = attn_split_launch(p, D, causal != 0, sp, workspace, (hipStream_t)stream);
+        return src == 0 ? ATTN_OK : src == -2 ? ATTN_ERR_BAD_SHAPE : ATTN_ERR_LAUNCH;
+    }
     const int rc = attn_launch(p, D, causal != 0, wg_rows, (hipStream_t)stream);
     return rc == 0 ? ATTN_OK : rc == -2 ? ATTN_ERR_BAD_SHAPE : ATTN_ERR_LAUNCH;
 }
@@ -58,7 +64,7 @@ extern "C" int attn_fwd(const void* q, const void* k, const void* v, void* o, fl
     if (int rc = check_dims(B, Hq, Hkv, Sq, Sk, D)) return (q && k && v && o) ? rc : ATTN_ERR_NULL_PTR;
     const long long qs[3] = {(long long)Hq * Sq * D, (long long)Sq * D, D};
     const long long ks[3] = {(long long)Hkv * Sk * D, (long long)Sk * D, D};
-    return attn_fwd_impl(q, k, v, o, lse, B, Hq, Hkv, Sq, Sk, D, qs, ks, ks, qs, causal, scale, 0, stream);
+    return attn_fwd_impl(q, k, v, o, lse, B, Hq, Hkv, Sq, Sk, D, qs, ks, ks, qs, causal, scale, 0, nullptr, 0, 0, stream);
 }
 
 extern "C" int attn_fwd_strided(const void* q, const void* k, const void* v, void* o, float* lse,
@@ -68,7 +74,24 @@ extern "C" int attn_fwd_strided(const void* q, const void* k, const void* v, voi
                                 int causal, float scale, void* stream) {
     if (!q_strides || !k_strides || !v_strides || !o_strides) return ATTN_ERR_NULL_PTR;
     return attn_fwd_impl(q, k, v, o, lse, B, Hq, Hkv, Sq, Sk, D, q_strides, k_strides, v_strides, o_strides,
-                         causal, scale, 0, stream);
+                         causal, scale, 0, nullptr, 0, 0, stream);
+}
+
+extern "C" size_t attn_fwd_workspace_bytes(int B, int Hq, int Hkv, int Sq, int Sk, int D) {
+    if (check_dims(B, Hq, Hkv, Sq, Sk, D) || (D != 64 && D != 128) || !attn_split_sizes(Sq, Sk)) return 0;
+    return attn_split_bytes(B, Hq, Sq, D, attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 0).splits);
+}
+
+extern "C" int attn_fwd_workspace(const void* q, const void* k, const void* v, void* o, float* lse,
+                                  int B, int Hq, int Hkv, int Sq, int Sk, int D,
+                                  const long long* q_strides, const long long* k_strides,
+                                  const long long* v_strides, const long long* o_strides,
+                                  int causal, float scale, void* workspace, size_t workspace_bytes, int splits, void* stream) {
+    if (!q_strides || !k_strides || !v_strides || !o_strides) return ATTN_ERR_NULL_PTR;
+    if (splits < 0 || splits > kMaxSplits) return ATTN_ERR_UNSUPPORTED;
+    if ((uintptr_t)workspace & 15u) return ATTN_ERR_MISALIGNED;
+    return attn_fwd_impl(q, k, v, o, lse, B, Hq, Hkv, Sq, Sk, D, q_strides, k_strides, v_strides, o_strides,
+                         causal, scale, 0, workspace, workspace_bytes, splits, stream);
 }
 
 extern "C" int attn_fwd_tile(const void* q, const void* k, const void* v, void* o, float* lse,
@@ -77,7 +100,7 @@ extern "C" int attn_fwd_tile(const void* q, const void* k, const void* v, void* 
     if (int rc = check_dims(B, Hq, Hkv, Sq, Sk, D)) return (q && k && v && o) ? rc : ATTN_ERR_NULL_PTR;
     const long long qs[3] = {(long long)Hq * Sq * D, (long long)Sq * D, D};
     const long long ks[3] = {(long long)Hkv * Sk * D, (long long)Sk * D, D};
-    return attn_fwd_impl(q, k, v, o, lse, B, Hq, Hkv, Sq, Sk, D, qs, ks, ks, qs, causal, scale, wg_rows, stream);
+    return attn_fwd_impl(q, k, v, o, lse, B, Hq, Hkv, Sq, Sk, D, qs, ks, ks, qs, causal, scale, wg_rows, nullptr, 0, 0, stream);
 }
 
 extern "C" double attn_mfma_calibration(float* sink, int blocks, int iters, void* stream) {

@@ -24,6 +24,25 @@ struct AttnParams {
 // Returns 0, -1 if the runtime refused the launch, -2 if the grid would not fit 31 bits.
 int attn_launch(AttnParams p, int D, int causal, int wg_rows, hipStream_t stream);
 
+// Keys of one kv head cut over workgroups (attn_split_kernel.hip): the path of calls with few query rows.
+constexpr int kMaxSplits = 256;
+struct AttnSplit {
+    int rb;            // 32-row blocks of packed query rows per workgroup: 1, 2 or 4
+    int waves;         // wavefronts per workgroup: 4, or 2 (rb = 1)
+    int row_wgs;       // workgroups along the packed query rows of a kv head
+    int splits;        // workgroups along its keys
+    float* part;       // [B*Hq*Sq, splits, D] unnormalised O of every split, relative to its own maximum
+    float* ml;         // [B*Hq*Sq, splits, 2] that maximum (raw score units) and the row sum
+};
+// Whether the call's shape is one for that path.
+bool attn_split_sizes(int Sq, int Sk);
+bool attn_split_fits(const AttnParams& p);
+// Its cut; splits 0: by size.  Host arithmetic only.
+AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int splits);
+// Bytes of workspace that cut needs: none for one split.
+size_t attn_split_bytes(int B, int Hq, int Sq, int D, int splits);
+int attn_split_launch(AttnParams p, int D, int causal, AttnSplit sp, void* workspace, hipStream_t stream);
+
 // Enqueue the pure-MFMA calibration kernel (blocks x 8 wavefronts x iters x 4 MFMAs); returns
 // the FLOPs it performs, or -1 if the launch was refused.  sink: >= 4 bytes of device memory.
 double attn_launch_mfma_calibration(float* sink, int blocks, int iters, int data, hipStream_t stream);

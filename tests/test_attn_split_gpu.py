@@ -1,0 +1,102 @@
+"""attn_fwd_workspace (few query rows, keys cut over workgroups) against the fp64 CPU reference, at the edges of its cuts:
+one tile per key group and one key more or less, 1 / 32 / 33 / 64 / 65 packed query rows, empty parts, both combine
+kernels, and the call without memory."""
+import numpy as np
+import pytest
+
+from paper_2604_18616_amd import inputs as I
+from tests._util import check, from_dev_bf16, oracle_parallel, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# B, Hq, Hkv, Sq, Sk, D, causal
+SHAPES = [
+    (1, 2, 2, 1, 129, 128, False),       # 5 tiles, the last with one key
+    (2, 8, 1, 4, 1000, 128, True),       # 32 packed rows: one row block
+    (1, 3, 1, 11, 417, 64, True),        # 33: two row blocks share a workgroup's tiles
+    (2, 2, 1, 32, 640, 128, True),       # 64
+    (1, 5, 1, 13, 333, 128, False),      # 65: four row blocks
+    (1, 6, 2, 64, 161, 64, True),        # 192 rows: two workgroups along the rows
+    (1, 1, 1, 1, 8300, 64, False),       # enough keys for every number of splits
+]
+
+
+def call(q, k, v, causal, scale, splits, memory=True, lse=True):
+    import torch
+    from paper_2604_18616_amd import binding
+    lib = binding.load_library()
+    B, Hq, Sq, D = q.shape
+    o = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+    ls = torch.full(q.shape[:3], float("nan"), dtype=torch.float32, device="cuda")
+    n = 4 * B * Hq * Sq * max(splits, 1) * (D + 2) if splits else lib.attn_fwd_workspace_bytes(B, Hq, k.shape[1], Sq, k.shape[2], D)
+    ws = torch.full((max(n, 16),), 0xFF, dtype=torch.uint8, device="cuda")
+    s3 = binding._strides3
+    rc = lib.attn_fwd_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), ls.data_ptr() if lse else None,
+                                B, Hq, k.shape[1], Sq, k.shape[2], D, s3(q), s3(k), s3(v), s3(o), int(causal), scale,
+                                ws.data_ptr() if memory else None, n if memory else 0, splits,
+                                torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, binding.strerror(rc)
+    torch.cuda.synchronize()
+    return o, ls
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "B%d_H%d_%d_S%d_%d_D%d_%s" % s)
+def test_every_cut_against_the_reference(shape):
+    B, Hq, Hkv, Sq, Sk, D, causal = shape
+    w = I.Workload("split", B, Hq, Hkv, Sq, Sk, D, causal, 41)
+    qb, kb, vb = I.make_qkv(w)
+    ref = oracle_parallel(qb, kb, vb, causal, w.scale)
+    q, k, v = to_dev(qb), to_dev(kb), to_dev(vb)
+    for splits in (0, 1, 2, 5, 8, 9, 64, 65, 256):
+        print(shape, splits, flush=True)
+        o, lse = call(q, k, v, causal, w.scale, splits)
+        check(from_dev_bf16(o), lse.cpu().numpy().astype(np.float64), *ref, "%s splits %d" % (shape, splits))
+    # without memory: one workgroup along the keys
+    o1, lse1 = call(q, k, v, causal, w.scale, 1)
+    o0, lse0 = call(q, k, v, causal, w.scale, 7, memory=False)
+    assert bool((o0 == o1).all()) and bool((lse0 == lse1).all())
+    o2, _ = call(q, k, v, causal, w.scale, 3, lse=False)
+    assert np.abs(from_dev_bf16(o2) - ref[0]).max() <= 2e-2
+
+
+@pytest.mark.parametrize("direction", ["rising", "falling"])
+@pytest.mark.parametrize("splits", [1, 6, 40])
+def test_score_maxima_that_differ_between_the_parts(direction, splits):
+    """Keys scaled along the sequence: every key group and every part has its own maximum, far from the others'."""
+    w = I.Workload("drift", 1, 4, 2, 3, 900, 128, False, 42)
+    qb, kb, vb = I.make_qkv(w)
+    k32 = I.bf16_bits_to_f32(kb)
+    ramp = np.linspace(0.0, 12.0, w.Sk, dtype=np.float32)[None, None, :, None]
+    kb = I.f32_to_bf16_bits(k32 * (ramp if direction == "rising" else ramp[:, :, ::-1]))
+    ref = oracle_parallel(qb, kb, vb, w.causal, w.scale)
+    o, lse = call(to_dev(qb), to_dev(kb), to_dev(vb), w.causal, w.scale, splits)
+    check(from_dev_bf16(o), lse.cpu().numpy().astype(np.float64), *ref, direction)
+
+
+def test_keys_past_the_last_one_are_not_read_into_the_result():
+    """K and V are the first rows of longer buffers whose other rows hold NaN."""
+    import torch
+    from paper_2604_18616_amd import attn_fwd
+    gen = torch.Generator(device="cuda").manual_seed(43)
+    full = lambda: torch.full((2, 512, 4, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    q = torch.randn((2, 2, 8, 128), generator=gen, device="cuda", dtype=torch.bfloat16).transpose(1, 2)
+    k, v = full(), full()
+    for t in (k, v):
+        t[:, :301] = torch.randn((2, 301, 4, 128), generator=gen, device="cuda", dtype=torch.bfloat16)
+    k, v = (t[:, :301].transpose(1, 2) for t in (k, v))
+    o, lse = attn_fwd(q, k, v, causal=True)
+    want = attn_fwd(q.contiguous(), k.contiguous(), v.contiguous(), causal=True)
+    assert torch.isfinite(o.float()).all() and torch.equal(o.contiguous(), want[0]) and torch.equal(lse, want[1])
+
+
+def test_call_on_another_stream_than_torchs_current_one():
+    import torch
+    from paper_2604_18616_amd import attn_fwd
+    gen = torch.Generator(device="cuda").manual_seed(44)
+    q, k, v = (torch.randn((1, 4, s, 64), generator=gen, device="cuda", dtype=torch.bfloat16) for s in (1, 3000, 3000))
+    want = attn_fwd(q, k, v)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    got = attn_fwd(q, k, v, stream=side)
+    torch.cuda.synchronize()
+    assert (got[0].float() - want[0].float()).abs().max() <= 2e-2 and (got[1] - want[1]).abs().max() <= 1e-3
