@@ -22,8 +22,9 @@
  *
  * Supported: any M, N, K >= 1 with lda >= K, ldb >= (b_is_nk ? K : N), ldc >= N and every
  * pitch < 2^31.  The tiled matrix-core kernel runs when a, b, c are 16-byte aligned and
- * N, K, lda, ldb, ldc are multiples of 8 (M is free); any other shape runs a slower
- * general kernel with the same result contract.  Pointers must be 2-byte aligned.
+ * N, K, lda, ldb, ldc are multiples of 8 (M is free).  Other operands take a matrix-core kernel
+ * fed through registers (K >= 64 and, for B stored [K, N], N >= 64), the smallest of them a
+ * general kernel, with the same result contract.  Pointers must be 2-byte aligned.
  *
  * `stream` is a hipStream_t passed as void* (NULL = the default stream).  The call
  * enqueues one kernel and returns.  Thread-safe, no global state.  Every argument check
@@ -54,7 +55,8 @@ int gemm_bf16(const void *a, const void *b, void *c, int M, int N, int K,
  * poor number of workgroups (3072 x 3072: 192 instead of 144 for 256 CUs).
  * 0 = what gemm_bf16 does: of 25616, 19216, 128, 1284 and 64 the shape with the best estimate of (throughput of the
  * shape on a full chip) x (how full its last round of workgroups leaves the 256 CUs); see gemm_bf16_auto_tile.
- * Any other value: ATTN_ERR_UNSUPPORTED.  Shapes that only the general kernel can take ignore the choice.
+ * Any other value: ATTN_ERR_UNSUPPORTED.  Operands of the register-fed kernel take 64 x 64 tiles for 64 and 128 x 128 tiles
+ * for the other values; the general kernel ignores the choice.
  * For tuning and for tests.
  */
 int gemm_bf16_tile(const void *a, const void *b, void *c, int M, int N, int K,

@@ -11,7 +11,7 @@ CSRC = os.path.join(_HERE, "csrc")
 OBJ_DIR = os.path.join(_HERE, "_build")
 LIB_PATH = os.path.join(_HERE, "libattn_mi355x.so")
 SOURCES = ["attn_api.cpp", "attn_fwd_kernel.hip", "attn_split_kernel.hip", "gemm_api.cpp", "gemm_bf16_kernel.hip",
-           "moe_api.cpp", "moe_fp8_kernel.hip"]
+           "gemm_unaligned_kernel.hip", "moe_api.cpp", "moe_fp8_kernel.hip"]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed-fp32 instructions are kept out of all device code on the test machines

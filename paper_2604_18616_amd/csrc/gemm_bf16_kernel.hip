@@ -400,7 +400,8 @@ __global__ __launch_bounds__(T::kWaves * 64, T::kWaves >= 4 ? T::kPerCU : 1) voi
 // ------------------------------------------------------------------------------------
 // General kernel: any M, N, K, pitches and 2-byte-aligned pointers.  64 x 64 tile, 16-deep
 // k steps through fp32 LDS tiles with zero fill past the edges, 4 x 4 outputs per thread,
-// plain fp32 FMAs in k order.  Serves the shapes the tiled kernel's 16-byte pieces cannot.
+// plain fp32 FMAs in k order.  Serves what neither matrix-core kernel takes: unaligned rows with fewer than
+// 64 of k, or fewer than 64 columns of B stored [K,N].
 // ------------------------------------------------------------------------------------
 template <bool B_NK>
 __global__ __launch_bounds__(256) void gemm_bf16_general(GemmParams p) {
@@ -504,6 +505,8 @@ int gemm_launch(GemmParams p, int b_is_nk, bool tiled, int tile, hipStream_t str
         else if (tile == 128416) launch_tiled<TileSmall4_16>(p, b_is_nk, stream);
         else if (tile == 6416) launch_tiled<TileTiny16>(p, b_is_nk, stream);
         else launch_tiled<TileSmall>(p, b_is_nk, stream);
+    } else if (gemm_unaligned_sizes(p.N, p.K, b_is_nk)) {
+        gemm_unaligned_launch(p, b_is_nk, tile, stream);
     } else {
         p.tiles_m = (p.M + 63) / 64;
         p.tiles_n = (p.N + 63) / 64;

@@ -20,3 +20,8 @@ int gemm_auto_tile(int M, int N);
 // alignment rules of the matrix-core kernel; `tile` is 0 (gemm_auto_tile) or one of the values
 // gemm_bf16_tile accepts.  Returns 0, or -1 if the launch was refused.
 int gemm_launch(GemmParams p, int b_is_nk, bool tiled, int tile, hipStream_t stream);
+
+// Operands that fail those alignment rules: whether the register-fed matrix-core kernel takes these sizes, and its
+// launch; `tile` is 64, 0 (by size) or anything else for 128.
+bool gemm_unaligned_sizes(int N, int K, int b_is_nk);
+void gemm_unaligned_launch(const GemmParams& p, int b_is_nk, int tile, hipStream_t stream);
