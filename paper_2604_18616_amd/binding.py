@@ -50,6 +50,10 @@ def load_library(build_if_missing: bool = True):
         lib.gemm_bf16.argtypes = [p, p, p, i, i, i, ll, ll, ll, i, p]
         lib.gemm_bf16_tile.restype = i
         lib.gemm_bf16_tile.argtypes = [p, p, p, i, i, i, ll, ll, ll, i, i, p]
+        lib.gemm_bf16_workspace_bytes.restype = ctypes.c_size_t
+        lib.gemm_bf16_workspace_bytes.argtypes = [i, i, i]
+        lib.gemm_bf16_workspace.restype = i
+        lib.gemm_bf16_workspace.argtypes = [p, p, p, i, i, i, ll, ll, ll, i, i, i, p, ctypes.c_size_t, p]
         lib.gemm_bf16_auto_tile.restype = i
         lib.gemm_bf16_auto_tile.argtypes = [i, i]
         lib.gemm_bf16_flops.restype = ctypes.c_double
@@ -194,10 +198,20 @@ def gemm_bf16(a, b, c=None, b_is_nk=False, stream=None, tile=0):
         c = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
     if c.shape != (M, N) or c.dtype != torch.bfloat16 or c.stride(1) != 1:
         raise ValueError("c must be bfloat16 [M,N] with contiguous rows")
+    current = torch.cuda.current_stream(a.device)
     if stream is None:
-        stream = torch.cuda.current_stream(a.device)
-    rc = load_library().gemm_bf16_tile(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K,
-                                       a.stride(0), b.stride(0), c.stride(0), int(bool(b_is_nk)), int(tile), stream.cuda_stream)
+        stream = current
+    lib = load_library()
+    # results of few tiles: cut k over workgroups too, with torch's memory for the parts (only on the stream torch will
+    # reuse that memory on; elsewhere the call does without it)
+    need = lib.gemm_bf16_workspace_bytes(M, N, K) if tile == 0 and stream.cuda_stream == current.cuda_stream else 0
+    if need:
+        ws = torch.empty(need, dtype=torch.uint8, device=a.device)
+        rc = lib.gemm_bf16_workspace(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, a.stride(0), b.stride(0), c.stride(0),
+                                     int(bool(b_is_nk)), 0, 0, ws.data_ptr(), need, stream.cuda_stream)
+    else:
+        rc = lib.gemm_bf16_tile(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, a.stride(0), b.stride(0), c.stride(0),
+                                int(bool(b_is_nk)), int(tile), stream.cuda_stream)
     if rc != 0:
         raise AttnError(rc, strerror(rc))
     return c

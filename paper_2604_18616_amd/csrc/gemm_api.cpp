@@ -3,11 +3,11 @@
 #include <stdint.h>
 
 #include "../../include/attn.h"
-#include "../../include/gemm.h"
+#include "../../include/gemm_workspace.h"
 #include "gemm_launch.h"
 
-extern "C" int gemm_bf16_tile(const void* a, const void* b, void* c, int M, int N, int K,
-                              long long lda, long long ldb, long long ldc, int b_is_nk, int tile, void* stream) {
+static int gemm_bf16_impl(const void* a, const void* b, void* c, int M, int N, int K, long long lda, long long ldb, long long ldc,
+                          int b_is_nk, int tile, int splits, void* workspace, size_t workspace_bytes, void* stream) {
     if (!a || !b || !c) return ATTN_ERR_NULL_PTR;
     if (tile != 0 && tile != 64 && tile != 128 && tile != 256 && tile != 2564 && tile != 1284 && tile != 25616 && tile != 19216 && tile != 256416 && tile != 12816 && tile != 128416 && tile != 6416) return ATTN_ERR_UNSUPPORTED;
     if (M <= 0 || N <= 0 || K <= 0) return ATTN_ERR_BAD_SHAPE;
@@ -29,7 +29,34 @@ extern "C" int gemm_bf16_tile(const void* a, const void* b, void* c, int M, int 
     p.M = M; p.N = N; p.K = K;
     p.lda = lda; p.ldb = ldb; p.ldc = ldc;
     p.tiles_m = 0; p.tiles_n = 0;
+    p.splits = 1; p.split_stages = 0; p.part = nullptr;
+    if (aligned && small_pitch && workspace) {
+        const GemmPlan plan = gemm_plan(M, N, K, tile, splits);
+        if (plan.splits > 1 && workspace_bytes >= gemm_plan_bytes(M, N, plan)) {
+            tile = plan.tile;
+            p.splits = plan.splits;
+            p.part = (float*)workspace;
+        }
+    }
     return gemm_launch(p, b_is_nk != 0, aligned && small_pitch, tile, (hipStream_t)stream) == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
+}
+
+extern "C" int gemm_bf16_tile(const void* a, const void* b, void* c, int M, int N, int K,
+                              long long lda, long long ldb, long long ldc, int b_is_nk, int tile, void* stream) {
+    return gemm_bf16_impl(a, b, c, M, N, K, lda, ldb, ldc, b_is_nk, tile, 1, nullptr, 0, stream);
+}
+
+extern "C" size_t gemm_bf16_workspace_bytes(int M, int N, int K) {
+    if (M <= 0 || N <= 0 || K <= 0 || ((N | K) & 7)) return 0;
+    return gemm_plan_bytes(M, N, gemm_plan(M, N, K, 0, 0));
+}
+
+extern "C" int gemm_bf16_workspace(const void* a, const void* b, void* c, int M, int N, int K,
+                                   long long lda, long long ldb, long long ldc, int b_is_nk, int tile, int splits,
+                                   void* workspace, size_t workspace_bytes, void* stream) {
+    if (splits < 0 || splits > kMaxGemmSplits) return ATTN_ERR_UNSUPPORTED;
+    if ((uintptr_t)workspace & 15u) return ATTN_ERR_MISALIGNED;
+    return gemm_bf16_impl(a, b, c, M, N, K, lda, ldb, ldc, b_is_nk, tile, splits, workspace, workspace_bytes, stream);
 }
 
 extern "C" int gemm_bf16(const void* a, const void* b, void* c, int M, int N, int K,

@@ -57,10 +57,16 @@ __global__ __launch_bounds__(T::kWaves * 64, T::kWaves >= 4 ? T::kPerCU : 1) voi
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % T::WM, wn = wave / T::WM;
 
-    const TileCoord tc = tile_coord(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n);
+    // k cut over workgroups (p.splits > 1): split `split` of every tile takes stages U0 .. U0 + nK - 1, and everything
+    // below sees a product that starts there; the workgroups of one split are neighbours, as they share the panels
+    const int tiles = p.tiles_m * p.tiles_n;
+    const int split = p.splits == 1 ? 0 : (int)blockIdx.x / tiles;
+    const TileCoord tc = tile_coord((int)blockIdx.x - split * tiles, tiles, p.tiles_m, p.tiles_n);
     const int m0 = tc.tm * kBM, n0 = tc.tn * kBN;
-    const int M = p.M, N = p.N, K = p.K;
-    const int nK = (K + kBK - 1) / kBK;
+    const int M = p.M, N = p.N;
+    const int U0 = split * p.split_stages;
+    const int K = p.K - U0 * kBK;
+    const int nK = min((K + kBK - 1) / kBK, p.split_stages);
     const unsigned lds_base = (unsigned)(size_t)LDS_PTR(char, smem);
     const unsigned a_rb = 2u * (unsigned)p.lda, b_rb = 2u * (unsigned)p.ldb;   // row pitches in bytes
 
@@ -86,8 +92,9 @@ __global__ __launch_bounds__(T::kWaves * 64, T::kWaves >= 4 ? T::kPerCU : 1) voi
             b_off[n] = (unsigned)nt_dma_row<RB>(i, lane) * b_rb + 2u * (unsigned)col;
         }
     }
-    const char* const a_base = (const char*)(p.a + (long long)m0 * p.lda);
-    const char* const b_base = B_NK ? (const char*)(p.b + (long long)n0 * p.ldb) : (const char*)(p.b + n0);
+    const char* const a_base = (const char*)(p.a + (long long)m0 * p.lda + (long long)U0 * kBK);
+    const char* const b_base = B_NK ? (const char*)(p.b + (long long)n0 * p.ldb + (long long)U0 * kBK)
+                                    : (const char*)(p.b + (long long)U0 * kBK * p.ldb + n0);
 
     // one copy instruction: j < kCopiesA part j of A, else part j-kCopiesA of B, of stage U into LDS stage `buf`
     const unsigned lds_copy_base = lds_base + w4 * 1024;   // instruction i = w4 + kCopiers n lands at i * 1024
@@ -356,6 +363,26 @@ __global__ __launch_bounds__(T::kWaves * 64, T::kWaves >= 4 ? T::kPerCU : 1) voi
 
     // ---- epilogue: C^T fragments -> bf16 -> this wavefront's 128 x 64 staging tile -> 16-byte stores ----
     // (no copy is in flight: the last stage was awaited before it was read)
+    if (p.splits > 1) {                              // this split's part of the sum, in fp32
+        float* const part = p.part + ((long long)split * M + m0 + wm * kWaveM) * N + (n0 + wn * kWaveN);
+        auto put4 = [&](int m, int n, float x, float y, float z, float w) __attribute__((always_inline)) {
+            if (m0 + wm * kWaveM + m < M && n0 + wn * kWaveN + n < N) *(f32x4*)(part + (long long)m * N + n) = f32x4{x, y, z, w};
+        };
+#pragma unroll
+        for (int in = 0; in < kRN; ++in)
+#pragma unroll
+            for (int jm = 0; jm < kRM; ++jm) {
+                if constexpr (MI16) {
+                    put4(jm * 16 + mfma16_rc(lane), in * 16 + mfma16_out_row(lane, 0), acc[in][jm][0], acc[in][jm][1], acc[in][jm][2], acc[in][jm][3]);
+                } else {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        put4(jm * 32 + mfma_rc(lane), in * 32 + mfma_out_row(lane, 4 * g), acc[in][jm][4 * g], acc[in][jm][4 * g + 1], acc[in][jm][4 * g + 2],
+                             acc[in][jm][4 * g + 3]);
+                }
+            }
+        return;
+    }
     char* const stage = smem + wave * (kWaveM * 128);
     if constexpr (MI16) {
 #pragma unroll
@@ -453,18 +480,41 @@ __global__ __launch_bounds__(256) void gemm_bf16_general(GemmParams p) {
         }
 }
 
+// Sum of the parts of a product whose k was cut: four columns per thread, the parts in order, one rounding.
+__global__ __launch_bounds__(256) void gemm_split_sum(GemmParams p) {
+    const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4, total = (long long)p.M * p.N;
+    if (i >= total) return;
+    f32x4 v[4];
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < p.splits; s0 += 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = *(const f32x4*)(p.part + min(s0 + j, p.splits - 1) * total + i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) if (s0 + j < p.splits) sum += v[j];
+    }
+    const int m = (int)(i / p.N), n = (int)(i - (long long)m * p.N);
+    *(u32x2*)(p.c + (long long)m * p.ldc + n) = u32x2{pack_bf16x2(sum[0], sum[1]), pack_bf16x2(sum[2], sum[3])};
+}
+
 }  // namespace
 
 template <class T>
 static void launch_tiled(GemmParams p, int b_is_nk, hipStream_t stream) {
     p.tiles_m = (p.M + T::BM - 1) / T::BM;
     p.tiles_n = (p.N + T::BN - 1) / T::BN;
-    const dim3 grid((unsigned)(p.tiles_m * p.tiles_n)), block(T::kWaves * 64);
+    const int stages = (p.K + T::BK - 1) / T::BK;
+    p.split_stages = (stages + p.splits - 1) / p.splits;
+    p.splits = (stages + p.split_stages - 1) / p.split_stages;      // every split has work
+    const dim3 grid((unsigned)(p.tiles_m * p.tiles_n * p.splits)), block(T::kWaves * 64);
     const bool ktail = (p.K % T::BK) != 0;
 #define GEMM_LAUNCH_TILED(NK, KT) hipLaunchKernelGGL((gemm_bf16_tiled<T, NK, KT>), grid, block, 0, stream, p)
     if (b_is_nk) { if (ktail) GEMM_LAUNCH_TILED(true, true); else GEMM_LAUNCH_TILED(true, false); }
     else         { if (ktail) GEMM_LAUNCH_TILED(false, true); else GEMM_LAUNCH_TILED(false, false); }
 #undef GEMM_LAUNCH_TILED
+    if (p.splits > 1) {
+        const long long quads = ((long long)p.M * p.N + 3) / 4;
+        hipLaunchKernelGGL(gemm_split_sum, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, p);
+    }
 }
 
 // Tile-size choice: the shape that promises the most throughput, estimated as (what the shape delivers when
@@ -487,6 +537,46 @@ int gemm_auto_tile(int M, int N) {
         const double useful = (double)M * (double)N / ((double)tiles * sh.edge_m * sh.edge_n);   // edge tiles compute padding
         const double rate = sh.peak * useful * (double)tiles / (double)(rounds * sh.slots);
         if (rate > best_rate) { best_rate = rate; best = sh.tile; }
+    }
+    return best;
+}
+
+// Whether to cut k over workgroups, and how: the least estimated time in microseconds, against the uncut product in
+// gemm_auto_tile's shape, which stays unless the cut promises an eighth less.  Measured (B stored [N,K], its memory cold):
+// a workgroup's 64-deep stage takes, with one workgroup per CU and with every slot taken, 0.28 / 0.42 us on 64 x 64
+// tiles, 0.50 / 0.57 on 128 x 128 tiles in four stages, 0.88 / 1.06 on them in two, 1.5 on 256 x 256 tiles; start and
+// end 3 us; the operands arrive at 5.1 TB/s at most (3.6 where two rows of 64 x 64 tiles read each weight); the sum of the parts costs 2.5 us and its traffic at 6 TB/s.
+// Uncut against cut, M N K: 1 1024 14336: 63.9 -> 11.2 us; 16 4096 4096: 21.4 -> 10.5; 128 4096 14336: 71.4 -> 34.0;
+// 256 256 10240: 45.2 -> 10.7; 1024 1024 8192: 40.6 -> 29.2.  Where the uncut product has its fill of workgroups or is
+// bound by its operands the parts only cost: 16 14336 4096: 27.1 against 30.2 in two; 2048 2048 2048: 21.3 against 32.2.
+GemmPlan gemm_plan(int M, int N, int K, int tile, int splits) {
+    GemmPlan best{tile ? tile : gemm_auto_tile(M, N), 1};
+    if (splits) { best.splits = splits; return best; }
+    const int stages = (K + 63) / 64;
+    if (tile || stages < 8) return best;
+    struct Shape { int tile, edge_m, edge_n, slots; double alone, full; };
+    static const Shape shapes[5] = {{64, 64, 64, 512, 0.28, 0.42}, {1284, 128, 128, 256, 0.50, 0.57}, {128, 128, 128, 512, 0.88, 1.06},
+                                    {25616, 256, 256, 256, 1.5, 1.5}, {19216, 192, 256, 256, 1.3, 1.3}};
+    const double results = (double)M * N, arrive = 2.0 * ((double)M * K + (double)N * K) / 5.1e6;
+    auto cost = [&](const Shape& sh, int s) {
+        const long long wgs = (long long)((M + sh.edge_m - 1) / sh.edge_m) * ((N + sh.edge_n - 1) / sh.edge_n) * s;
+        const long long rest = wgs % sh.slots;
+        const int per = (stages + s - 1) / s;
+        double t = (double)(wgs / sh.slots) * per * sh.full + (rest == 0 ? 0.0 : per * (rest <= 256 ? sh.alone : sh.full));
+        const double least_t = arrive * (sh.edge_m == 64 && M > 64 ? 1.4 : 1.0);
+        if (t < least_t) t = least_t;
+        return 3.0 + t + (s > 1 ? 2.5 + 8.0 * s * results / 6e6 : 0.0);
+    };
+    double least = 0.0;
+    for (const Shape& sh : shapes) if (sh.tile == best.tile) least = 0.875 * cost(sh, 1);
+    static const int cuts[] = {2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64};
+    for (const Shape& sh : shapes) {
+        if (sh.tile == 19216) continue;                      // (in the table as an uncut choice only)
+        for (int s : cuts) {
+            if (4 * s > stages) break;                       // a workgroup's start is paid for by at least four stages
+            const double t = cost(sh, s);
+            if (t < least) { least = t; best = GemmPlan{sh.tile, s}; }
+        }
     }
     return best;
 }
