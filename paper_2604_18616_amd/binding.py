@@ -158,9 +158,9 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     if stream is None:
         stream = current
     lib = load_library()
-    # few query rows: cut the keys over workgroups too, with torch's memory for the parts (only on the stream torch
+    # few query rows or few heads: cut the keys over workgroups too, with torch's memory for the parts (only on the stream torch
     # will reuse that memory on; elsewhere the call does without it)
-    need = lib.attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) if Sq <= 64 and stream.cuda_stream == current.cuda_stream else 0
+    need = lib.attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) if (Sq <= 64 or B * Hq * Sq <= 160 * 128) and stream.cuda_stream == current.cuda_stream else 0
     if need:
         ws = torch.empty(need, dtype=torch.uint8, device=q.device)
         rc = lib.attn_fwd_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),

@@ -48,9 +48,15 @@ static int attn_fwd_impl(const void* q, const void* k, const void* v, void* o, f
     p.nQt = 0; p.nblocks = 0; p.hpw = 1; p.hpw_log2 = 0;   // set by the launcher
     p.scale = scale;
     p.scale_log2 = (float)((double)scale * 1.4426950408889634074);
-    if (wg_rows == 0 && attn_split_fits(p)) {
+    const bool few = attn_split_sizes(Sq, Sk);
+    if (wg_rows == 0 && (few || (workspace && attn_split_pays(B, Hq, Hkv, Sq, Sk, D))) && attn_split_fits(p)) {
         AttnSplit sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, splits);
-        if (!workspace || workspace_bytes < attn_split_bytes(B, Hq, Sq, D, sp.splits)) sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 1);
+        const bool room = workspace && workspace_bytes >= attn_split_bytes(B, Hq, Sq, D, sp.splits);
+        if (!room) sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 1);
+        if (!few && sp.splits == 1) {                      // nothing to gain over the tiled kernel
+            const int trc = attn_launch(p, D, causal != 0, 0, (hipStream_t)stream);
+            return trc == 0 ? ATTN_OK : trc == -2 ? ATTN_ERR_BAD_SHAPE : ATTN_ERR_LAUNCH;
+        }
         const int src = attn_split_launch(p, D, causal != 0, sp, workspace, (hipStream_t)stream);
         return src == 0 ? ATTN_OK : src == -2 ? ATTN_ERR_BAD_SHAPE : ATTN_ERR_LAUNCH;
     }
@@ -78,7 +84,7 @@ extern "C" int attn_fwd_strided(const void* q, const void* k, const void* v, voi
 }
 
 extern "C" size_t attn_fwd_workspace_bytes(int B, int Hq, int Hkv, int Sq, int Sk, int D) {
-    if (check_dims(B, Hq, Hkv, Sq, Sk, D) || (D != 64 && D != 128) || !attn_split_sizes(Sq, Sk)) return 0;
+    if (check_dims(B, Hq, Hkv, Sq, Sk, D) || (D != 64 && D != 128) || !attn_split_pays(B, Hq, Hkv, Sq, Sk, D)) return 0;
     return attn_split_bytes(B, Hq, Sq, D, attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 0).splits);
 }
 

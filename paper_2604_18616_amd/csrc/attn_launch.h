@@ -24,18 +24,21 @@ struct AttnParams {
 // Returns 0, -1 if the runtime refused the launch, -2 if the grid would not fit 31 bits.
 int attn_launch(AttnParams p, int D, int causal, int wg_rows, hipStream_t stream);
 
-// Keys of one kv head cut over workgroups (attn_split_kernel.hip): the path of calls with few query rows.
+// Keys of one kv head cut over workgroups (attn_split_kernel.hip): the path of calls with few query rows or few heads.
 constexpr int kMaxSplits = 256;
 struct AttnSplit {
     int rb;            // 32-row blocks of packed query rows per workgroup: 1, 2 or 4
     int waves;         // wavefronts per workgroup: 4, or 2 (rb = 1)
     int row_wgs;       // workgroups along the packed query rows of a kv head
     int splits;        // workgroups along its keys
+    double cost;       // estimated time, microseconds
     float* part;       // [B*Hq*Sq, splits, D] unnormalised O of every split, relative to its own maximum
     float* ml;         // [B*Hq*Sq, splits, 2] that maximum (raw score units) and the row sum
 };
-// Whether the call's shape is one for that path.
+// Whether the call's shape is one for that path: with or without memory for parts (few query rows), or with it (a grid of
+// tiles that would leave most of the chip idle); and whether its strides are.
 bool attn_split_sizes(int Sq, int Sk);
+bool attn_split_pays(int B, int Hq, int Hkv, int Sq, int Sk, int D);
 bool attn_split_fits(const AttnParams& p);
 // Its cut; splits 0: by size.  Host arithmetic only.
 AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int splits);

@@ -1,4 +1,4 @@
-// Attention forward for few query rows (decoding, speculated tokens, short chunks) on gfx950: the keys, not the
+// Attention forward for few query rows or few heads (decoding, speculated tokens, chunks) on gfx950: the keys, not the
 // query rows, are what there is to spread over the chip.
 //
 // The query rows that share a kv head (g = Hq / Hkv heads x Sq positions) are packed into 32-row blocks, one block
@@ -421,13 +421,27 @@ bool attn_split_sizes(int Sq, int Sk) { return Sq <= 64 && Sk > 128; }
 
 bool attn_split_fits(const AttnParams& p) {
     const long long kv_ss = p.k_ss > p.v_ss ? p.k_ss : p.v_ss;
-    return attn_split_sizes(p.Sq, p.Sk) && ((long long)p.Sk + 64) * kv_ss * 2 < (1LL << 32);      // byte offsets inside a head in 32 bits
+    return ((long long)p.Sk + 64) * kv_ss * 2 < (1LL << 32);      // byte offsets inside a head in 32 bits
+}
+
+// More than 64 query positions: only where the tiled kernel's 128-row workgroups leave most CUs without one (up to 160 of
+// them on 256 CUs) and its time, 1.0 us (D 128) or 0.73 us (D 64) per 64 keys and 2 us, is clearly more than the cut's.
+// Measured, tiled -> cut, B Hq Hkv Sq Sk D causal: 1 1 1 2048 18000 128: 268 -> 41 us; 1 32 8 128 8192 128: 127 -> 41;
+// 1 8 1 1024 9000 128: 140 -> 60; 2 32 8 128 5000 128: 84 -> 42; 1 16 16 512 2500 128: 44 -> 30; 4 16 2 256 9000 128 (128
+// workgroups): 139 -> 100; 2 16 16 512 8000 64 (128): 92 -> 58.  With 256 of them the tiled kernel's larger tiles win:
+// 2 32 8 512 5000 128: 89 against 108; 8 32 8 100 2000 128: 40 against 55.
+bool attn_split_pays(int B, int Hq, int Hkv, int Sq, int Sk, int D) {
+    if (attn_split_sizes(Sq, Sk)) return true;
+    if (Sq <= 64 || Sk < 512 || (long long)B * Hq * ((Sq + 127) / 128) > 160) return false;
+    const AttnSplit sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 0);
+    return sp.splits > 1 && sp.cost < 0.85 * (2.0 + (Sk + 63) / 64 * (D == 128 ? 1.0 : 0.73));
 }
 
 // The cut with the least estimated time, in microseconds.  Measured: a step of a workgroup (one tile per key group;
 // 64 KB per CU at RB = 1) takes 1.3 us while HBM is no limit, which 128 CUs reach together, and 2.7 us with all CUs at
 // it; two workgroups of two wavefronts per CU hide each other's start and end, which pays from several rounds of them
-// on; with the row blocks sharing tiles 0.9 and 2.2 us; the combine costs 4 us, its traffic and its workgroups.
+// on; with two row blocks sharing tiles 0.9 and 2.2 us, with four 1.14 and 1.6 (D 128, two workgroups per CU; a third adds
+// nothing) or 0.75 and 1.5 (D 64, four per CU); the combine costs 4 us, its traffic and its workgroups.
 // Estimate against measurement at D = 128, B Hq Hkv Sq Sk: 32 32 8 1 4096: 88 / 92 us (one split); 16 32 8 1 1000:
 // 12 / 15 us (two splits: 16 / 18); 40 8 8 1 5000: 163 / 159 us with one split, 146 / 143 us with four.
 AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int splits) {
@@ -443,9 +457,9 @@ AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int spl
     double least = 1e300;
     for (int waves = 4; waves >= (best.rb == 1 ? 2 : 4); waves -= 2) {
         const int groups = waves / best.rb;
-        const long long slots = best.rb == 1 ? (D == 128 ? 1024 : 2048) / waves : best.rb == 2 ? 512 : 768;
-        const double start = waves == 2 ? 0.5 : 1.5, full = best.rb == 1 ? 2.7 : 2.2;
-        const double alone = best.rb > 1 ? 0.9 : waves == 2 ? 2.0 : 1.3;
+        const long long slots = best.rb == 1 ? (D == 128 ? 1024 : 2048) / waves : best.rb == 4 && D == 64 ? 1024 : 512;
+        const double start = waves == 2 ? 0.5 : 1.5, full = best.rb == 1 ? 2.7 : best.rb == 2 ? 2.2 : D == 128 ? 1.6 : 1.5;
+        const double alone = best.rb == 4 ? (D == 128 ? 1.14 : 0.75) : best.rb == 2 ? 0.9 : waves == 2 ? 2.0 : 1.3;
         const int most = (tiles + groups - 1) / groups;           // at least one tile per key group
         for (int s = splits ? splits : 1; s <= (splits ? splits : kMaxSplits) && (s == 1 || s <= most); s += s < 16 ? 1 : s >> 3) {
             const double steps = (double)((tiles + (long long)s * groups - 1) / ((long long)s * groups));
@@ -453,7 +467,7 @@ AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int spl
             const double step = full * part > alone ? full * part : alone;
             const double cost = (waves == 2 ? 1.5 : 0.0) + rounds * (start + steps * full) + (part > 0 ? start + steps * step : 0.0)
                               + (s > 1 ? 4.0 + rows * (s <= kFewSplits ? 0.0002 : 0.0013) + rows * s * (D + 2) * 1e-6 : 0.0);
-            if (cost < least) { least = cost; best.splits = s; best.waves = waves; }
+            if (cost < least) { least = cost; best.splits = s; best.waves = waves; best.cost = cost; }
         }
     }
     return best;
