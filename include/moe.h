@@ -61,9 +61,10 @@ int moe_ffn_fp8(const void *x, const int *ids, const float *wts,
  *   first_stage..last_stage  run only these stages (0 routing, 1 activation quantization, 2 gate/up product
  *       with SiLU and requantization, 3 down product, 4 combine); the stages before first_stage must have run
  *       on the same arguments, workspace and row_tile.  moe_ffn_fp8 is 0..4.
- *   row_tile  rows of one expert per workgroup of the two products: 64, 128, or 0 = what moe_ffn_fp8 does (128).
- *       An expert's rows are cut into tiles of row_tile rows and a remainder (an expert with row_tile + 1 ..
- *       row_tile + 32 rows gets a single tile); every tile runs the 64-, 128- or 160-row code that fits its rows.
+ *   row_tile  rows of one expert per workgroup of the two products: 64, 128, or 0 = what moe_ffn_fp8 does: one
+ *       tile for up to 160 rows, more rows evenly into the fewest tiles of at most 256.
+ *       For 64 and 128 an expert's rows are cut into tiles of row_tile rows and a remainder (an expert with row_tile + 1 ..
+ *       row_tile + 32 rows gets a single tile); every tile runs the code that fits its rows.
  * A stage range outside 0..4 or another row_tile: ATTN_ERR_UNSUPPORTED.
  */
 int moe_ffn_fp8_ex(const void *x, const int *ids, const float *wts,
@@ -106,8 +107,8 @@ int moe_ffn_fp8_static(const void *x, const int *ids, const float *wts,
  */
 long long moe_ffn_fp8_workspace_offset(int T, int H, int I, int E, int KTOP, int part);
 
-/* Row tiles (workgroups per column tile) an expert with `rows` routed rows is cut into for row_tile = 0, 64 or
- * 128 as in moe_ffn_fp8_ex: tiles of row_tile rows and a remainder, except that an expert with row_tile + 1 ..
+/* Row tiles (workgroups per column tile) an expert with `rows` routed rows is cut into for row_tile = 64 or
+ * 128 as in moe_ffn_fp8_ex (0 answers for 128): tiles of row_tile rows and a remainder, except that an expert with row_tile + 1 ..
  * row_tile + 32 rows gets a single tile.  -1 for a negative count or another row_tile.  Host-only helper. */
 int moe_ffn_fp8_row_tiles(int rows, int row_tile);
 

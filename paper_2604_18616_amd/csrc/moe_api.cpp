@@ -76,10 +76,11 @@ extern "C" int moe_ffn_fp8_ex(const void* x, const int* ids, const float* wts,
     p.w13 = (const uint8_t*)w13; p.s13 = s13; p.w2 = (const uint8_t*)w2; p.s2 = s2;
     p.y = (__bf16*)y;
     p.T = T; p.H = H; p.I = I; p.E = E; p.KTOP = KTOP;
-    // rows of one expert per row tile: 128 (a remainder of up to 32 rows joins the tile before it, and each tile
-    // runs the 64-, 128- or 160-row code that fits the rows it really has); `bm_override` is for tests
-    p.bm = bm_override ? bm_override : 128;
-    p.max_tiles = (int)(((size_t)T * KTOP + p.bm - 1) / p.bm + E);
+    // how an expert's rows are cut into tiles (moe_tiles); each tile runs the 64-, 128-, 160- or 256-row code that fits
+    // the rows it really has.  `bm_override` is for tests
+    p.bm = bm_override;
+    const int bound = p.bm ? p.bm : 128;                 // (the library's rule makes no more tiles than tiles of 128 rows would be)
+    p.max_tiles = (int)(((size_t)T * KTOP + bound - 1) / bound + E);
     // narrow column tiles of the down product are for problems whose wide tiles would not fill the chip: the grid is
     // sized for them only if the upper bound on the row tiles is small enough for that to be possible
     p.dn_narrow_ok = (long long)p.max_tiles * ((H + 255) / 256) < 4096 ? 1 : 0;

@@ -77,7 +77,7 @@ __device__ __forceinline__ void route_block(const MoeParams& p) {
             for (int w = 0; w < 16; ++w) { const int c = wcnt[w * 256 + tid]; wcnt[w * 256 + tid] = run; run += c; }
         cnt[tid] = run;
         rows_scan[tid] = run;
-        tiles_scan[tid] = moe_row_tiles(run, p.bm);
+        tiles_scan[tid] = moe_tiles(run, p.bm);
     }
     __syncthreads();
     for (int d = 1; d < 256; d <<= 1) {      // inclusive scans over the experts
@@ -88,7 +88,7 @@ __device__ __forceinline__ void route_block(const MoeParams& p) {
         __syncthreads();
     }
     if (tid < E) {
-        const int nt = moe_row_tiles(cnt[tid], p.bm);
+        const int nt = moe_tiles(cnt[tid], p.bm);
         const int start = rows_scan[tid] - cnt[tid], tstart = tiles_scan[tid] - nt;
         p.offsets[tid] = start;
         for (int w = 0; w < 16; ++w) wcnt[w * 256 + tid] += start;
@@ -165,9 +165,13 @@ __global__ __launch_bounds__(1024) void moe_prepare(MoeParams p, int stages) {
 
 // ------------------------------------------------------------------------------------
 // Grouped block-scaled FP8 product.  Workgroup = 8 wavefronts = 4 (n) x 2 (m) for the MFMAs: 256 weight rows x
-// BM routed rows.  An expert's rows are cut into tiles of p.bm (128 unless the caller asks for 64) and a
-// remainder (moe_row_tiles: an expert with bm + 1 .. bm + 32 rows gets one tile); each workgroup picks
-// the code for BM = 64, 128 or 160 from the rows its tile really has.
+// BM routed rows.  An expert's rows are cut into one tile of up to 160, or evenly into the fewest of up to 256 rows
+// (moe_tiles; a caller may ask for tiles of 128 or 64); each workgroup picks the code for BM = 64, 128, 160 or 256 from
+// the rows its tile really has.  Up to 160 rows the weights come from HBM for that one tile and three LDS stages cover
+// the latency.  From there on the copies L2 -> LDS bound it (10 TB/s over the chip): a 256-row tile, whose 64 KB stages
+// fit twice, copies a third less per product than two of 128.  Gate/up + down, us, 128-row against 256-row tiles: 256
+// rows per expert (7168 x 2048, 32 experts) 771 -> 681; 2048 rows (4096 x 14336, 8 experts) 3587 -> 3099 (1860 TFLOP/s);
+// 192 rows (2048 x 1408, 64 experts) 229 -> 192; 512 rows (2048 x 768, 128 experts) 643 -> 548.
 // Wavefront (wn, wm): weight rows 64 wn .. +63 as two 32-row MFMA operands, routed rows
 // (BM/2) wm .. in the lanes, BM/64 blocks of 32 (transposed product, as in the bf16 GEMM).
 //   UP:  the 256 weight rows of column tile nt are, per wavefront, 32 gate rows j and the 32 up
@@ -188,14 +192,14 @@ typedef __attribute__((address_space(3))) float* LdsFloat;    // turn the scale 
 template <bool UP, int BM, int BN>
 __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row0, int rows, int nt, LdsChar smem, LdsFloat sa_stage, LdsFloat sb_tab) {
     static_assert(BN == 256 || (BN == 128 && !UP), "the gate/up product pairs two 32-row weight blocks per wavefront");
-    constexpr int NS = 3;                           // LDS stages
+    constexpr int NS = BM == 256 ? 2 : 3;           // LDS stages: what 160 KB hold
     constexpr int NIN = BN / 128;                   // 32-row weight blocks per wavefront (wavefront wn: weight rows 32 NIN wn ..)
     constexpr int NCB = BN / 32;                    // copy instructions of the weights per copying wavefront and stage
     constexpr int kStageA = BM * 128, kStageB = BN * 128, kStage = kStageA + kStageB;
+    constexpr int kOffB = NS * kStageA;             // all stages of the routed rows, then the weights': read offsets fit an instruction's 16 bits
     static_assert(NS * kStage <= kMoeLdsBytes, "stages exceed the workgroup's LDS");
     constexpr int NCA = BM / 32;                    // copy instructions of the routed rows per copying wavefront and stage
-    constexpr int kW0 = BM == 160 ? 96 : BM / 2;    // routed rows of the wavefronts wm = 0; wm = 1 takes the rest
-    constexpr int MB = BM == 160 ? 3 : BM / 64;     // 32-row blocks of routed rows per wavefront (BM = 160: the third only for wm = 0)
+    constexpr int MB = BM == 160 ? 3 : BM / 64;     // 32-row blocks of routed rows per wavefront, at most
     constexpr int RPW = BM / 8;                     // routed rows per row group: a group's scales are one dword copy per stage
     static_assert(RPW <= 32, "a row group's scales fill at most the 32 dwords of its slot");
     constexpr int kCopies = NCA + NCB + 2;          // vmem operations per copying wavefront and stage
@@ -209,6 +213,10 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 3, wm = wave >> 2;
     const int half = lane >> 5;
+    // 32-row blocks of routed rows: the wavefronts wm = 0 take the first half (and the odd one), wm = 1 the rest; BM = 256
+    // has the blocks its rows need, the others all of theirs
+    const int blocks = BM == 256 ? (rows + 31) >> 5 : BM / 32;
+    const int blocks0 = (blocks + 1) >> 1, kW0 = 32 * blocks0, my_blocks = wm == 0 ? blocks0 : blocks - blocks0;
 
     const int KB = UP ? p.H : p.I;                  // bytes (= elements) per row of both operands
     const int nK = KB >> 7;
@@ -222,7 +230,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     // already in flight, so lines touched early are evicted before the copies ask for them.) ----
     const bool copier = wave < 4;
     const int c4 = wave & 3;
-    unsigned a_off[NCA], b_off[NCB], s_off[2];
+    unsigned a_off[NCA], b_off, s_off[2];
     {
 #pragma unroll
         for (int n = 0; n < NCA; ++n) {
@@ -230,35 +238,36 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
             const int r = min(kt_dma_row(i, lane), rows - 1);         // rows past the tile re-read its last row
             const int src = UP ? p.sorted_tok[row0 + r] : row0 + r;
             a_off[n] = (unsigned)src * (unsigned)KB + 16u * (unsigned)kt_dma_chunk(i, lane);
+            asm("" : "+v"(a_off[n]));               // one register: the 64-bit product would be kept whole
         }
-#pragma unroll
-        for (int n = 0; n < NCB; ++n) {
-            const int i = c4 + 4 * n, tr = kt_dma_row(i, lane);
-            int wrow;
-            if (UP) wrow = ((tr & 63) >> 5) * p.I + nt * 128 + ((tr >> 6) << 5) + (tr & 31);
-            else wrow = min(nt * BN + tr, p.H - 1);                   // rows past H re-read the last one
-            b_off[n] = (unsigned)wrow * (unsigned)KB + 16u * (unsigned)kt_dma_chunk(i, lane);
-        }
+        // (the weight rows of copy n lie a wavefront-uniform number of rows, w_rows(n), behind those of copy 0)
+        b_off = (unsigned)kt_dma_row(c4, lane) * (unsigned)KB + 16u * (unsigned)kt_dma_chunk(c4, lane);
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
             const int r = min(RPW * (c4 + 4 * n) + (lane % RPW), rows - 1);
             const int src = UP ? p.sorted_tok[row0 + r] : row0 + r;
             s_off[n] = 4u * (unsigned)src * (unsigned)nK;
+            asm("" : "+v"(s_off[n]));
         }
     }
     const char* const a_base = UP ? (const char*)p.xq : (const char*)p.aq;
     const char* const b_base = UP ? (const char*)(p.w13 + (size_t)e * 2 * (size_t)p.I * (size_t)p.H)
                                   : (const char*)(p.w2 + (size_t)e * (size_t)p.H * (size_t)p.I);
+    // first weight row of copies n of the four copying wavefronts: 32 rows of the tile
+    auto w_rows = [&](int n) __attribute__((always_inline)) {
+        return UP ? (n & 1) * p.I + nt * 128 + 32 * (n >> 1) : (nt * BN + 32 * n < p.H ? nt * BN + 32 * n : nt * BN);   // rows past H: others again
+    };
     const char* const s_base = UP ? (const char*)p.xs : (const char*)p.as;
     const unsigned lds_copy_base = lds_base + c4 * 1024;
     const unsigned sa_base = (unsigned)(size_t)LDS_PTR(float, sa_stage) + c4 * 128;
     auto dma_stage = [&](int U, auto sc) __attribute__((always_inline)) {
         constexpr int s = decltype(sc)::value;
         static_for<0, NCA>([&](auto n) __attribute__((always_inline)) {
-            dma_to_lds_16B<s * kStage + n.value * 4096>(a_base + (size_t)U * 128, a_off[n.value], lds_copy_base);
+            if (BM == 256 && 8 * (c4 + 4 * n.value) >= rows) return;   // (two stages: waits are for everything, not for a count)
+            dma_to_lds_16B<s * kStageA + n.value * 4096>(a_base + (size_t)U * 128, a_off[n.value], lds_copy_base);
         });
         static_for<0, NCB>([&](auto n) __attribute__((always_inline)) {
-            dma_to_lds_16B<s * kStage + kStageA + n.value * 4096>(b_base + (size_t)U * 128, b_off[n.value], lds_copy_base);
+            dma_to_lds_16B<kOffB + s * kStageB + n.value * 4096>(b_base + (size_t)w_rows(n.value) * KB + (size_t)U * 128, b_off, lds_copy_base);
         });
         if (lane < 32) {                            // a slot holds 32 dwords: the upper half of the wavefront stays out
             dma_to_lds_4B<s * kSaBytes>(s_base + (size_t)U * 4, s_off[0], sa_base);
@@ -284,7 +293,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             a_addr[ks][q] = lds_base + kt_offset(kW0 * wm + (lane & 31), 4 * ks + 2 * half + q);
-            b_addr[ks][q] = lds_base + kStageA + kt_offset(32 * NIN * wn + (lane & 31), 4 * ks + 2 * half + q);
+            b_addr[ks][q] = lds_base + kOffB + kt_offset(32 * NIN * wn + (lane & 31), 4 * ks + 2 * half + q);
         }
     // row scale of routed row m of the tile: dword m % RPW of row group m / RPW
     int sa_idx[MB];
@@ -353,14 +362,10 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
         const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         i32x8 fb[NIN][2];
         static_for<0, NIN>([&](auto in) __attribute__((always_inline)) {
-            fb[in.value][0] = frag(b_addr[0][0], b_addr[0][1], s * kStage + in.value * 4096);
-            fb[in.value][1] = frag(b_addr[1][0], b_addr[1][1], s * kStage + in.value * 4096);
+            fb[in.value][0] = frag(b_addr[0][0], b_addr[0][1], s * kStageB + in.value * 4096);
+            fb[in.value][1] = frag(b_addr[1][0], b_addr[1][1], s * kStageB + in.value * 4096);
         });
-        static_for<0, MB>([&](auto mb) __attribute__((always_inline)) {
-            if (BM == 160 && mb.value == 2 && wm != 0) return;        // rows 160..191 do not exist
-            const float sa = sa_stage[s * (kSaBytes / 4) + sa_idx[mb.value]];
-            const i32x8 fa0 = frag(a_addr[0][0], a_addr[0][1], s * kStage + mb.value * 4096);
-            const i32x8 fa1 = frag(a_addr[1][0], a_addr[1][1], s * kStage + mb.value * 4096);
+        auto multiply = [&](auto mb, i32x8 fa0, i32x8 fa1, float sa) __attribute__((always_inline)) {
             static_for<0, NIN>([&](auto in) __attribute__((always_inline)) {
                 f32x16 part = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[in.value][0], fa0, zero, 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
                 part = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[in.value][1], fa1, part, 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
@@ -368,7 +373,33 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[in.value][mb.value][r] = fmaf(part[r], f, acc[in.value][mb.value][r]);
             });
-        });
+        };
+        auto row_scale = [&](int mb) __attribute__((always_inline)) { return sa_stage[s * (kSaBytes / 4) + (RPW == 32 ? sa_idx[0] + 32 * mb : sa_idx[mb])]; };
+        if constexpr (BM == 256) {
+            // 128 accumulators leave room for two blocks of routed rows: each is read one block ahead (a block that does
+            // not exist too: its memory does), and the fences keep the compiler from reading all four first
+            i32x8 fa[2][2];
+            float sa[2];
+            auto read_block = [&](auto mb) __attribute__((always_inline)) {
+                constexpr int set = decltype(mb)::value & 1;
+                sa[set] = row_scale(mb.value);
+                fa[set][0] = frag(a_addr[0][0], a_addr[0][1], s * kStageA + mb.value * 4096);
+                fa[set][1] = frag(a_addr[1][0], a_addr[1][1], s * kStageA + mb.value * 4096);
+                asm volatile("" ::: "memory");
+            };
+            read_block(IntC<0>{});
+            static_for<0, MB>([&](auto mb) __attribute__((always_inline)) {
+                if constexpr (mb.value + 1 < MB) read_block(IntC<mb.value + 1>{});
+                if (mb.value < my_blocks) multiply(mb, fa[mb.value & 1][0], fa[mb.value & 1][1], sa[mb.value & 1]);      // uniform
+            });
+        } else {
+            static_for<0, MB>([&](auto mb) __attribute__((always_inline)) {
+                if (BM == 160 && mb.value >= my_blocks) return;            // uniform: rows 160..191 do not exist
+                const i32x8 fa0 = frag(a_addr[0][0], a_addr[0][1], s * kStageA + mb.value * 4096);
+                const i32x8 fa1 = frag(a_addr[1][0], a_addr[1][1], s * kStageA + mb.value * 4096);
+                multiply(mb, fa0, fa1, row_scale(mb.value));
+            });
+        }
     };
     for (int U = 0;;) {
         step(U, IntC<0>{}); if (++U >= nK) break;
@@ -405,6 +436,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
         barrier();
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
+            if (mb >= my_blocks) break;
             float am = amax[mb];
 #pragma unroll
             for (int w = 0; w < 4; ++w) am = fmaxf(am, ex[((wm * MB + mb) * 4 + w) * 32 + (lane & 31)]);
@@ -433,7 +465,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const int m = kW0 * wm + 32 * mb + (lane & 31);
-            if (m < rows) {
+            if (mb < my_blocks && m < rows) {
                 const int dst = __float_as_int(hand[2 * m]);
                 const float w = hand[2 * m + 1];
 #pragma unroll
@@ -470,35 +502,38 @@ __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
     // expert; inside an expert column tile by column tile, the expert's row tiles innermost: neighbours
     // share their weight tile (same nt) or their routed rows (same mt), which the XCD's L2 then
     // fetches once.
-    // Down product: column tiles of 256 weight rows, or of 128 when the wide ones would not give every CU a
-    // workgroup (few experts in use, or a small H: 8 experts of 4096 x 14336 make 128 wide tiles).  The host
-    // sizes the grid for the narrow tiles when the problem is small enough for that to happen (p.dn_narrow_ok);
-    // the choice itself needs the number of row tiles, known only here.  (With enough wide tiles the narrow ones
-    // are 3-15 % slower: measured.)
+    // Down product: column tiles of 256 weight rows, or of 128 when the wide ones would fill half the chip at most (few
+    // experts in use, or a small H: 8 experts of 4096 x 14336 make 128 wide tiles).  The host sizes the grid for the
+    // narrow tiles when the problem is small enough for that to happen (p.dn_narrow_ok); the choice itself needs the
+    // number of row tiles, known only here.  (With 128 to 256 wide tiles the narrow ones run two rounds of half the work
+    // at a lower rate; beyond, they are 3-15 % slower: measured.)
     const int ntl = p.ntiles[0];
-    const bool narrow = !UP && p.dn_narrow_ok && ntl * ((p.H + kMoeBN - 1) / kMoeBN) < 256;
+    const bool narrow = !UP && p.dn_narrow_ok && ntl * ((p.H + kMoeBN - 1) / kMoeBN) <= 128;
     const int NT = UP ? (p.I >> 7) : narrow ? (p.H >> 7) : (p.H + kMoeBN - 1) / kMoeBN;
     const int live = ntl * NT, per_xcd = (live + 7) >> 3;
     const int bid = blockIdx.x;
     const int logical = (bid & 7) * per_xcd + (bid >> 3);
     if ((bid >> 3) >= per_xcd || logical >= live) return;   // uniform: before any barrier
     const MoeTileRec rec = p.tile_rec[logical / NT];             // the expert whose block of ids holds `logical`
-    const int cnt = moe_row_tiles(rec.rows, p.bm);                // its row tiles; the last takes what is left: up to bm + 32 rows
+    const int cnt = moe_tiles(rec.rows, p.bm);                    // its row tiles
     const int off = logical - rec.first * NT;                     // in [0, cnt * NT)
     const int nt = off / cnt, j = off - nt * cnt;                 // column tile, row tile within the expert
-    const int e = rec.expert, row0 = rec.row0 + j * p.bm;
-    const int rows = j == cnt - 1 ? rec.rows - j * p.bm : p.bm;   // uniform
+    const int begin = moe_tile_begin(rec.rows, cnt, j, p.bm);
+    const int e = rec.expert, row0 = rec.row0 + begin;
+    const int rows = moe_tile_begin(rec.rows, cnt, j + 1, p.bm) - begin;   // uniform
     const LdsChar tiles = LDS_PTR(char, smem);
     const LdsFloat sa = LDS_PTR(float, sa_stage), sb = LDS_PTR(float, sb_tab);
     if constexpr (!UP) {
         if (narrow) {
-            if (rows > 128) moe_gemm_tile<false, 160, 128>(p, e, row0, rows, nt, tiles, sa, sb);
+            if (rows > 160) moe_gemm_tile<false, 256, 128>(p, e, row0, rows, nt, tiles, sa, sb);
+            else if (rows > 128) moe_gemm_tile<false, 160, 128>(p, e, row0, rows, nt, tiles, sa, sb);
             else if (rows > 64) moe_gemm_tile<false, 128, 128>(p, e, row0, rows, nt, tiles, sa, sb);
             else moe_gemm_tile<false, 64, 128>(p, e, row0, rows, nt, tiles, sa, sb);
             return;
         }
     }
-    if (rows > 128) moe_gemm_tile<UP, 160, 256>(p, e, row0, rows, nt, tiles, sa, sb);
+    if (rows > 160) moe_gemm_tile<UP, 256, 256>(p, e, row0, rows, nt, tiles, sa, sb);
+    else if (rows > 128) moe_gemm_tile<UP, 160, 256>(p, e, row0, rows, nt, tiles, sa, sb);
     else if (rows > 64) moe_gemm_tile<UP, 128, 256>(p, e, row0, rows, nt, tiles, sa, sb);
     else moe_gemm_tile<UP, 64, 256>(p, e, row0, rows, nt, tiles, sa, sb);
 }

@@ -15,7 +15,7 @@ struct MoeTileRec {
     int expert;               // the expert
     int row0;                 // its first sorted row
     int rows;                 // its number of rows
-    int first;                // index of its first row tile
+    int first;                // index of its first row tile (moe_tiles of them)
 };
 
 // Row tiles of an expert with cnt rows: tiles of bm rows and a remainder.  An expert with one full tile and
@@ -28,12 +28,24 @@ __host__ __device__ inline int moe_row_tiles(int cnt, int bm) {
     return (n == 1 && r <= 32) ? 1 : n + (r > 0 ? 1 : 0);
 }
 
+// The library's own rule (bm = 0): an expert with up to 160 rows gets one tile, more rows the fewest tiles of at most 256,
+// cut evenly at multiples of 32.
+__host__ __device__ inline int moe_tiles(int cnt, int bm) {
+    if (bm != 0) return moe_row_tiles(cnt, bm);
+    return cnt <= 160 ? (cnt > 0 ? 1 : 0) : (cnt + 255) / 256;
+}
+// First row of tile j of the n = moe_tiles(cnt, bm) of an expert; j = n gives its number of rows.
+__host__ __device__ inline int moe_tile_begin(int cnt, int n, int j, int bm) {
+    const int at = bm != 0 ? j * bm : (int)((long long)j * ((cnt + 31) / 32) / n) * 32;
+    return j >= n || at > cnt ? cnt : at;
+}
+
 struct MoeParams {
     const __bf16* x; const int* ids; const float* wts;
     const uint8_t* w13; const float* s13; const uint8_t* w2; const float* s2;
     __bf16* y;
     int T, H, I, E, KTOP;
-    int bm;                   // rows per tile for this call: 64 or 128
+    int bm;                   // rows per tile for this call: 64, 128, or 0 for the library's own rule
     int max_tiles;            // upper bound on the number of row tiles: ceil(T*KTOP / bm) + E
     int dn_narrow_ok;         // the grid of the down product is sized for 128-row column tiles (the kernel decides whether to use them)
     // workspace carve-up (all device pointers into the caller's workspace)

@@ -1,0 +1,47 @@
+"""moe_ffn_fp8 with the library's own row tiles (row_tile 0), against the fp64 reference with the stage-by-stage bounds of
+test_moe_parity_gpu: experts at the edges of the tile rules, where neither 64- nor 128-row tiles are forced."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2604_18616_amd import inputs as I
+from tests.test_moe_parity_gpu import check_routing, check_stage1, check_y, run, sanity_net
+
+pytestmark = pytest.mark.gpu
+
+
+def check_rows_per_expert(counts, H, Isz, twice=False):
+    """One call in which expert e gets counts[e] rows, a token each, or every token a second, shared choice (twice)."""
+    T, E = int(sum(counts)), len(counts) + int(twice)
+    w = I.MoeWorkload("t", T, 500 + T, H=H, I=Isz, E=E, KTOP=1 + int(twice), EP=1)
+    d = I.make_moe(w)
+    first = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
+    np.random.default_rng(T).shuffle(first)
+    d["ids"] = np.ascontiguousarray(np.stack([first] + ([np.full(T, E - 1, np.int32)] if twice else []), axis=1))
+    print("moe tiles", counts, H, Isz, twice, flush=True)
+    g = run(d)
+    check_routing(w, d, g)
+    order = np.argsort(g["pos"][:, 0])                    # tokens in row order: the first, last and odd rows of every expert
+    ends = np.cumsum(counts)
+    rows = sorted({min(max(r, 0), T - 1) for e, n in zip(ends, counts) if n for r in (e - n, e - n + 31, e - n + 128, e - 33, e - 2, e - 1)})
+    tokens = [int(order[r]) for r in rows]
+    check_stage1(w, d, g, tokens)
+    check_y(w, d, g, tokens)
+    sanity_net(g["y"], oracle.moe_ref(**d), str(counts))
+
+
+# up to 160 rows one tile; 161 to 256 one tile of the 256-row code with 6 to 8 blocks of 32 rows; from 257 on tiles cut
+# evenly at multiples of 32.  H 384: a last wide column tile that is half empty, and narrow column tiles
+@pytest.mark.parametrize("H,Isz", [(256, 256), (384, 128)])
+@pytest.mark.parametrize("counts", [(160, 161), (192, 193, 1), (224, 225), (255, 256, 257), (512, 513), (300, 40), (700,)])
+def test_edges_of_the_tile_rule(counts, H, Isz):
+    check_rows_per_expert(counts, H, Isz)
+
+
+def test_wide_column_tiles_of_the_down_product():
+    """Enough experts that the down product keeps its wide column tiles, with 161 rows each."""
+    check_rows_per_expert((161,) * 24, 2816, 128)
+
+
+def test_tiles_with_two_local_slots():
+    check_rows_per_expert((170, 230), 256, 128, twice=True)
