@@ -129,9 +129,10 @@ __device__ __forceinline__ void quant_x_block(const MoeParams& p, unsigned block
     if (item >= (long long)p.T * cpt) return;
     const int t = (int)(item / cpt), g0 = (int)(item - (long long)t * cpt) * kQG;
     {   // tokens without a local slot are never read by the products: skip them
-        bool local = false;
-        for (int k = 0; k < p.KTOP; ++k) { const int e = p.ids[t * p.KTOP + k]; local |= (e >= 0 && e < p.E); }
-        if (!local) return;
+        const int k = threadIdx.x & 31;                           // (at most 16 slots: one load of a lane each)
+        const int e = k < p.KTOP ? p.ids[t * p.KTOP + k] : -1;
+        const unsigned long long local = __builtin_amdgcn_ballot_w64(e >= 0 && e < p.E);
+        if ((unsigned)(threadIdx.x & 32 ? local >> 32 : local) == 0) return;
     }
     const int l = threadIdx.x & 31;
     u32x2 raw[kQG];
@@ -540,29 +541,53 @@ __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
 
 // ------------------------------------------------------------------------------------
 // Combine: y[t][c] = sum over local slots k (ascending) of wts[t][k] * o[pos[t][k]][c], bf16.  Tokens with exactly
-// one local slot were written by the down product.
+// one local slot were written by the down product; those with none get zeros.
+// What bounds it: y, mostly zeros where the experts are spread over ranks, and the rows of o.  A wavefront takes a token,
+// or one of `segs` interleaved parts of its columns where there are few tokens: the slots are one load of a lane each
+// (read one after the other they were a chain of KTOP round trips in each of 65536 short workgroups: 58 us for
+// T16384 H7168 with 137 MB to write and 75 MB to read, now 45), and up to four rows of o are in flight at once.
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void moe_combine(MoeParams p) {
-    const int cblocks = (p.H / 8 + 255) / 256;
-    const int t = blockIdx.x / cblocks;
-    const int c = ((blockIdx.x - t * cblocks) * 256 + threadIdx.x) * 8;
-    if (c >= p.H) return;
-    int nlocal = 0;
-    for (int k = 0; k < p.KTOP; ++k) nlocal += p.pos[t * p.KTOP + k] >= 0 ? 1 : 0;
+__global__ __launch_bounds__(256) void moe_combine(MoeParams p, int segs) {
+    const int lane = threadIdx.x & 63, item = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = item / segs, seg = item - t * segs;
+    if (t >= p.T) return;
+    const int pos = lane < p.KTOP ? p.pos[t * p.KTOP + lane] : -1;
+    const float wt = lane < p.KTOP ? p.wts[t * p.KTOP + lane] : 0.0f;
+    const unsigned long long local = __builtin_amdgcn_ballot_w64(pos >= 0);
+    const int nlocal = __popcll(local);
     if (nlocal == 1) return;
-    float acc[8] = {};
-    for (int k = 0; k < p.KTOP; ++k) {
-        const int r = p.pos[t * p.KTOP + k];
-        if (r < 0) continue;
-        const float w = p.wts[t * p.KTOP + k];
-        const f32x4 a = *(const f32x4*)(p.o + (size_t)r * p.H + c), b = *(const f32x4*)(p.o + (size_t)r * p.H + c + 4);
+    __bf16* const y = p.y + (size_t)t * p.H;
+    for (int c = seg * 512 + lane * 8; c < p.H; c += segs * 512) {
+        float acc[8] = {};
+        for (unsigned long long left = local; left != 0;) {
+            constexpr int NR = 4;
+            f32x4 a[NR], b[NR];
+            float w[NR];
+            int n = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { acc[i] = fmaf(w, a[i], acc[i]); acc[4 + i] = fmaf(w, b[i], acc[4 + i]); }
+            for (int j = 0; j < NR; ++j) {
+                if (left != 0) {                              // uniform
+                    const int k = __builtin_ctzll(left);
+                    left &= left - 1;
+                    w[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wt), k));
+                    const float* const o = p.o + (size_t)__builtin_amdgcn_readlane(pos, k) * p.H + c;
+                    a[j] = *(const f32x4*)o;
+                    b[j] = *(const f32x4*)(o + 4);
+                    n = j + 1;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (j < n) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { acc[i] = fmaf(w[j], a[j][i], acc[i]); acc[4 + i] = fmaf(w[j], b[j][i], acc[4 + i]); }
+                }
+        }
+        bf16x8 out;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) out[i] = (__bf16)acc[i];
+        *(bf16x8*)(y + c) = out;
     }
-    bf16x8 out;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) out[i] = (__bf16)acc[i];
-    *(bf16x8*)(p.y + (size_t)t * p.H + c) = out;
 }
 
 }  // namespace
@@ -603,6 +628,10 @@ int moe_launch(const MoeParams& p, int first, int last, hipStream_t stream) {
                g_dn = grid8((long long)p.max_tiles * (p.dn_narrow_ok ? p.H / 128 : (p.H + kMoeBN - 1) / kMoeBN));
     if (on(2)) hipLaunchKernelGGL((moe_gemm<true>), g_up, dim3(512), 0, stream, p);
     if (on(3)) hipLaunchKernelGGL((moe_gemm<false>), g_dn, dim3(512), 0, stream, p);
-    if (on(4)) hipLaunchKernelGGL(moe_combine, dim3((unsigned)(((p.H / 8 + 255) / 256) * p.T)), dim3(256), 0, stream, p);
+    if (on(4)) {
+        // parts of a token's columns: enough wavefronts for the chip (8192 slots) down to one pass of 512 columns each
+        const int most = (p.H + 511) / 512, want = (8192 + p.T - 1) / p.T, segs = want < most ? want : most;
+        hipLaunchKernelGGL(moe_combine, dim3((unsigned)(((long long)p.T * segs + 3) / 4)), dim3(256), 0, stream, p, segs);
+    }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

@@ -45,3 +45,15 @@ def test_wide_column_tiles_of_the_down_product():
 
 def test_tiles_with_two_local_slots():
     check_rows_per_expert((170, 230), 256, 128, twice=True)
+
+
+# the combine step: a token's columns in one to sixteen parts of 512, none / one / several local slots side by side
+@pytest.mark.parametrize("T,H,KTOP,EP", [(1, 128, 2, 1), (3, 640, 16, 2), (40, 1152, 7, 3), (5, 8320, 4, 1), (300, 512, 2, 2)])
+def test_combine_over_column_parts_and_slot_counts(T, H, KTOP, EP):
+    w = I.MoeWorkload("t", T, 900 + T, H=H, I=128, E=16, KTOP=KTOP, EP=EP)
+    d = I.make_moe(w)
+    print("combine", w, flush=True)
+    g = run(d)
+    check_routing(w, d, g)
+    check_y(w, d, g, list(range(min(T, 8))))
+    sanity_net(g["y"], oracle.moe_ref(**d), str(w))
