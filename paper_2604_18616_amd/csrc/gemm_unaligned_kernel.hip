@@ -11,9 +11,9 @@
 // seen before is zeroed on its way to LDS in both operands (0 x inf would be NaN), and columns a neighbouring tile owns
 // are not stored.  That needs K >= 64 and, for B stored [K,N], N >= BN.
 //
-// What bounds it: these products are small (below a few thousand in each direction), so the time is the chain of
-// stages of a workgroup (24 of 0.8 us for K = 1501, two workgroups per CU), not the matrix cores.  M999 N2001 K1501
-// [K,N]: 20.5 us, 252 us with the fp32 FMA kernel that served these sizes; M2001 N2001 K2001: 36 us (450 TFLOP/s).
+// What bounds it: the copies L2 -> registers, 36 to 40 bytes per ns and CU: M999 N2001 K1501 [K,N] on 64 x 64 tiles, two
+// workgroups per CU, reads 786 KB per CU in 20.5 us; on 256 tiles of 128 x 64 it is 590 KB and 18.6 us.  The fp32 FMA kernel
+// that served these sizes needed 252 us.  M2001 N2001 K2001 on 128 x 128 tiles: 35.6 us (450 TFLOP/s).
 #include <stdint.h>
 
 #include "gemm_layout.h"
@@ -41,6 +41,7 @@ template <int BM_, int BN_, int WM_, int WN_, int PF_> struct UTile {
     static_assert(kMB >= 1 && kNB >= 1 && kPA >= 1 && kPB >= 1 && (PF == 2 || PF == 4), "unsupported tile");
 };
 using USmall = UTile<64, 64, 2, 2, 4>;
+using UTall = UTile<128, 64, 2, 2, 4>;
 using ULarge = UTile<128, 128, 2, 2, 2>;
 
 // keep elements e >= z of the eight starting at element `first`
@@ -229,11 +230,18 @@ void launch_unaligned(GemmParams p, int b_is_nk, hipStream_t stream) {
 bool gemm_unaligned_sizes(int N, int K, int b_is_nk) { return K >= kUBK && (b_is_nk || N >= USmall::BN); }
 
 void gemm_unaligned_launch(const GemmParams& p, int b_is_nk, int tile, hipStream_t stream) {
-    // 128 x 128 tiles from the number of them on that keeps half the CUs busy.  Measured, 64 x 64 against 128 x 128 tiles,
-    // us, by the number of the latter: 121: 19.4 / 25.5; 128: 20.9 / 27.9; 144: 18.5 / 18.5 (K 801) and 45.1 / 42.3 (K 2499);
-    // 165: 38.0 / 35.7; 225: 24.0 / 18.6; 256: 49.7 / 36.1; 400: 98.9 / 64.9.
-    const long long large = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128);
-    if (tile == 0) tile = large >= 140 ? 128 : 64;
-    if (tile != 64 && (b_is_nk || p.N >= ULarge::BN)) launch_unaligned<ULarge>(p, b_is_nk, stream);
+    const auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
+    if (tile == 0) {
+        // The bytes of the busiest CU, tiles per CU x (rows + columns); 128 x 128 tiles hold two stages in registers instead
+        // of four and are charged 1.3 times theirs.  Measured, us, 64 x 64 / 128 x 64 / 128 x 128, M N K: 999 2001 1501:
+        // 20.5 / 19.1 / 27.7; 1201 1201 1201: 17.0 / 16.5 / 23.6; 101 1501 2201: 13.4 / 22.6 / 34.6; 1501 1501 2499:
+        // 45.0 / 46.4 / 41.6; 1801 1801 801: 23.7 / 20.9 / 18.5; 2001 2001 2001: 48.7 / 42.8 / 37.2; 2499 2499 2499:
+        // 98 / 88 / 65: the rule takes the fastest of the three on each.
+        const auto cost = [&](int bm, int bn) { return (double)((tiles(bm, bn) + 255) / 256 * (bm + bn)); };
+        const double small = cost(64, 64), tall = cost(128, 64), large = 1.3 * cost(128, 128);
+        tile = large < tall && large < small ? 128 : tall < small ? 1284 : 64;
+    }
+    if (tile == 1284) launch_unaligned<UTall>(p, b_is_nk, stream);
+    else if (tile != 64 && (b_is_nk || p.N >= ULarge::BN)) launch_unaligned<ULarge>(p, b_is_nk, stream);
     else launch_unaligned<USmall>(p, b_is_nk, stream);
 }

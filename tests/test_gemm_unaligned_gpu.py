@@ -14,7 +14,7 @@ CASES = [(1, 64, 64, (0, 1, 0), 1), (33, 65, 65, (0, 0, 0), 0), (64, 127, 127, (
          (257, 191, 320, (8, 0, 8), 1), (7, 77, 1000, (0, 0, 0), 0), (129, 385, 577, (0, 0, 2), 5), (96, 33, 201, (0, 0, 0), 0)]
 
 
-@pytest.mark.parametrize("tile", [64, 128, 0])
+@pytest.mark.parametrize("tile", [64, 128, 1284, 0])
 @pytest.mark.parametrize("b_is_nk", [False, True])
 @pytest.mark.parametrize("M,N,K,pad,shift", CASES)
 def test_unaligned_rows(M, N, K, pad, shift, b_is_nk, tile):
@@ -31,7 +31,7 @@ def test_infinities_stay_where_the_definition_puts_them(b_is_nk):
     A[3, 40] = np.inf                                  # k = 40: seen by the first stage and by the second
     B[50, 7] = -np.inf
     want = A.astype(np.float64) @ B.astype(np.float64)
-    for tile in (64, 128):
+    for tile in (64, 128, 1284):
         got = run(I.f32_to_bf16_bits(A), I.f32_to_bf16_bits(np.ascontiguousarray(B.T) if b_is_nk else B), b_is_nk, tile=tile)
         finite = np.isfinite(want)
         assert np.array_equal(np.isnan(got), np.isnan(want))
