@@ -118,8 +118,22 @@ def attn_fwd_raw(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, Hq, Hkv, Sq, Sk, D, cau
                         int(bool(causal)), float(scale), stream_ptr)
 
 
+_Int64x3 = ctypes.c_longlong * 3
+
+
 def _strides3(t):
-    return (ctypes.c_longlong * 3)(t.stride(0), t.stride(1), t.stride(2))
+    return _Int64x3(*t.stride()[:3])
+
+
+def _streams(t, stream):
+    """(handle to launch on, whether torch's memory for t's device may be used on it without keeping it alive).  Handles
+    instead of Stream objects: making one is a large part of the host time of a small call."""
+    import torch
+    current = torch._C._cuda_getCurrentRawStream(t.get_device())
+    if stream is None:
+        return current, True
+    handle = stream.cuda_stream
+    return handle, handle == current
 
 
 def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
@@ -135,45 +149,49 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
 
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
         raise ValueError("q, k, v must be CUDA tensors: there is no CPU path")
-    for t in (q, k, v):
-        if t.dtype != torch.bfloat16 or t.dim() != 4 or t.stride(3) != 1:
-            raise ValueError("q, k, v must be 4-D bfloat16 tensors with a contiguous last dimension")
-    B, Hq, Sq, D = q.shape
-    Bk, Hkv, Sk, Dk = k.shape
-    if v.shape != k.shape or Bk != B or Dk != D:
+    bf16 = torch.bfloat16
+    qst, kst, vst = q.stride(), k.stride(), v.stride()
+    if (q.dtype != bf16 or k.dtype != bf16 or v.dtype != bf16 or len(qst) != 4 or len(kst) != 4 or len(vst) != 4
+            or qst[3] != 1 or kst[3] != 1 or vst[3] != 1):
+        raise ValueError("q, k, v must be 4-D bfloat16 tensors with a contiguous last dimension")
+    qs, ks = q.shape, k.shape
+    B, Hq, Sq, D = qs
+    Bk, Hkv, Sk, Dk = ks
+    if v.shape != ks or Bk != B or Dk != D:
         raise ValueError("inconsistent q/k/v shapes")
+    device = q.device
     if o is None:
         o = torch.empty_like(q)          # keeps q's layout for dense views
-    if o.shape != q.shape or o.dtype != torch.bfloat16 or o.stride(3) != 1:
+    elif o.shape != qs or o.dtype != bf16:
+        raise ValueError("o must be bfloat16 with q's shape and a contiguous last dimension")
+    ost = o.stride()
+    if ost[3] != 1:
         raise ValueError("o must be bfloat16 with q's shape and a contiguous last dimension")
     if lse is None:
-        lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=q.device)
-    if not lse.is_cuda or lse.dtype != torch.float32 or tuple(lse.shape) != (B, Hq, Sq) or not lse.is_contiguous():
+        lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=device)
+    elif not lse.is_cuda or lse.dtype != torch.float32 or tuple(lse.shape) != (B, Hq, Sq) or not lse.is_contiguous():
         raise ValueError("lse must be a contiguous float32 CUDA tensor of shape [B, Hq, Sq]")
-    if not o.is_cuda or any(t.device != q.device for t in (k, v, o, lse)):
+    if k.device != device or v.device != device or o.device != device or lse.device != device:
         raise ValueError("q, k, v, o, lse must live on one CUDA device")
-    if scale is None:
-        scale = float(D) ** -0.5
-    current = torch.cuda.current_stream(q.device)
-    if stream is None:
-        stream = current
+    scale = float(D) ** -0.5 if scale is None else float(scale)
+    causal = 1 if causal else 0
+    stream, own = _streams(q, stream)
     lib = load_library()
     # few query rows or few heads: cut the keys over workgroups too, with torch's memory for the parts (only on the stream torch
     # will reuse that memory on; elsewhere the call does without it)
-    need = lib.attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) if (Sq <= 64 or B * Hq * Sq <= 160 * 128) and stream.cuda_stream == current.cuda_stream else 0
+    need = lib.attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) if own and (Sq <= 64 or B * Hq * Sq <= 160 * 128) else 0
     if need:
-        ws = torch.empty(need, dtype=torch.uint8, device=q.device)
+        ws = torch.empty(need, dtype=torch.uint8, device=device)
         rc = lib.attn_fwd_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
-                                    B, Hq, Hkv, Sq, Sk, D, _strides3(q), _strides3(k), _strides3(v), _strides3(o),
-                                    int(bool(causal)), float(scale), ws.data_ptr(), need,
-                                    need // (4 * B * Hq * Sq * (D + 2)), stream.cuda_stream)
-    elif all(t.is_contiguous() for t in (q, k, v, o)):
+                                    B, Hq, Hkv, Sq, Sk, D, _Int64x3(*qst[:3]), _Int64x3(*kst[:3]), _Int64x3(*vst[:3]), _Int64x3(*ost[:3]),
+                                    causal, scale, ws.data_ptr(), need, need // (4 * B * Hq * Sq * (D + 2)), stream)
+    elif q.is_contiguous() and k.is_contiguous() and v.is_contiguous() and o.is_contiguous():
         rc = lib.attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
-                          B, Hq, Hkv, Sq, Sk, D, int(bool(causal)), float(scale), stream.cuda_stream)
+                          B, Hq, Hkv, Sq, Sk, D, causal, scale, stream)
     else:
         rc = lib.attn_fwd_strided(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
-                                  B, Hq, Hkv, Sq, Sk, D, _strides3(q), _strides3(k), _strides3(v), _strides3(o),
-                                  int(bool(causal)), float(scale), stream.cuda_stream)
+                                  B, Hq, Hkv, Sq, Sk, D, _Int64x3(*qst[:3]), _Int64x3(*kst[:3]), _Int64x3(*vst[:3]), _Int64x3(*ost[:3]),
+                                  causal, scale, stream)
     if rc != 0:
         raise AttnError(rc, strerror(rc))
     return o, lse
@@ -196,22 +214,20 @@ def gemm_bf16(a, b, c=None, b_is_nk=False, stream=None, tile=0):
         raise ValueError("inner dimensions differ")
     if c is None:
         c = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
-    if c.shape != (M, N) or c.dtype != torch.bfloat16 or c.stride(1) != 1:
+    elif c.shape != (M, N) or c.dtype != torch.bfloat16 or c.stride(1) != 1:
         raise ValueError("c must be bfloat16 [M,N] with contiguous rows")
-    current = torch.cuda.current_stream(a.device)
-    if stream is None:
-        stream = current
+    stream, own = _streams(a, stream)
     lib = load_library()
     # results of few tiles: cut k over workgroups too, with torch's memory for the parts (only on the stream torch will
     # reuse that memory on; elsewhere the call does without it)
-    need = lib.gemm_bf16_workspace_bytes(M, N, K) if tile == 0 and stream.cuda_stream == current.cuda_stream else 0
+    need = lib.gemm_bf16_workspace_bytes(M, N, K) if tile == 0 and own else 0
     if need:
         ws = torch.empty(need, dtype=torch.uint8, device=a.device)
         rc = lib.gemm_bf16_workspace(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, a.stride(0), b.stride(0), c.stride(0),
-                                     int(bool(b_is_nk)), 0, 0, ws.data_ptr(), need, stream.cuda_stream)
+                                     1 if b_is_nk else 0, 0, 0, ws.data_ptr(), need, stream)
     else:
         rc = lib.gemm_bf16_tile(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, a.stride(0), b.stride(0), c.stride(0),
-                                int(bool(b_is_nk)), int(tile), stream.cuda_stream)
+                                1 if b_is_nk else 0, int(tile), stream)
     if rc != 0:
         raise AttnError(rc, strerror(rc))
     return c
@@ -251,13 +267,11 @@ def moe_ffn_fp8(x, ids, wts, w13, s13, w2, s2, y=None, workspace=None, stream=No
         y = torch.empty((T, H), dtype=torch.bfloat16, device=x.device)
     if not y.is_cuda or y.dtype != torch.bfloat16 or tuple(y.shape) != (T, H) or not y.is_contiguous():
         raise ValueError("y must be a contiguous bfloat16 CUDA tensor of shape [T, H]")
-    current = torch.cuda.current_stream(x.device)
-    if stream is None:
-        stream = current
+    stream, own = _streams(x, stream)
     if workspace is None:
         # a temporary is only safe on the stream torch will reuse its memory on: the kernels are still queued
         # when this function returns
-        if stream.cuda_stream != current.cuda_stream:
+        if not own:
             raise ValueError("pass a workspace when `stream` is not torch's current stream")
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
     if (not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous()
@@ -265,7 +279,7 @@ def moe_ffn_fp8(x, ids, wts, w13, s13, w2, s2, y=None, workspace=None, stream=No
         raise ValueError("workspace must be a contiguous uint8 CUDA tensor of at least moe_workspace_bytes(...) bytes, 256-byte aligned")
     rc = lib.moe_ffn_fp8_ex(x.data_ptr(), ids.data_ptr(), wts.data_ptr(), w13.data_ptr(), s13.data_ptr(), w2.data_ptr(),
                             s2.data_ptr(), y.data_ptr(), T, H, I, E, K, workspace.data_ptr(), workspace.numel(),
-                            0, 4, int(row_tile), stream.cuda_stream)
+                            0, 4, int(row_tile), stream)
     if rc != 0:
         raise AttnError(rc, strerror(rc))
     return y
