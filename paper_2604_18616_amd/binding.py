@@ -136,6 +136,15 @@ def _streams(t, stream):
     return handle, handle == current
 
 
+def _scratch(need, device):
+    """Torch memory for a call's parts; None where there is none left: such a call runs uncut, as it would without it."""
+    import torch
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     """O, LSE = attention forward of bf16 CUDA tensors q [B,Hq,Sq,D], k/v [B,Hkv,Sk,D].
 
@@ -180,8 +189,8 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     # few query rows or few heads: cut the keys over workgroups too, with torch's memory for the parts (only on the stream torch
     # will reuse that memory on; elsewhere the call does without it)
     need = lib.attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) if own and (Sq <= 64 or B * Hq * Sq <= 160 * 128) else 0
-    if need:
-        ws = torch.empty(need, dtype=torch.uint8, device=device)
+    ws = _scratch(need, device) if need else None
+    if ws is not None:
         rc = lib.attn_fwd_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
                                     B, Hq, Hkv, Sq, Sk, D, _Int64x3(*qst[:3]), _Int64x3(*kst[:3]), _Int64x3(*vst[:3]), _Int64x3(*ost[:3]),
                                     causal, scale, ws.data_ptr(), need, need // (4 * B * Hq * Sq * (D + 2)), stream)
@@ -221,8 +230,8 @@ def gemm_bf16(a, b, c=None, b_is_nk=False, stream=None, tile=0):
     # results of few tiles: cut k over workgroups too, with torch's memory for the parts (only on the stream torch will
     # reuse that memory on; elsewhere the call does without it)
     need = lib.gemm_bf16_workspace_bytes(M, N, K) if tile == 0 and own else 0
-    if need:
-        ws = torch.empty(need, dtype=torch.uint8, device=a.device)
+    ws = _scratch(need, a.device) if need else None
+    if ws is not None:
         rc = lib.gemm_bf16_workspace(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, a.stride(0), b.stride(0), c.stride(0),
                                      1 if b_is_nk else 0, 0, 0, ws.data_ptr(), need, stream)
     else:

@@ -49,6 +49,21 @@ def test_too_small_a_workspace_means_no_cut():
     assert np.array_equal(run_split(a, b, True, 64, 4, 0, given=4 * 64 * 64 * 4 - 16), run_split(a, b, True, 64, 1, 0))
 
 
+def test_no_memory_left_for_the_parts_means_no_cut(monkeypatch):
+    import torch
+    from paper_2604_18616_amd import attn_fwd, binding, gemm_bf16
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    randn = lambda *s: torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)
+    a, b = randn(16, 4096), randn(512, 4096)
+    q, k, v = randn(1, 2, 100, 128), randn(1, 2, 3000, 128), randn(1, 2, 3000, 128)
+    cut = gemm_bf16(a, b, b_is_nk=True), attn_fwd(q, k, v)[0]
+    monkeypatch.setattr(binding, "_scratch", lambda need, device: None)
+    whole = gemm_bf16(a, b, b_is_nk=True), attn_fwd(q, k, v)[0]
+    assert torch.equal(whole[0], gemm_bf16(a, b, b_is_nk=True, tile=64))
+    for x, y in zip(cut, whole):                          # both within a rounding to bf16 and, for P, one before the sum
+        assert (x.float() - y.float()).norm() <= 2.0 ** -7 * y.float().norm()
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1024, 2048), (100, 512, 4096), (256, 256, 2056), (512, 512, 4096)])
 def test_the_librarys_own_cut(M, N, K):
     from paper_2604_18616_amd import binding
