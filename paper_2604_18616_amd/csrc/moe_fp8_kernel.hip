@@ -18,7 +18,8 @@
 //                 two or more local slots; zeros for those with none.
 // With 16 to 256 rows per expert the products are bound by streaming the expert weights from
 // HBM (each byte is used for 2 x rows FLOPs), so the grouped product keeps three 40-52 KB stages
-// of direct-to-LDS copies per workgroup, two of them in flight, and does nothing clever with the MFMAs.
+// (two of 64 KB for tiles of more than 160 rows, which L2 -> LDS copies bound) of direct-to-LDS copies
+// per workgroup, all but one of them in flight, and does nothing clever with the MFMAs.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
