@@ -426,9 +426,9 @@ bool attn_split_fits(const AttnParams& p) {
 
 // More than 64 query positions: only where the tiled kernel's 128-row workgroups leave most CUs without one (up to 160 of
 // them on 256 CUs) and its time, 1.0 us (D 128) or 0.73 us (D 64) per 64 keys and 2 us, is clearly more than the cut's.
-// Measured, tiled -> cut, B Hq Hkv Sq Sk D causal: 1 1 1 2048 18000 128: 268 -> 41 us; 1 32 8 128 8192 128: 127 -> 41;
-// 1 8 1 1024 9000 128: 140 -> 60; 2 32 8 128 5000 128: 84 -> 42; 1 16 16 512 2500 128: 44 -> 30; 4 16 2 256 9000 128 (128
-// workgroups): 139 -> 100; 2 16 16 512 8000 64 (128): 92 -> 58.  With 256 of them the tiled kernel's larger tiles win:
+// Measured, tiled -> cut, B Hq Hkv Sq Sk D causal: 1 1 1 2048 18000 128: 268 -> 43 us; 1 32 8 128 8192 128: 126 -> 42;
+// 1 8 1 1024 9000 128: 138 -> 61; 2 32 8 128 5000 128: 80 -> 42; 1 16 16 512 2500 128: 46 -> 29; 4 16 2 256 9000 128 (128
+// workgroups): 139 -> 102; 2 16 16 512 8000 64 (128): 89 -> 63.  With 256 of them the tiled kernel's larger tiles win:
 // 2 32 8 512 5000 128: 89 against 108; 8 32 8 100 2000 128: 40 against 55.
 bool attn_split_pays(int B, int Hq, int Hkv, int Sq, int Sk, int D) {
     if (attn_split_sizes(Sq, Sk)) return true;
@@ -440,8 +440,8 @@ bool attn_split_pays(int B, int Hq, int Hkv, int Sq, int Sk, int D) {
 // The cut with the least estimated time, in microseconds.  Measured: a step of a workgroup (one tile per key group;
 // 64 KB per CU at RB = 1) takes 1.3 us while HBM is no limit, which 128 CUs reach together, and 2.7 us with all CUs at
 // it; two workgroups of two wavefronts per CU hide each other's start and end, which pays from several rounds of them
-// on; with two row blocks sharing tiles 0.9 and 2.2 us, with four 1.14 and 1.6 (D 128, two workgroups per CU; a third adds
-// nothing) or 0.75 and 1.5 (D 64, four per CU); the combine costs 4 us, its traffic and its workgroups.
+// on; with two row blocks sharing tiles 0.9 and 2.2 us, with four 1.0 with one workgroup per CU and 1.25 with two (D 128; a
+// third adds nothing) or 0.75 with up to two and 1.5 with four (D 64); the combine costs 4 us, its traffic and its workgroups.
 // Estimate against measurement at D = 128, B Hq Hkv Sq Sk: 32 32 8 1 4096: 88 / 92 us (one split); 16 32 8 1 1000:
 // 12 / 15 us (two splits: 16 / 18); 40 8 8 1 5000: 163 / 159 us with one split, 146 / 143 us with four.
 AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int splits) {
@@ -458,12 +458,15 @@ AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int spl
     for (int waves = 4; waves >= (best.rb == 1 ? 2 : 4); waves -= 2) {
         const int groups = waves / best.rb;
         const long long slots = best.rb == 1 ? (D == 128 ? 1024 : 2048) / waves : best.rb == 4 && D == 64 ? 1024 : 512;
-        const double start = waves == 2 ? 0.5 : 1.5, full = best.rb == 1 ? 2.7 : best.rb == 2 ? 2.2 : D == 128 ? 1.6 : 1.5;
-        const double alone = best.rb == 4 ? (D == 128 ? 1.14 : 0.75) : best.rb == 2 ? 0.9 : waves == 2 ? 2.0 : 1.3;
+        const double start = best.rb == 4 ? (D == 128 ? 5.0 : 3.0) : waves == 2 ? 0.5 : 1.5;
+        const double full = best.rb == 1 ? 2.7 : best.rb == 2 ? 2.2 : D == 128 ? 1.25 : 1.5;
+        const double alone = best.rb == 4 ? (D == 128 ? 1.0 : 0.75) : best.rb == 2 ? 0.9 : waves == 2 ? 2.0 : 1.3;
         const int most = (tiles + groups - 1) / groups;           // at least one tile per key group
         for (int s = splits ? splits : 1; s <= (splits ? splits : kMaxSplits) && (s == 1 || s <= most); s += s < 16 ? 1 : s >> 3) {
             const double steps = (double)((tiles + (long long)s * groups - 1) / ((long long)s * groups));
-            const double rounds = (double)(base * s / slots), part = (double)(base * s % slots) / (double)slots;
+            long long rest = base * s % slots;
+            if (best.rb == 4) rest = (rest + 255) / 256 * 256;        // the CUs with one workgroup more set the time
+            const double rounds = (double)(base * s / slots), part = (double)rest / (double)slots;
             const double step = full * part > alone ? full * part : alone;
             const double cost = (waves == 2 ? 1.5 : 0.0) + rounds * (start + steps * full) + (part > 0 ? start + steps * step : 0.0)
                               + (s > 1 ? 4.0 + rows * (s <= kFewSplits ? 0.0002 : 0.0013) + rows * s * (D + 2) * 1e-6 : 0.0);
