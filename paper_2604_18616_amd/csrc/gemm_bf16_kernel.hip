@@ -545,7 +545,8 @@ int gemm_auto_tile(int M, int N) {
 // gemm_auto_tile's shape, which stays unless the cut promises an eighth less.  Measured (B stored [N,K], its memory cold):
 // a workgroup's 64-deep stage takes, with one workgroup per CU and with every slot taken, 0.28 / 0.42 us on 64 x 64
 // tiles, 0.50 / 0.57 on 128 x 128 tiles in four stages, 0.88 / 1.06 on them in two, 1.5 on 256 x 256 tiles; start and
-// end 3 us; the operands arrive at 5.1 TB/s at most (3.6 where two rows of 64 x 64 tiles read each weight); the sum of the parts costs 2.5 us and its traffic at 6 TB/s.
+// end 3 us; the operands arrive at 5.1 TB/s at most (3.6 where two rows of 64 x 64 tiles read each weight); the sum of
+// the parts costs 2.5 us and its traffic at 6 TB/s.
 // Uncut against cut, M N K: 1 1024 14336: 63.9 -> 11.2 us; 16 4096 4096: 21.4 -> 10.5; 128 4096 14336: 71.4 -> 34.0;
 // 256 256 10240: 45.2 -> 10.7; 1024 1024 8192: 40.6 -> 29.2.  Where the uncut product has its fill of workgroups or is
 // bound by its operands the parts only cost: 16 14336 4096: 27.1 against 30.2 in two; 2048 2048 2048: 21.3 against 32.2.
