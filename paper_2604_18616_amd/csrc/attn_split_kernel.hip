@@ -461,8 +461,8 @@ AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int spl
         const double start = best.rb == 4 ? (D == 128 ? 5.0 : 3.0) : waves == 2 ? 0.5 : 1.5;
         const double full = best.rb == 1 ? 2.7 : best.rb == 2 ? 2.2 : D == 128 ? 1.25 : 1.5;
         const double alone = best.rb == 4 ? (D == 128 ? 1.0 : 0.75) : best.rb == 2 ? 0.9 : waves == 2 ? 2.0 : 1.3;
-        const int most = (tiles + groups - 1) / groups;           // at least one tile per key group
-        for (int s = splits ? splits : 1; s <= (splits ? splits : kMaxSplits) && (s == 1 || s <= most); s += s < 16 ? 1 : s >> 3) {
+        const int most = (tiles + groups - 1) / groups;           // at least one tile per key group, unless the caller asks for more parts
+        for (int s = splits ? splits : 1; s <= (splits ? splits : kMaxSplits) && (splits || s == 1 || s <= most); s += s < 16 ? 1 : s >> 3) {
             const double steps = (double)((tiles + (long long)s * groups - 1) / ((long long)s * groups));
             long long rest = base * s % slots;
             if (best.rb == 4) rest = (rest + 255) / 256 * 256;        // the CUs with one workgroup more set the time

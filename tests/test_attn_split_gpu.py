@@ -17,7 +17,11 @@ SHAPES = [
     (2, 2, 1, 32, 640, 128, True),       # 64
     (1, 5, 1, 13, 333, 128, False),      # 65: four row blocks
     (1, 6, 2, 64, 161, 64, True),        # 192 rows: two workgroups along the rows
-    (1, 1, 1, 1, 8300, 64, False),       # enough keys for every number of splits
+    (1, 1, 1, 1, 8300, 64, False),       # 130 parts of two tiles and empty ones, where 256 are asked for
+    (1, 2, 1, 1, 16500, 64, False),      # 172 of three
+    (1, 1, 1, 2, 33000, 128, False),     # 207 of five
+    (1, 8, 1, 4, 60000, 128, True),      # 157 parts of 12 tiles: the library's own cut is that fine
+    (128, 8, 8, 1, 1000, 64, False),     # D = 64, two wavefronts per workgroup
 ]
 
 
@@ -37,6 +41,10 @@ def call(q, k, v, causal, scale, splits, memory=True, lse=True):
                                 torch.cuda.current_stream().cuda_stream)
     assert rc == 0, binding.strerror(rc)
     torch.cuda.synchronize()
+    # the parts that ran: a cut call writes all of the memory it asks for, the surplus parts as empty ones; an uncut call none
+    cut = memory and (splits > 1 if splits else n > 0)
+    left = ws.view(torch.int32) == -1
+    assert not bool(left.any()) if cut else bool(left.all()), (q.shape, k.shape, splits)
     return o, ls
 
 

@@ -13,14 +13,17 @@ SHAPES = [
     (1, 2, 1, 130, 1500, 64, False),      # 260 packed rows: three blocks, the last with four rows
     (2, 2, 2, 257, 1029, 128, True),
     (1, 3, 1, 128, 1600, 128, True),      # whole blocks, a head each
-    (1, 1, 1, 900, 800, 64, True),        # the first 100 rows see no key
+    (1, 1, 1, 2000, 1500, 64, True),      # the first 500 rows see no key
+    (1, 1, 1, 1100, 1000, 128, True),     # the first 100
 ]
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "B%d_H%d_%d_S%d_%d_D%d_%s" % s)
 def test_long_queries_against_the_reference(shape):
+    from paper_2604_18616_amd import binding
     B, Hq, Hkv, Sq, Sk, D, causal = shape
+    assert binding.load_library().attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) > 0
     w = I.Workload("split", B, Hq, Hkv, Sq, Sk, D, causal, 47)
     qb, kb, vb = I.make_qkv(w)
     ref = oracle_parallel(qb, kb, vb, causal, w.scale)
