@@ -31,12 +31,14 @@ constexpr int kTileKeys = 32;      // keys per tile and key group
 
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Query row r of a kv head's g * Sq packed rows -> offset of its head among the g, position.
+// Query row r of a kv head's g * Sq packed rows -> offset of its head among the g, position.  The g heads of a position lie
+// side by side: a 32-row block spans 32 / g positions, inside one group of 32 of them for any g, so that under the
+// causal mask its rows end at nearly the same key.
 struct PackedRow { int h, i; };
-__device__ __forceinline__ PackedRow packed_row(int r, int Sq) {
+__device__ __forceinline__ PackedRow packed_row(int r, int g) {
     PackedRow x;
-    x.h = r / Sq;
-    x.i = r - x.h * Sq;
+    x.i = r / g;
+    x.h = r - x.i * g;
     return x;
 }
 
@@ -85,18 +87,17 @@ __global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : (D == 128 && RB == 1) ? 1 : 
 
     // key tiles this workgroup's rows can see, and this split's share of them
     const int first = rowblk * (RB * kWaveRows), last = min(first + RB * kWaveRows, R) - 1;
-    int lim_wg = Sk - 1;
-    if (CAUSAL) {
-        const PackedRow a = packed_row(first, Sq), z = packed_row(last, Sq);
-        lim_wg = min(Sk - 1, (a.h == z.h ? z.i : Sq - 1) + shift);
-    }
+    const int lim_wg = CAUSAL ? min(Sk - 1, packed_row(last, g).i + shift) : Sk - 1;
     const int nT = lim_wg < 0 ? 0 : lim_wg / kTileKeys + 1;
     const int per = (nT + sp.splits - 1) / sp.splits;
     const int t0 = split * per, t1 = min(nT, t0 + per);
 
     const int r = first + rb * kWaveRows + (lane & 31);
-    const PackedRow row = packed_row(min(r, R - 1), Sq);
+    const PackedRow row = packed_row(min(r, R - 1), g);
     const int lim = CAUSAL ? min(Sk - 1, row.i + shift) : Sk - 1;
+    // the last key any row of this wavefront sees: later tiles are left out, so that V behind the mask (0 * inf is NaN)
+    // reaches no row from further away than the mask's own tile
+    const int lim_wave = CAUSAL ? min(Sk - 1, packed_row(min(first + rb * kWaveRows + kWaveRows, R) - 1, g).i + shift) : Sk - 1;
     const float c = p.scale_log2;
 
     // copies: lane offsets inside a tile (the LDS side is lane-contiguous, the swizzle is applied to the source)
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : (D == 128 && RB == 1) ? 1 : 
     for (int s = 0; s < steps; ++s) {
         const int t = t0 + kg + s * KG, st = s & 1;
         if constexpr (RB > 1) { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_barrier(); __builtin_amdgcn_sched_barrier(0); }
-        if (t < t1) {
+        if (t < t1 && t * kTileKeys <= lim_wave) {
             const char* const sK = smem + kg * (4 * TB) + st * (2 * TB);
             const char* const sV = sK + TB;
             f32x16 sc;

@@ -108,3 +108,27 @@ def test_call_on_another_stream_than_torchs_current_one():
     got = attn_fwd(q, k, v, stream=side)
     torch.cuda.synchronize()
     assert (got[0].float() - want[0].float()).abs().max() <= 2e-2 and (got[1] - want[1]).abs().max() <= 1e-3
+
+
+# B, Hq, Hkv, Sq, Sk, D: one to five heads on a kv head, one, two and four row blocks per workgroup
+@pytest.mark.parametrize("shape", [(2, 4, 2, 64, 400, 128), (1, 2, 1, 64, 449, 64), (1, 3, 3, 40, 513, 128), (1, 6, 2, 50, 513, 64), (1, 5, 1, 33, 513, 128), (1, 2, 1, 200, 1900, 128)],
+                         ids=lambda s: "B%d_H%d_%d_S%d_%d_D%d" % s)
+@pytest.mark.parametrize("splits", [1, 3])
+def test_values_behind_the_mask_reach_no_row_from_further_away_than_in_the_tiled_kernels(shape, splits):
+    """V holds infinities and NaN at the last key.  The tiled kernels multiply 0 by them in the 64-key tile in which the
+    last of a group of 32 query positions ends, and nowhere before it; nor may the cut do so."""
+    B, Hq, Hkv, Sq, Sk, D = shape
+    w = I.Workload("mask", B, Hq, Hkv, Sq, Sk, D, True, 45)
+    qb, kb, vb = I.make_qkv(w)
+    vb[:, :, -1] = 0
+    o_ref, lse_ref = oracle_parallel(qb, kb, vb, True, w.scale)
+    bad = vb.copy()
+    bad[:, :, -1, ::2], bad[:, :, -1, 1::2] = 0x7F80, 0x7FC0
+    print(shape, splits, flush=True)
+    o, lse = call(to_dev(qb), to_dev(kb), to_dev(bad), True, w.scale, splits)
+    o, lse = from_dev_bf16(o), lse.cpu().numpy().astype(np.float64)
+    last = (Sk - Sq) + np.minimum(np.arange(Sq) // 32 * 32 + 31, Sq - 1)
+    clean = last // 64 * 64 + 63 < Sk - 1
+    assert clean.any()
+    check(o[:, :, clean], lse[:, :, clean], o_ref[:, :, clean], lse_ref[:, :, clean], str(shape))
+    assert not np.isfinite(o[:, :, -1]).any() and np.abs(lse - lse_ref).max() <= 1e-3     # the last row sees the key
