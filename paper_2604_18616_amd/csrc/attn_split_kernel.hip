@@ -272,7 +272,7 @@ __global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : (D == 128 && RB == 1) ? 1 : 
 #pragma unroll
                 for (int k = 0; k < KG; ++k) {
                     const float mk = sml[0][k * RB + rb][rw];
-                    l += mk == -INFINITY ? 0.f : sml[1][k * RB + rb][rw] * exp2_hw((mk - m) * c);
+                    l += sml[1][k * RB + rb][rw] * (mk == -INFINITY ? 0.f : exp2_hw((mk - m) * c));   // a NaN sum stays one
                 }
                 put_ml(row, m, l);
                 s_inv[rb * kWaveRows + rw] = l > 0.f ? 1.0f / l : 0.f;

@@ -132,3 +132,27 @@ def test_values_behind_the_mask_reach_no_row_from_further_away_than_in_the_tiled
     assert clean.any()
     check(o[:, :, clean], lse[:, :, clean], o_ref[:, :, clean], lse_ref[:, :, clean], str(shape))
     assert not np.isfinite(o[:, :, -1]).any() and np.abs(lse - lse_ref).max() <= 1e-3     # the last row sees the key
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+def test_a_score_that_is_no_number_shows_in_o_and_lse(splits):
+    """The last key, alone in its tile, is NaN: every row that sees it gives NaN, and no finite LSE, as the 128-row kernel does."""
+    from tests._util import run_hip
+    w = I.Workload("nan", 1, 4, 2, 3, 129, 128, False, 46)
+    qb, kb, vb = I.make_qkv(w)
+    kb[:, :, -1] = 0x7FC0
+    o, lse = call(to_dev(qb), to_dev(kb), to_dev(vb), False, w.scale, splits)
+    want = run_hip(qb, kb, vb, False, w.scale, wg_rows=128)
+    assert np.isnan(from_dev_bf16(o)).all() and np.isnan(want[0]).all()
+    assert np.array_equal(lse.cpu().numpy().astype(np.float64), want[1])
+
+
+def test_results_repeat_exactly():
+    import torch
+    from paper_2604_18616_amd import attn_fwd
+    gen = torch.Generator(device="cuda").manual_seed(47)
+    q, k, v = (torch.randn((2, h, s, 128), generator=gen, device="cuda", dtype=torch.bfloat16) for h, s in ((8, 4), (2, 3000), (2, 3000)))
+    first = attn_fwd(q, k, v, causal=True)
+    for _ in range(5):
+        again = attn_fwd(q, k, v, causal=True)
+        assert torch.equal(again[0], first[0]) and torch.equal(again[1], first[1])
