@@ -53,12 +53,12 @@ static int attn_fwd_impl(const void* q, const void* k, const void* v, void* o, f
         AttnSplit sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, splits);
         const bool room = workspace && workspace_bytes >= attn_split_bytes(B, Hq, Sq, D, sp.splits);
         if (!room) sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 1);
-        if (!few && sp.splits == 1) {                      // nothing to gain over the tiled kernel
-            const int trc = attn_launch(p, D, causal != 0, 0, (hipStream_t)stream);
-            return trc == 0 ? ATTN_OK : trc == -2 ? ATTN_ERR_BAD_SHAPE : ATTN_ERR_LAUNCH;
+        // a cut that the caller asks for is run; else whichever kernel is the faster one
+        const bool asked = splits > 1 && sp.splits > 1;
+        if (asked || (few ? attn_split_wins(sp, B, Hq, Sk, D) : sp.splits > 1)) {
+            const int src = attn_split_launch(p, D, causal != 0, sp, workspace, (hipStream_t)stream);
+            return src == 0 ? ATTN_OK : src == -2 ? ATTN_ERR_BAD_SHAPE : ATTN_ERR_LAUNCH;
         }
-        const int src = attn_split_launch(p, D, causal != 0, sp, workspace, (hipStream_t)stream);
-        return src == 0 ? ATTN_OK : src == -2 ? ATTN_ERR_BAD_SHAPE : ATTN_ERR_LAUNCH;
     }
     const int rc = attn_launch(p, D, causal != 0, wg_rows, (hipStream_t)stream);
     return rc == 0 ? ATTN_OK : rc == -2 ? ATTN_ERR_BAD_SHAPE : ATTN_ERR_LAUNCH;
@@ -85,7 +85,9 @@ extern "C" int attn_fwd_strided(const void* q, const void* k, const void* v, voi
 
 extern "C" size_t attn_fwd_workspace_bytes(int B, int Hq, int Hkv, int Sq, int Sk, int D) {
     if (check_dims(B, Hq, Hkv, Sq, Sk, D) || (D != 64 && D != 128) || !attn_split_pays(B, Hq, Hkv, Sq, Sk, D)) return 0;
-    return attn_split_bytes(B, Hq, Sq, D, attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 0).splits);
+    const AttnSplit sp = attn_split_plan(B, Hq, Hkv, Sq, Sk, D, 0);
+    if (attn_split_sizes(Sq, Sk) && !attn_split_wins(sp, B, Hq, Sk, D)) return 0;
+    return attn_split_bytes(B, Hq, Sq, D, sp.splits);
 }
 
 extern "C" int attn_fwd_workspace(const void* q, const void* k, const void* v, void* o, float* lse,

@@ -40,6 +40,8 @@ struct AttnSplit {
 bool attn_split_sizes(int Sq, int Sk);
 bool attn_split_pays(int B, int Hq, int Hkv, int Sq, int Sk, int D);
 bool attn_split_fits(const AttnParams& p);
+// Up to 64 query positions: whether that cut is faster than the 128-row kernel.
+bool attn_split_wins(const AttnSplit& sp, int B, int Hq, int Sk, int D);
 // Its cut; splits 0: by size.  Host arithmetic only.
 AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int splits);
 // Bytes of workspace that cut needs: none for one split.

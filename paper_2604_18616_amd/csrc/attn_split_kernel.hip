@@ -438,6 +438,21 @@ bool attn_split_pays(int B, int Hq, int Hkv, int Sq, int Sk, int D) {
     return sp.splits > 1 && sp.cost < 0.85 * (2.0 + (Sk + 63) / 64 * (D == 128 ? 1.0 : 0.73));
 }
 
+// Up to 64 query positions: whether this cut, or this kernel uncut, beats a 128-row workgroup per query head.  It does up to 64
+// packed rows per kv head, and with more query heads than the chip holds workgroups at two per CU (or at D = 64 at one, where it
+// is level with them).  Below, with four row blocks per workgroup, the 128-row kernel walks 64 keys in 1.45 us (D 128; 1.12 at
+// D 64) with one workgroup per CU and 2.25 with two, this one 32 in 1.0 (0.75).  Measured, 128-row kernel against this one,
+// B Hq Hkv Sq Sk D: uncut 1 8 1 32 6000 128: 131 / 174 us; 5 16 2 50 296 64: 9.2 / 10.7; 25 8 2 20 238 128: 9.3 / 11.8;
+// 10 32 2 18 7419 128 (320 heads): 256 / 210; 45 8 1 17 967 128 (360): 39 / 34; cut 2 32 2 53 339 128: 11.9 / 15.1;
+// 7 32 2 13 834 128: 24.8 / 17.1.  Estimates that are level within 3 % stay uncut, which takes no memory.
+bool attn_split_wins(const AttnSplit& sp, int B, int Hq, int Sk, int D) {
+    const long long heads = (long long)B * Hq;
+    if (sp.rb < 4 || heads > (D == 128 ? 512 : 256)) return true;
+    const int tiles = (Sk + 63) / 64;
+    const double rows128 = D == 128 ? 3.7 + tiles * (heads <= 256 ? 1.45 : 2.25) : 2.9 + tiles * 1.12;
+    return sp.cost < (sp.splits > 1 ? 0.97 : 1.0) * rows128;
+}
+
 // The cut with the least estimated time, in microseconds.  Measured: a step of a workgroup (one tile per key group;
 // 64 KB per CU at RB = 1) takes 1.3 us while HBM is no limit, which 128 CUs reach together, and 2.7 us with all CUs at
 // it; two workgroups of two wavefronts per CU hide each other's start and end, which pays from several rounds of them

@@ -59,7 +59,7 @@ def test_every_cut_against_the_reference(shape):
         print(shape, splits, flush=True)
         o, lse = call(q, k, v, causal, w.scale, splits)
         check(from_dev_bf16(o), lse.cpu().numpy().astype(np.float64), *ref, "%s splits %d" % (shape, splits))
-    # without memory: one workgroup along the keys
+    # without memory: uncut
     o1, lse1 = call(q, k, v, causal, w.scale, 1)
     o0, lse0 = call(q, k, v, causal, w.scale, 7, memory=False)
     assert bool((o0 == o1).all()) and bool((lse0 == lse1).all())
@@ -156,3 +156,31 @@ def test_results_repeat_exactly():
     for _ in range(5):
         again = attn_fwd(q, k, v, causal=True)
         assert torch.equal(again[0], first[0]) and torch.equal(again[1], first[1])
+
+
+# B, Hq, Hkv, Sq, Sk, D, causal: more than 64 packed rows on a kv head and few heads, without memory and where no cut pays
+@pytest.mark.parametrize("shape,cut", [((1, 8, 1, 32, 1500, 128, True), True), ((7, 8, 2, 52, 800, 64, False), True), ((5, 16, 2, 50, 296, 64, True), False),
+                                       ((3, 16, 2, 15, 170, 128, False), False), ((25, 8, 2, 20, 238, 128, False), False)],
+                         ids=lambda s: "B%d_H%d_%d_S%d_%d_D%d_%s" % s if isinstance(s, tuple) else "cut" if s else "uncut")
+def test_uncut_calls_of_many_packed_rows_run_on_the_128_row_kernel(shape, cut):
+    """One workgroup along the keys is slower there than the 128-row kernel's workgroup per head: the same bits as attn_fwd_tile."""
+    from paper_2604_18616_amd import binding
+    from tests._util import run_hip
+    B, Hq, Hkv, Sq, Sk, D, causal = shape
+    assert (binding.load_library().attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) > 0) == cut
+    w = I.Workload("rows", B, Hq, Hkv, Sq, Sk, D, causal, 48)
+    qb, kb, vb = I.make_qkv(w)
+    want = run_hip(qb, kb, vb, causal, w.scale, wg_rows=128)
+    got = run_hip(qb, kb, vb, causal, w.scale)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    for splits, memory in ((1, True), (7, False)) + (() if cut else ((0, True),)):
+        o, lse = call(to_dev(qb), to_dev(kb), to_dev(vb), causal, w.scale, splits, memory=memory)
+        assert np.array_equal(from_dev_bf16(o), want[0]) and np.array_equal(lse.cpu().numpy().astype(np.float64), want[1])
+
+
+def test_four_row_blocks_per_workgroup_uncut():
+    """More heads than the 128-row kernel has places for: the kernel of the cut, uncut."""
+    w = I.Workload("rows", 16, 36, 4, 8, 130, 128, True, 49)      # 72 packed rows, 576 heads
+    qb, kb, vb = I.make_qkv(w)
+    o, lse = call(to_dev(qb), to_dev(kb), to_dev(vb), True, w.scale, 1)
+    check(from_dev_bf16(o), lse.cpu().numpy().astype(np.float64), *oracle_parallel(qb, kb, vb, True, w.scale), "uncut")
