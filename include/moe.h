@@ -61,8 +61,9 @@ int moe_ffn_fp8(const void *x, const int *ids, const float *wts,
  *   first_stage..last_stage  run only these stages (0 routing, 1 activation quantization, 2 gate/up product
  *       with SiLU and requantization, 3 down product, 4 combine); the stages before first_stage must have run
  *       on the same arguments, workspace and row_tile.  moe_ffn_fp8 is 0..4.
- *   row_tile  rows of one expert per workgroup of the two products: 64, 128, or 0 = what moe_ffn_fp8 does: one
- *       tile for up to 160 rows, more rows evenly into the fewest tiles of at most 256.
+ *   row_tile  rows of one expert per workgroup of the two products: 64, 128, or 0 = what moe_ffn_fp8 does, which is
+ *       128, or tiles of up to 256 rows where their smaller number fills the GPU as well (one tile for up to 160 rows, more
+ *       rows evenly into the fewest tiles): the faster one by an estimate from the routed rows of the whole call.
  *       For 64 and 128 an expert's rows are cut into tiles of row_tile rows and a remainder (an expert with row_tile + 1 ..
  *       row_tile + 32 rows gets a single tile); every tile runs the code that fits its rows.
  * A stage range outside 0..4 or another row_tile: ATTN_ERR_UNSUPPORTED.

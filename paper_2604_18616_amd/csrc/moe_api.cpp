@@ -26,7 +26,7 @@ size_t moe_workspace_layout(int T, int H, int I, int E, int KTOP, size_t off[13]
     auto take = [&](int idx, size_t bytes) { off[idx] = cur; cur = align256(cur + bytes); };
     take(0, sizeof(int) * (E + 1));          // offsets
     take(1, sizeof(int) * E);                // cursor
-    take(2, sizeof(int));                    // ntiles
+    take(2, 2 * sizeof(int));                // ntiles
     take(3, 4 * sizeof(int) * max_tiles);    // tile_rec
     take(4, sizeof(int));                    // (not in use)
     take(5, sizeof(int));                    // (not in use)
@@ -76,10 +76,10 @@ extern "C" int moe_ffn_fp8_ex(const void* x, const int* ids, const float* wts,
     p.w13 = (const uint8_t*)w13; p.s13 = s13; p.w2 = (const uint8_t*)w2; p.s2 = s2;
     p.y = (__bf16*)y;
     p.T = T; p.H = H; p.I = I; p.E = E; p.KTOP = KTOP;
-    // how an expert's rows are cut into tiles (moe_tiles); each tile runs the 64-, 128-, 160- or 256-row code that fits
+    // how an expert's rows are cut into tiles (moe_layout.h); each tile runs the 64-, 128-, 160- or 256-row code that fits
     // the rows it really has.  `bm_override` is for tests
     p.bm = bm_override;
-    const int bound = p.bm ? p.bm : 128;                 // (the library's rule makes no more tiles than tiles of 128 rows would be)
+    const int bound = p.bm ? p.bm : 128;                 // (neither of the library's two cuts makes more tiles than that)
     p.max_tiles = (int)(((size_t)T * KTOP + bound - 1) / bound + E);
     // narrow column tiles of the down product are for problems whose wide tiles would not fill the chip: the grid is
     // sized for them only if the upper bound on the row tiles is small enough for that to be possible

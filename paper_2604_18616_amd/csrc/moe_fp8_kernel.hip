@@ -78,7 +78,7 @@ __device__ __forceinline__ void route_block(const MoeParams& p) {
             for (int w = 0; w < 16; ++w) { const int c = wcnt[w * 256 + tid]; wcnt[w * 256 + tid] = run; run += c; }
         cnt[tid] = run;
         rows_scan[tid] = run;
-        tiles_scan[tid] = moe_tiles(run, p.bm);
+        tiles_scan[tid] = p.bm ? moe_tiles(run, p.bm) : moe_tiles(run, 128) << 16 | moe_tiles(run, 0);      // (both cuts: at most 8448 tiles)
     }
     __syncthreads();
     for (int d = 1; d < 256; d <<= 1) {      // inclusive scans over the experts
@@ -89,14 +89,16 @@ __device__ __forceinline__ void route_block(const MoeParams& p) {
         __syncthreads();
     }
     if (tid < E) {
-        const int nt = moe_tiles(cnt[tid], p.bm);
-        const int start = rows_scan[tid] - cnt[tid], tstart = tiles_scan[tid] - nt;
+        const int all = tiles_scan[255];
+        const int bm = p.bm || rows_scan[255] == 0 ? p.bm : moe_choose(rows_scan[255], all >> 16, all & 0xffff, p.H, p.I);   // uniform
+        const int nt = moe_tiles(cnt[tid], bm), upto = p.bm ? tiles_scan[tid] : bm ? tiles_scan[tid] >> 16 : tiles_scan[tid] & 0xffff;
+        const int start = rows_scan[tid] - cnt[tid], tstart = upto - nt;
         p.offsets[tid] = start;
         for (int w = 0; w < 16; ++w) wcnt[w * 256 + tid] += start;
         for (int m = 0; m < nt; ++m) {
             p.tile_rec[tstart + m] = MoeTileRec{tid, start, cnt[tid], tstart};
         }
-        if (tid == E - 1) { p.offsets[E] = rows_scan[tid]; p.ntiles[0] = tiles_scan[tid]; }
+        if (tid == E - 1) { p.offsets[E] = rows_scan[tid]; p.ntiles[0] = upto; p.ntiles[1] = bm; }
     }
     __syncthreads();
     for (int i0 = tid; i0 < n; i0 += 1024 * kRU) {
@@ -168,7 +170,8 @@ __global__ __launch_bounds__(1024) void moe_prepare(MoeParams p, int stages) {
 // ------------------------------------------------------------------------------------
 // Grouped block-scaled FP8 product.  Workgroup = 8 wavefronts = 4 (n) x 2 (m) for the MFMAs: 256 weight rows x
 // BM routed rows.  An expert's rows are cut into one tile of up to 160, or evenly into the fewest of up to 256 rows
-// (moe_tiles; a caller may ask for tiles of 128 or 64); each workgroup picks the code for BM = 64, 128, 160 or 256 from
+// (moe_tiles), or into tiles of 128 where those fill the chip better (moe_choose, once per call; a caller may ask for 128
+// or 64); each workgroup picks the code for BM = 64, 128, 160 or 256 from
 // the rows its tile really has.  Up to 160 rows the weights come from HBM for that one tile and three LDS stages cover
 // the latency.  From there on the copies L2 -> LDS bound it (10 TB/s over the chip): a 256-row tile, whose 64 KB stages
 // fit twice, copies a third less per product than two of 128.  Gate/up + down, us, 128-row against 256-row tiles: 256
@@ -509,7 +512,7 @@ __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
     // narrow tiles when the problem is small enough for that to happen (p.dn_narrow_ok); the choice itself needs the
     // number of row tiles, known only here.  (With 128 to 256 wide tiles the narrow ones run two rounds of half the work
     // at a lower rate; beyond, they are 3-15 % slower: measured.)
-    const int ntl = p.ntiles[0];
+    const int ntl = p.ntiles[0], bm = p.ntiles[1];
     const bool narrow = !UP && p.dn_narrow_ok && ntl * ((p.H + kMoeBN - 1) / kMoeBN) <= 128;
     const int NT = UP ? (p.I >> 7) : narrow ? (p.H >> 7) : (p.H + kMoeBN - 1) / kMoeBN;
     const int live = ntl * NT, per_xcd = (live + 7) >> 3;
@@ -517,12 +520,12 @@ __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
     const int logical = (bid & 7) * per_xcd + (bid >> 3);
     if ((bid >> 3) >= per_xcd || logical >= live) return;   // uniform: before any barrier
     const MoeTileRec rec = p.tile_rec[logical / NT];             // the expert whose block of ids holds `logical`
-    const int cnt = moe_tiles(rec.rows, p.bm);                    // its row tiles
+    const int cnt = moe_tiles(rec.rows, bm);                      // its row tiles
     const int off = logical - rec.first * NT;                     // in [0, cnt * NT)
     const int nt = off / cnt, j = off - nt * cnt;                 // column tile, row tile within the expert
-    const int begin = moe_tile_begin(rec.rows, cnt, j, p.bm);
+    const int begin = moe_tile_begin(rec.rows, cnt, j, bm);
     const int e = rec.expert, row0 = rec.row0 + begin;
-    const int rows = moe_tile_begin(rec.rows, cnt, j + 1, p.bm) - begin;   // uniform
+    const int rows = moe_tile_begin(rec.rows, cnt, j + 1, bm) - begin;   // uniform
     const LdsChar tiles = LDS_PTR(char, smem);
     const LdsFloat sa = LDS_PTR(float, sa_stage), sb = LDS_PTR(float, sb_tab);
     if constexpr (!UP) {

@@ -5,10 +5,12 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "moe_layout.h"
+
 constexpr int kMoeBM = 64;   // smallest row tile (routed token slots of one expert) of the grouped products: sizes the tile tables
 
 // What a workgroup of the grouped products needs to know about the expert its row tile belongs to, in one
-// 16-byte load: the tile's own first row and row count follow from these by arithmetic (moe_row_tiles), so the
+// 16-byte load: the tile's own first row and row count follow from these by arithmetic (moe_tile_begin), so the
 // chain of dependent loads in front of a workgroup's first copy is: number of tiles -> this record -> (gate/up
 // only) the tokens of its rows.
 struct MoeTileRec {
@@ -18,40 +20,18 @@ struct MoeTileRec {
     int first;                // index of its first row tile (moe_tiles of them)
 };
 
-// Row tiles of an expert with cnt rows: tiles of bm rows and a remainder.  An expert with one full tile and
-// at most 32 rows more gets a single tile of up to bm + 32 rows (one more 32-row MFMA block instead of a
-// second copy of every weight tile: 13 % on the whole call where experts have about bm rows).  With two or
-// more full tiles the remainder stays a tile of its own: measured, the short tiles then cost little (their
-// weights are L2 hits) and fill the last round of workgroups, which equal long tiles leave mostly idle.
-__host__ __device__ inline int moe_row_tiles(int cnt, int bm) {
-    const int n = cnt / bm, r = cnt - n * bm;
-    return (n == 1 && r <= 32) ? 1 : n + (r > 0 ? 1 : 0);
-}
-
-// The library's own rule (bm = 0): an expert with up to 160 rows gets one tile, more rows the fewest tiles of at most 256,
-// cut evenly at multiples of 32.
-__host__ __device__ inline int moe_tiles(int cnt, int bm) {
-    if (bm != 0) return moe_row_tiles(cnt, bm);
-    return cnt <= 160 ? (cnt > 0 ? 1 : 0) : (cnt + 255) / 256;
-}
-// First row of tile j of the n = moe_tiles(cnt, bm) of an expert; j = n gives its number of rows.
-__host__ __device__ inline int moe_tile_begin(int cnt, int n, int j, int bm) {
-    const int at = bm != 0 ? j * bm : (int)((long long)j * ((cnt + 31) / 32) / n) * 32;
-    return j >= n || at > cnt ? cnt : at;
-}
-
 struct MoeParams {
     const __bf16* x; const int* ids; const float* wts;
     const uint8_t* w13; const float* s13; const uint8_t* w2; const float* s2;
     __bf16* y;
     int T, H, I, E, KTOP;
-    int bm;                   // rows per tile for this call: 64, 128, or 0 for the library's own rule
-    int max_tiles;            // upper bound on the number of row tiles: ceil(T*KTOP / bm) + E
+    int bm;                   // rows per tile for this call: 64, 128, or 0 for the library's choice (moe_choose, by the routing stage)
+    int max_tiles;            // upper bound on the number of row tiles: ceil(T*KTOP / (bm or 128)) + E
     int dn_narrow_ok;         // the grid of the down product is sized for 128-row column tiles (the kernel decides whether to use them)
     // workspace carve-up (all device pointers into the caller's workspace)
     int* offsets;             // [E + 1] first sorted row of each expert
     int* cursor;              // [E]     scatter cursors
-    int* ntiles;              // [1]     row tiles in use
+    int* ntiles;              // [2]     row tiles in use, and the bm of moe_tiles that they follow
     MoeTileRec* tile_rec;     // [max_tiles] one record per row tile
     int* sorted_tok;          // [T*KTOP] token of each sorted row
     int* pos;                 // [T*KTOP] sorted row of slot (t, k), or -1 if the slot is not local

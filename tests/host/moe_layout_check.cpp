@@ -1,0 +1,52 @@
+// Host-side check of the expert layer's row tiles (csrc/moe_layout.h), compiled with g++ by tests/test_layout_host.py: every
+// cut of every row count is a partition the kernel can run, the two cuts of a call fit the tables sized for 128-row tiles,
+// and the choice between them is the faster one at the sizes both were measured at.
+#include <cstdio>
+#define __host__
+#define __device__
+#include "../../paper_2604_18616_amd/csrc/moe_layout.h"
+
+static int failures = 0;
+#define CHECK(cond, ...) do { if (!(cond) && ++failures < 20) { printf(__VA_ARGS__); printf("\n"); } } while (0)
+
+static void check_cuts() {
+    const int bms[] = {0, 64, 128};
+    for (int bm : bms)
+        for (int cnt = 0; cnt <= 20000; ++cnt) {
+            const int n = moe_tiles(cnt, bm), most = bm ? bm + 32 : 256;
+            CHECK((n == 0) == (cnt == 0), "bm %d, %d rows: %d tiles", bm, cnt, n);
+            CHECK(bm != 0 || n <= moe_tiles(cnt, 128), "%d rows: %d tiles, more than of 128 rows", cnt, n);
+            for (int j = 0; j < n; ++j) {
+                const int begin = moe_tile_begin(cnt, n, j, bm), end = moe_tile_begin(cnt, n, j + 1, bm);
+                CHECK(begin % 32 == 0 && end > begin && end - begin <= most, "bm %d, %d rows: tile %d is %d .. %d", bm, cnt, j, begin, end);
+                CHECK(j > 0 || begin == 0, "bm %d, %d rows: starts at %d", bm, cnt, begin);
+            }
+            CHECK(n == 0 || moe_tile_begin(cnt, n, n, bm) == cnt, "bm %d, %d rows: ends at %d", bm, cnt, moe_tile_begin(cnt, n, n, bm));
+        }
+    CHECK((1 << 20) / 128 + 256 < 1 << 15, "two tile counts share an int");
+}
+
+static void check_choice() {
+    // E experts with `rows` rows each; us of the two products with tiles of 128 rows and of up to 256
+    struct { int H, I, E, rows; double t128, t256; } const measured[] = {
+        {1024, 512, 8, 175, 21.3, 28.9}, {1024, 512, 8, 256, 21.7, 34.2}, {1024, 512, 8, 512, 23.5, 35.4}, {1024, 512, 8, 1000, 31.2, 38.5},
+        {1024, 512, 8, 2000, 59.3, 50.9}, {4096, 1408, 4, 200, 48.9, 74.9}, {4096, 1408, 4, 500, 58.4, 84.0}, {4096, 1408, 4, 700, 106.4, 90.5},
+        {2944, 1152, 12, 200, 62.3, 68.9}, {2944, 1152, 12, 300, 85.7, 78.1}, {4096, 14336, 8, 256, 471.4, 520.4}, {4096, 14336, 8, 400, 841.1, 711.5},
+        {2048, 1408, 64, 200, 242.9, 207.2}, {2048, 768, 128, 256, 314.1, 277.3}, {5120, 1536, 16, 256, 156.5, 149.0}, {7168, 2048, 32, 256, 520.0, 479.8}};
+    for (const auto& m : measured) {
+        const int bm = moe_choose(m.E * m.rows, m.E * moe_tiles(m.rows, 128), m.E * moe_tiles(m.rows, 0), m.H, m.I);
+        CHECK(bm == (m.t128 < m.t256 ? 128 : 0), "%d experts of %d x %d, %d rows: bm %d, measured %.1f / %.1f us", m.E, m.H, m.I, m.rows, bm, m.t128, m.t256);
+    }
+    // the largest sums that the estimate can meet stay inside an int and positive
+    const int tiles = (1 << 20) / 128 + 256;
+    CHECK(moe_product_time(1 << 20, tiles, 128, 128, false) > 0 && moe_product_time(1 << 20, tiles / 2, 128, 128, true) > 0, "overflow");
+    CHECK(moe_choose(1, 1, 1, 128, 128) == 0, "one row");
+}
+
+int main() {
+    check_cuts();
+    check_choice();
+    if (failures) { printf("%d moe layout check(s) FAILED\n", failures); return 1; }
+    printf("moe layout checks passed\n");
+    return 0;
+}

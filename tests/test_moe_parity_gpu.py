@@ -70,7 +70,7 @@ def run(d, row_tile=0):
     slots = T * K
     offsets = part(0, np.int32, E + 1)
     A = int(offsets[E])
-    out = dict(y=I.bf16_bits_to_f32(y.view(torch.int16).cpu().numpy().view(np.uint16)).astype(np.float64),
+    out = dict(ntiles=int(part(2, np.int32, 1)[0]), y=I.bf16_bits_to_f32(y.view(torch.int16).cpu().numpy().view(np.uint16)).astype(np.float64),
                offsets=offsets, sorted_tok=part(6, np.int32, slots)[:A], pos=part(7, np.int32, slots).reshape(T, K),
                xq=part(8, np.uint8, T * H).reshape(T, H), xs=part(9, np.float32, T * (H // 128)).reshape(T, H // 128),
                aq=part(10, np.uint8, max(A, 1) * Isz).reshape(-1, Isz)[:A],

@@ -10,32 +10,60 @@ from tests.test_moe_parity_gpu import check_routing, check_stage1, check_y, run,
 pytestmark = pytest.mark.gpu
 
 
-def check_rows_per_expert(counts, H, Isz, twice=False):
-    """One call in which expert e gets counts[e] rows, a token each, or every token a second, shared choice (twice)."""
+def tiles_256(counts):
+    return sum(1 if 0 < n <= 160 else -(-n // 256) for n in counts)
+
+
+def check_rows_per_expert(counts, H, Isz, twice=False, filler=(), tiles=None):
+    """One call in which expert e gets counts[e] rows, a token each, or every token a second, shared choice (twice).  The
+    experts of `filler` follow; their rows are not looked at.  tiles: the number of row tiles the call has to make."""
+    counts, looked_at = tuple(counts) + tuple(filler), len(counts)
     T, E = int(sum(counts)), len(counts) + int(twice)
     w = I.MoeWorkload("t", T, 500 + T, H=H, I=Isz, E=E, KTOP=1 + int(twice), EP=1)
     d = I.make_moe(w)
     first = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
     np.random.default_rng(T).shuffle(first)
     d["ids"] = np.ascontiguousarray(np.stack([first] + ([np.full(T, E - 1, np.int32)] if twice else []), axis=1))
-    print("moe tiles", counts, H, Isz, twice, flush=True)
+    print("moe tiles", counts[:looked_at], H, Isz, twice, flush=True)
     g = run(d)
+    assert tiles is None or g["ntiles"] == tiles
     check_routing(w, d, g)
     order = np.argsort(g["pos"][:, 0])                    # tokens in row order: the first, last and odd rows of every expert
     ends = np.cumsum(counts)
-    rows = sorted({min(max(r, 0), T - 1) for e, n in zip(ends, counts) if n for r in (e - n, e - n + 31, e - n + 128, e - 33, e - 2, e - 1)})
+    rows = sorted({min(max(r, 0), T - 1) for e, n in list(zip(ends, counts))[:looked_at] if n for r in (e - n, e - n + 31, e - n + 128, e - 33, e - 2, e - 1)})
     tokens = [int(order[r]) for r in rows]
     check_stage1(w, d, g, tokens)
     check_y(w, d, g, tokens)
-    sanity_net(g["y"], oracle.moe_ref(**d), str(counts))
+    some = tokens if filler else list(range(T))
+    sanity_net(g["y"][some], oracle.moe_ref(**d, rows=some), str(counts[:looked_at]))
 
 
-# up to 160 rows one tile; 161 to 256 one tile of the 256-row code with 6 to 8 blocks of 32 rows; from 257 on tiles cut
-# evenly at multiples of 32.  H 384: a last wide column tile that is half empty, and narrow column tiles
+# experts at the edges of both cuts, in calls too small for the larger tiles: they take tiles of 128 rows
 @pytest.mark.parametrize("H,Isz", [(256, 256), (384, 128)])
 @pytest.mark.parametrize("counts", [(160, 161), (192, 193, 1), (224, 225), (255, 256, 257), (512, 513), (300, 40), (700,)])
 def test_edges_of_the_tile_rule(counts, H, Isz):
-    check_rows_per_expert(counts, H, Isz)
+    from paper_2604_18616_amd import binding
+    rt = binding.load_library().moe_ffn_fp8_row_tiles
+    check_rows_per_expert(counts, H, Isz, tiles=sum(rt(n, 128) for n in counts))
+
+
+# up to 160 rows one tile; 161 to 256 one tile of the 256-row code with 6 to 8 blocks of 32 rows; from 257 on tiles cut
+# evenly at multiples of 32
+EDGES = (160, 161, 192, 193, 1, 224, 225, 255, 256, 257, 512, 513, 300, 40, 700)
+
+
+# H 384: a last wide column tile that is half empty.  236 experts keep the down product's wide column tiles
+@pytest.mark.parametrize("H,Isz", [(256, 256), (384, 128)])
+def test_tiles_of_up_to_256_rows(H, Isz):
+    filler = (256,) * (236 - len(EDGES))
+    check_rows_per_expert(EDGES, H, Isz, filler=filler, tiles=tiles_256(EDGES + filler))
+
+
+def test_tiles_of_up_to_256_rows_with_narrow_column_tiles():
+    """At most 128 wide column tiles: the down product takes them by halves."""
+    counts, filler = (161, 192, 225, 256, 257, 320, 400, 512), (300,) * 40
+    assert tiles_256(counts + filler) <= 128
+    check_rows_per_expert(counts, 256, 256, filler=filler, tiles=tiles_256(counts + filler))
 
 
 def test_wide_column_tiles_of_the_down_product():
@@ -45,6 +73,7 @@ def test_wide_column_tiles_of_the_down_product():
 
 def test_tiles_with_two_local_slots():
     check_rows_per_expert((170, 230), 256, 128, twice=True)
+    check_rows_per_expert((170, 230, 300), 256, 256, twice=True, filler=(250,) * 200)
 
 
 # the combine step: a token's columns in one to sixteen parts of 512, none / one / several local slots side by side
