@@ -104,13 +104,15 @@ int moe_ffn_fp8_static(const void *x, const int *ids, const float *wts,
  *  10 aq         e4m3  [rows, I]  quantized intermediate      11 as   fp32 [rows, I/128]
  *  12 o          fp32  [rows, H]  down-projection rows of tokens with two or more local slots (the row of a token
  *                with a single local slot goes straight to y as wts * row, which is all its sum has; its o is not written)
- * (1-5 are internal scheduling tables.)  Host only.
+ * (1-5 are internal scheduling tables; part 2 starts with the number of row tiles, int32.)  Host only.
  */
 long long moe_ffn_fp8_workspace_offset(int T, int H, int I, int E, int KTOP, int part);
 
 /* Row tiles (workgroups per column tile) an expert with `rows` routed rows is cut into for row_tile = 64 or
- * 128 as in moe_ffn_fp8_ex (0 answers for 128): tiles of row_tile rows and a remainder, except that an expert with row_tile + 1 ..
- * row_tile + 32 rows gets a single tile.  -1 for a negative count or another row_tile.  Host-only helper. */
+ * 128 as in moe_ffn_fp8_ex: tiles of row_tile rows and a remainder, except that an expert with row_tile + 1 ..
+ * row_tile + 32 rows gets a single tile.  For 0 the most it is cut into, the answer for 128: tiles of up to 256 rows,
+ * which a call takes or not by all its routed rows, are never more; workspace part 2 holds the number of row tiles that a
+ * call made.  -1 for a negative count or another row_tile.  Host-only helper. */
 int moe_ffn_fp8_row_tiles(int rows, int row_tile);
 
 /* Algorithmic FLOPs per routed (token, local expert) pair: 2 * (2I*H + H*I).  Host-only helper. */
