@@ -56,7 +56,8 @@ int gemm_bf16(const void *a, const void *b, void *c, int M, int N, int K,
  * 0 = what gemm_bf16 does: of 25616, 19216, 128, 1284 and 64 the shape with the best estimate of (throughput of the
  * shape on a full chip) x (how full its last round of workgroups leaves the 256 CUs); see gemm_bf16_auto_tile.
  * Any other value: ATTN_ERR_UNSUPPORTED.  Operands of the register-fed kernel take 64 x 64 tiles for 64, 128 x 64 tiles
- * for 1284 and 128 x 128 tiles for the other values; the general kernel ignores the choice.
+ * for 1284 and 128 x 128 tiles for the other values (64 x 64 for B stored [K, N] with N < 128, where those cannot run);
+ * the general kernel ignores the choice.
  * For tuning and for tests.
  */
 int gemm_bf16_tile(const void *a, const void *b, void *c, int M, int N, int K,

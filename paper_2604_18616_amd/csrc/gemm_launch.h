@@ -30,6 +30,6 @@ inline size_t gemm_plan_bytes(int M, int N, GemmPlan plan) { return plan.splits 
 int gemm_launch(GemmParams p, int b_is_nk, bool tiled, int tile, hipStream_t stream);
 
 // Operands that fail those alignment rules: whether the register-fed matrix-core kernel takes these sizes, and its
-// launch; `tile` is 0 (by size), 64, 1284 for 128 x 64 tiles, or anything else for 128 x 128.
+// launch; `tile` as `asked` of unaligned_tile (gemm_layout.h).
 bool gemm_unaligned_sizes(int N, int K, int b_is_nk);
 void gemm_unaligned_launch(const GemmParams& p, int b_is_nk, int tile, hipStream_t stream);

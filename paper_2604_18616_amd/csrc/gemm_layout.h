@@ -148,4 +148,22 @@ GEMM_HD TileCoord tile_coord(int bid, int nblocks, int tiles_m, int tiles_n) {
     return TileCoord{first + (rem - tn * rows), tn};
 }
 
+// Workgroup tile of the register-fed kernel (gemm_unaligned_kernel.hip) for an M x N result: 64 for 64 x 64, 1284 for 128 x 64,
+// 128 for 128 x 128, which for B stored [K,N] needs 128 columns.  asked: 0 = by size, 64 and 1284 themselves, anything else
+// 128 x 128 or, where that cannot run, 64 x 64.
+// By size: the bytes of the busiest CU, tiles per CU x (rows + columns); 128 x 128 tiles hold two stages in registers instead
+// of four and are charged 1.3 times theirs.  Measured, us, 64 x 64 / 128 x 64 / 128 x 128, M N K: 999 2001 1501:
+// 20.5 / 19.1 / 27.7; 1201 1201 1201: 17.0 / 16.5 / 23.6; 101 1501 2201: 13.4 / 22.6 / 34.6; 1501 1501 2499:
+// 45.0 / 46.4 / 41.6; 1801 1801 801: 23.7 / 20.9 / 18.5; 2001 2001 2001: 48.7 / 42.8 / 37.2; 2499 2499 2499:
+// 98 / 88 / 65: the rule takes the fastest of the three on each.  Without the third, B [K,N]: 30001 100 1501: 35.2 / 31.2;
+// 100001 127 1501: 168 / 142; 16385 100 301: 8.2 / 9.6.
+GEMM_HD int unaligned_tile(int M, int N, bool b_is_nk, int asked) {
+    const bool large_runs = b_is_nk || N >= 128;
+    if (asked != 0) return asked == 64 || asked == 1284 ? asked : large_runs ? 128 : 64;
+    const auto cost = [M, N](int bm, int bn) { return (((long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256) * (bm + bn); };
+    const long long small = 10 * cost(64, 64), tall = 10 * cost(128, 64), large = 13 * cost(128, 128);
+    if (large_runs && large < tall && large < small) return 128;
+    return tall < small ? 1284 : 64;
+}
+
 }  // namespace gemm_layout

@@ -230,18 +230,8 @@ void launch_unaligned(GemmParams p, int b_is_nk, hipStream_t stream) {
 bool gemm_unaligned_sizes(int N, int K, int b_is_nk) { return K >= kUBK && (b_is_nk || N >= USmall::BN); }
 
 void gemm_unaligned_launch(const GemmParams& p, int b_is_nk, int tile, hipStream_t stream) {
-    const auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
-    if (tile == 0) {
-        // The bytes of the busiest CU, tiles per CU x (rows + columns); 128 x 128 tiles hold two stages in registers instead
-        // of four and are charged 1.3 times theirs.  Measured, us, 64 x 64 / 128 x 64 / 128 x 128, M N K: 999 2001 1501:
-        // 20.5 / 19.1 / 27.7; 1201 1201 1201: 17.0 / 16.5 / 23.6; 101 1501 2201: 13.4 / 22.6 / 34.6; 1501 1501 2499:
-        // 45.0 / 46.4 / 41.6; 1801 1801 801: 23.7 / 20.9 / 18.5; 2001 2001 2001: 48.7 / 42.8 / 37.2; 2499 2499 2499:
-        // 98 / 88 / 65: the rule takes the fastest of the three on each.
-        const auto cost = [&](int bm, int bn) { return (double)((tiles(bm, bn) + 255) / 256 * (bm + bn)); };
-        const double small = cost(64, 64), tall = cost(128, 64), large = 1.3 * cost(128, 128);
-        tile = large < tall && large < small ? 128 : tall < small ? 1284 : 64;
-    }
+    tile = unaligned_tile(p.M, p.N, b_is_nk != 0, tile);
     if (tile == 1284) launch_unaligned<UTall>(p, b_is_nk, stream);
-    else if (tile != 64 && (b_is_nk || p.N >= ULarge::BN)) launch_unaligned<ULarge>(p, b_is_nk, stream);
+    else if (tile == 128) launch_unaligned<ULarge>(p, b_is_nk, stream);
     else launch_unaligned<USmall>(p, b_is_nk, stream);
 }

@@ -303,7 +303,23 @@ template <class T> static void check_tile_shape() {
     check_c_stage<T>();
 }
 
+// 7. the tile of the register-fed kernel: the fastest of the three measured ones, and never one that cannot run.
+static void check_unaligned_tile() {
+    struct { int M, N; bool nk; int want; } const sizes[] = {
+        {999, 2001, false, 1284}, {1201, 1201, false, 1284}, {101, 1501, false, 64}, {1501, 1501, false, 128}, {1801, 1801, false, 128},
+        {2001, 2001, true, 128}, {2499, 2499, false, 128},
+        {16385, 100, false, 64}, {30001, 100, false, 1284}, {65536, 100, false, 1284}, {100001, 127, false, 1284},   // too narrow for 128 x 128
+        {65536, 100, true, 128}, {100001, 128, false, 128}};
+    for (const auto& s : sizes)
+        CHECK(unaligned_tile(s.M, s.N, s.nk, 0) == s.want, "%d x %d: tile %d, not %d", s.M, s.N, unaligned_tile(s.M, s.N, s.nk, 0), s.want);
+    for (int N = 64; N < 200; ++N)
+        for (int M = 1; M < 200000; M += 997)
+            CHECK(unaligned_tile(M, N, false, 0) != 128 || N >= 128, "%d x %d: a tile wider than the result", M, N);
+    CHECK(unaligned_tile(500, 100, false, 128) == 64 && unaligned_tile(500, 100, true, 256) == 128 && unaligned_tile(500, 100, false, 1284) == 1284, "asked tiles");
+}
+
 int main() {
+    check_unaligned_tile();
     check_tile_shape<TileLarge>();
     check_tile_shape<TileLarge4>();
     check_tile_shape<TileSmall>();
