@@ -64,6 +64,30 @@ def test_no_memory_left_for_the_parts_means_no_cut(monkeypatch):
         assert (x.float() - y.float()).norm() <= 2.0 ** -7 * y.float().norm()
 
 
+def test_memory_for_the_parts_is_taken_only_where_the_call_can_be_cut(monkeypatch):
+    import torch
+    from paper_2604_18616_amd import attn_fwd, binding, gemm_bf16
+    asked, scratch = [], binding._scratch
+    monkeypatch.setattr(binding, "_scratch", lambda need, device: asked.append(need) or scratch(need, device))
+    empty = lambda *s: torch.zeros(s, device="cuda", dtype=torch.bfloat16)
+    a, b = empty(16, 4096), empty(512, 4096)
+    gemm_bf16(a, b, b_is_nk=True)
+    assert len(asked) == 1
+    shifted = empty(16 * 4096 + 1)[1:].view(16, 4096)             # a row that starts at an odd element
+    odd_pitch = empty(16, 4097)[:, :4096]
+    odd_result = empty(16, 513)[:, :512]
+    gemm_bf16(shifted, b, b_is_nk=True), gemm_bf16(odd_pitch, b, b_is_nk=True), gemm_bf16(a, b, odd_result, b_is_nk=True)
+    gemm_bf16(a, b, b_is_nk=True, tile=64), gemm_bf16(a, b, b_is_nk=True, stream=torch.cuda.Stream())
+    assert len(asked) == 1
+    q, k = empty(1, 2, 4, 128), empty(1, 2, 3000, 128)
+    attn_fwd(q, k, k)
+    assert len(asked) == 2
+    far = empty(3000, 1 << 20).view(1, 1, 3000, 1 << 20)[..., :128]      # one head of K spans more than 4 GiB
+    attn_fwd(q[:, :1], far, k[:, :1]), attn_fwd(q, k, k, stream=torch.cuda.Stream())
+    assert len(asked) == 2
+    torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1024, 2048), (100, 512, 4096), (256, 256, 2056), (512, 512, 4096)])
 def test_the_librarys_own_cut(M, N, K):
     from paper_2604_18616_amd import binding
