@@ -33,7 +33,8 @@ def run_split(a_bits, b_bits, b_is_nk, tile, splits, pad, given=None):
 CASES = [(256, 256, 512, 2, 0), (64, 64, 256, 4, 8), (1, 128, 1024, 16, 0), (70, 200, 840, 3, 16), (257, 264, 1096, 5, 0), (130, 72, 136, 7, 8), (16, 1024, 4096, 12, 0)]
 
 
-@pytest.mark.parametrize("tile", [64, 128, 1284, 25616, 19216])
+# every tile the entry point takes: the 32x32x16 and the 16x16x32 epilogue of each wavefront tile
+@pytest.mark.parametrize("tile", [64, 128, 1284, 256, 2564, 25616, 19216, 256416, 12816, 128416, 6416])
 @pytest.mark.parametrize("b_is_nk", [False, True])
 @pytest.mark.parametrize("M,N,K,splits,pad", CASES)
 def test_parts_add_up(M, N, K, splits, pad, b_is_nk, tile):

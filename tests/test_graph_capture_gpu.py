@@ -14,13 +14,20 @@ def dev_bf16(bits):
     return torch.from_numpy(bits.view(np.int16)).view(torch.bfloat16).cuda()
 
 
-def test_captured_calls_replay_to_the_eager_bits():
+# calls that are not cut, and calls whose keys or k are cut over workgroups (few and many parts), with memory that the binding
+# takes from torch, under capture from the graph's own pool
+@pytest.mark.parametrize("attn,gemm,cut", [((2, 4, 2, 300, 333), (520, 264, 200), False), ((1, 4, 2, 3, 3000), (16, 512, 4096), True),
+                                           ((2, 2, 1, 600, 2000), (256, 256, 2056), True), ((3, 4, 4, 20, 700), (300, 256, 4096), True)],
+                         ids=["uncut", "few_rows", "long_queries", "two_row_blocks"])
+def test_captured_calls_replay_to_the_eager_bits(attn, gemm, cut):
     import torch
     from paper_2604_18616_amd import binding
 
-    aw = I.Workload("g", 2, 4, 2, 300, 333, 128, True, 21)
+    aw = I.Workload("g", *attn, 128, True, 21)
     q, k, v = (dev_bf16(x) for x in I.make_qkv(aw))
-    gw = I.GemmWorkload("g", 520, 264, 200, 22)
+    gw = I.GemmWorkload("g", *gemm, 22)
+    lib = binding.load_library()
+    assert (lib.attn_fwd_workspace_bytes(*attn, 128) > 0) == cut and (lib.gemm_bf16_workspace_bytes(*gemm) > 0) == cut
     a, b = (dev_bf16(x) for x in I.make_ab(gw))
     mw = I.MoeWorkload("g", 150, 23, H=256, I=256, E=4, KTOP=2, EP=2)
     md = I.make_moe(mw)
