@@ -11,7 +11,7 @@
 // What bounds it: reading K and V once.  A workgroup of 4 wavefronts keeps 64-128 KB of copies in flight per CU,
 // and with one key group per wavefront (RB = 1) there is no barrier in the loop at all: a wavefront only waits for
 // its own copies.  Measured at D = 128, B Hq Hkv Sq Sk, against a 128-row workgroup per query head: 32 32 8 1 4096:
-// 299 -> 92 us (5.8 TB/s of K and V); 1 32 8 1 2000: 47.6 -> 9 us (two launches, latency); 1 8 1 4 60000: 1230 -> 15 us;
+// 295 -> 102 us (5.3 TB/s of K and V); 1 32 8 1 2000: 47.6 -> 10 us (two launches, latency); 1 8 1 4 60000: 1230 -> 15 us;
 // 2 64 8 4 9001: 191 -> 20 us; 1 8 8 33 5000: 110 -> 13 us; with few long heads the cut is what fills the chip, with
 // many heads that the heads of a group read K and V once instead of Hq / Hkv times.
 #include <hip/hip_runtime.h>
@@ -458,7 +458,7 @@ bool attn_split_wins(const AttnSplit& sp, int B, int Hq, int Sk, int D) {
 // it; two workgroups of two wavefronts per CU hide each other's start and end, which pays from several rounds of them
 // on; with two row blocks sharing tiles 0.9 and 2.2 us, with four 1.0 with one workgroup per CU and 1.25 with two (D 128; a
 // third adds nothing) or 0.75 with up to two and 1.5 with four (D 64); the combine costs 4 us, its traffic and its workgroups.
-// Estimate against measurement at D = 128, B Hq Hkv Sq Sk: 32 32 8 1 4096: 88 / 92 us (one split); 16 32 8 1 1000:
+// Estimate against measurement at D = 128, B Hq Hkv Sq Sk: 32 32 8 1 4096: 88 / 100 us (one split); 16 32 8 1 1000:
 // 12 / 15 us (two splits: 16 / 18); 40 8 8 1 5000: 163 / 159 us with one split, 146 / 143 us with four.
 AttnSplit attn_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int splits) {
     AttnSplit best;

@@ -175,8 +175,9 @@ __global__ __launch_bounds__(1024) void moe_prepare(MoeParams p, int stages) {
 // the rows its tile really has.  Up to 160 rows the weights come from HBM for that one tile and three LDS stages cover
 // the latency.  From there on the copies L2 -> LDS bound it (10 TB/s over the chip): a 256-row tile, whose 64 KB stages
 // fit twice, copies a third less per product than two of 128.  Gate/up + down, us, 128-row against 256-row tiles: 256
-// rows per expert (7168 x 2048, 32 experts) 771 -> 681; 2048 rows (4096 x 14336, 8 experts) 3587 -> 3099 (1860 TFLOP/s);
-// 192 rows (2048 x 1408, 64 experts) 229 -> 192; 512 rows (2048 x 768, 128 experts) 643 -> 548.
+// rows on each expert (7168 x 2048, 32 experts) 528 -> 470, 16384 tokens routed at random (259 +- 16 rows) 610 -> 566; 2048
+// rows (4096 x 14336, 8 experts) 3453 -> 2976 (1940 TFLOP/s); 192 rows (2048 x 1408, 64 experts) 230 -> 189; 512 rows
+// (2048 x 768, 128 experts) 583 -> 491.
 // Wavefront (wn, wm): weight rows 64 wn .. +63 as two 32-row MFMA operands, routed rows
 // (BM/2) wm .. in the lanes, BM/64 blocks of 32 (transposed product, as in the bf16 GEMM).
 //   UP:  the 256 weight rows of column tile nt are, per wavefront, 32 gate rows j and the 32 up
@@ -510,8 +511,10 @@ __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
     // Down product: column tiles of 256 weight rows, or of 128 when the wide ones would fill half the chip at most (few
     // experts in use, or a small H: 8 experts of 4096 x 14336 make 128 wide tiles).  The host sizes the grid for the
     // narrow tiles when the problem is small enough for that to happen (p.dn_narrow_ok); the choice itself needs the
-    // number of row tiles, known only here.  (With 128 to 256 wide tiles the narrow ones run two rounds of half the work
-    // at a lower rate; beyond, they are 3-15 % slower: measured.)
+    // number of row tiles, known only here.  Narrow against wide, us: 64 wide tiles (4 experts of 4096 x 1408, 100 rows)
+    // 12.0 / 16.8, 128 (8 of 4096 x 14336, 130 rows) 122 / 196, (8 of 1024 x 512, 1000 rows) 15.9 / 20.5; with more than
+    // 128 the narrow ones run two rounds: 144 (12 of 2944 x 1152, 100 rows) 21.2 / 17.0, 192 (8 of 1024 x 512, 700 rows)
+    // 15.3 / 13.2; with more than 256 they are 3-15 % slower.
     const int ntl = p.ntiles[0], bm = p.ntiles[1];
     const bool narrow = !UP && p.dn_narrow_ok && ntl * ((p.H + kMoeBN - 1) / kMoeBN) <= 128;
     const int NT = UP ? (p.I >> 7) : narrow ? (p.H >> 7) : (p.H + kMoeBN - 1) / kMoeBN;
