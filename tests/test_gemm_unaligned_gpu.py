@@ -1,6 +1,7 @@
 """gemm_bf16 on operands that are not 16-byte aligned, against the fp64 reference with the tolerance of
 test_gemm_parity_gpu: one stage along k and a fraction more, an overlap of all but one element, one tile along n and a
-fraction more, single rows, pitches and pointers that are odd, both tile sizes and both storages of B."""
+fraction more, single rows, pitches and pointers that are odd, all three tiles (for B stored [K,N] the 128 x 128 one from 128
+columns on) and both storages of B."""
 import numpy as np
 import pytest
 
