@@ -189,9 +189,8 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     # few query rows or few heads: cut the keys over workgroups too, with torch's memory for the parts (only on the stream torch
     # will reuse that memory on, and where the byte offsets inside a head fit the 32 bits that the cut works in; elsewhere the
     # call does without it)
-    need = (lib.attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D)
-            if own and (Sq <= 64 or B * Hq * Sq <= 160 * 128) and (Sk + 64) * max(kst[2], vst[2]) < 1 << 31 else 0)
-    ws = _scratch(need, device) if need else None
+    need = lib.attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Sk, D) if own and (Sq <= 64 or B * Hq * Sq <= 160 * 128) else 0
+    ws = _scratch(need, device) if need and (Sk + 64) * (kst[2] if kst[2] > vst[2] else vst[2]) < 1 << 31 else None
     if ws is not None:
         rc = lib.attn_fwd_workspace(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
                                     B, Hq, Hkv, Sq, Sk, D, _Int64x3(*qst[:3]), _Int64x3(*kst[:3]), _Int64x3(*vst[:3]), _Int64x3(*ost[:3]),
@@ -206,6 +205,11 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     if rc != 0:
         raise AttnError(rc, strerror(rc))
     return o, lse
+
+
+def _aligned(a, b, c):
+    """Whether the rows of three matrices start at multiples of 16 bytes."""
+    return not ((a.data_ptr() | b.data_ptr() | c.data_ptr()) & 15 or (a.stride(0) | b.stride(0) | c.stride(0)) & 7)
 
 
 def gemm_bf16(a, b, c=None, b_is_nk=False, stream=None, tile=0):
@@ -229,15 +233,16 @@ def gemm_bf16(a, b, c=None, b_is_nk=False, stream=None, tile=0):
         raise ValueError("c must be bfloat16 [M,N] with contiguous rows")
     stream, own = _streams(a, stream)
     lib = load_library()
-    pa, pb, pc, lda, ldb, ldc = a.data_ptr(), b.data_ptr(), c.data_ptr(), a.stride(0), b.stride(0), c.stride(0)
     # results of few tiles: cut k over workgroups too, with torch's memory for the parts (only on the stream torch will
     # reuse that memory on, and for operands of the aligned kernel; elsewhere the call does without it)
-    need = lib.gemm_bf16_workspace_bytes(M, N, K) if tile == 0 and own and not ((pa | pb | pc) & 15 or (lda | ldb | ldc) & 7) else 0
-    ws = _scratch(need, a.device) if need else None
+    need = lib.gemm_bf16_workspace_bytes(M, N, K) if tile == 0 and own else 0
+    ws = _scratch(need, a.device) if need and _aligned(a, b, c) else None
     if ws is not None:
-        rc = lib.gemm_bf16_workspace(pa, pb, pc, M, N, K, lda, ldb, ldc, 1 if b_is_nk else 0, 0, 0, ws.data_ptr(), need, stream)
+        rc = lib.gemm_bf16_workspace(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, a.stride(0), b.stride(0), c.stride(0),
+                                     1 if b_is_nk else 0, 0, 0, ws.data_ptr(), need, stream)
     else:
-        rc = lib.gemm_bf16_tile(pa, pb, pc, M, N, K, lda, ldb, ldc, 1 if b_is_nk else 0, int(tile), stream)
+        rc = lib.gemm_bf16_tile(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, a.stride(0), b.stride(0), c.stride(0),
+                                1 if b_is_nk else 0, int(tile), stream)
     if rc != 0:
         raise AttnError(rc, strerror(rc))
     return c
