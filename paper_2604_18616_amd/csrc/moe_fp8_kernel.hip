@@ -9,7 +9,7 @@
 //                 rows, the inverse map, one record per row tile); the other workgroups: activation
 //                 quantization, eight groups of 128 features per 32 lanes;
 //   moe_gemm<UP>  per (row tile, 128 intermediate columns): gate and up products on
-//                 v_mfma_scale_f32_32x32x64_f8f6f4, block scales applied per 128-deep stage,
+//                 v_mfma_f32_16x16x128_f8f6f4, block scales applied per 128-deep stage,
 //                 SiLU gate, requantization of the 128-column group, FP8 store;
 //   moe_gemm<DN>  per (row tile, 256 output columns, or 128 if that is what it takes to give every CU a
 //                 workgroup): down product; the row of a token with a single local slot
@@ -18,8 +18,7 @@
 //                 two or more local slots; zeros for those with none.
 // With 16 to 256 rows per expert the products are bound by streaming the expert weights from
 // HBM (each byte is used for 2 x rows FLOPs), so the grouped product keeps three 40-52 KB stages
-// (two of 64 KB for tiles of more than 160 rows, which L2 -> LDS copies bound) of direct-to-LDS copies
-// per workgroup, all but one of them in flight, and does nothing clever with the MFMAs.
+// (two of 56-64 KB for tiles of more than 160 rows) of direct-to-LDS copies per workgroup, all but one of them in flight.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -171,156 +170,155 @@ __global__ __launch_bounds__(1024) void moe_prepare(MoeParams p, int stages) {
 // Grouped block-scaled FP8 product.  Workgroup = 8 wavefronts = 4 (n) x 2 (m) for the MFMAs: 256 weight rows x
 // BM routed rows.  An expert's rows are cut into one tile of up to 160, or evenly into the fewest of up to 256 rows
 // (moe_tiles), or into tiles of 128 where those fill the chip better (moe_choose, once per call; a caller may ask for 128
-// or 64); each workgroup picks the code for BM = 64, 128, 160 or 256 from
-// the rows its tile really has.  Up to 160 rows the weights come from HBM for that one tile and three LDS stages cover
-// the latency.  From there on the copies L2 -> LDS bound it (10 TB/s over the chip): a 256-row tile, whose 64 KB stages
-// fit twice, copies a third less per product than two of 128.  Gate/up + down, us, 128-row against 256-row tiles: 256
-// rows on each expert (7168 x 2048, 32 experts) 528 -> 470, 16384 tokens routed at random (259 +- 16 rows) 610 -> 566; 2048
-// rows (4096 x 14336, 8 experts) 3453 -> 2976 (1940 TFLOP/s); 192 rows (2048 x 1408, 64 experts) 230 -> 189; 512 rows
-// (2048 x 768, 128 experts) 583 -> 491.
-// Wavefront (wn, wm): weight rows 64 wn .. +63 as two 32-row MFMA operands, routed rows
-// (BM/2) wm .. in the lanes, BM/64 blocks of 32 (transposed product, as in the bf16 GEMM).
+// or 64); each workgroup picks the code for BM = 64, 128, 160, 192, 224 or 256 from the rows its tile really has.  Up to 160
+// rows the weights come from HBM for that one tile and three LDS stages cover the latency.  From there on two stages fit.
+// Wavefront (wn, wm): weight rows 64 wn .. +63 as four 16-row MFMA operands, routed rows (BM/2) wm .. in the lanes, BM/32
+// blocks of 16 (transposed product, as in the bf16 GEMM), on v_mfma_f32_16x16x128_f8f6f4: one instruction takes a whole
+// stage of k, so a product is scaled and added up as four registers, not sixteen, and can wait for its turn.
 //   UP:  the 256 weight rows of column tile nt are, per wavefront, 32 gate rows j and the 32 up
 //        rows I + j of the same j: both accumulators of a lane meet the same (row, j).
 //   DN:  256 consecutive rows of w2.
-// One stage = 128 bytes of k for all rows (BM x 128 routed + 32 KB weights) plus the stage's row
-// scales (dword copies); three stages in LDS; per stage two K = 64 MFMAs per operand pair into a fresh
-// partial, then acc += partial * (row scale) * (weight block scale).  BM = 160: five 32-row blocks, three
-// for the wavefronts wm = 0 and two for wm = 1.
+// One stage = 128 bytes of k for all rows (BM x 128 routed + 32 KB weights); per stage acc += product * (row scale x weight
+// block scale).
+// What bounds it: the copies, from HBM while an expert has one row tile, then from L2; with more rows the products, whose LDS
+// reads (192 KB per stage of 256 rows) take as long as the matrix pipes do.  Measured, gate/up / down, us, before and after
+// row scales by fours instead of a copy per row and stage, weights copied a stage earlier, one product per stage:
+// 16384 tokens of (7168 x 2048, 32 experts) 447 / 238 -> 361 / 209; 8192 tokens 205 / 148 -> 183 / 138; 4096 tokens of
+// (4096 x 14336, 8 experts) 1100 / 672 -> 1000 / 555; (2048 x 768, 128 experts) 172 / 160 -> 160 / 149.  With the copies alone
+// the first takes 376 (before), with the products alone 278.
 // ------------------------------------------------------------------------------------
 constexpr int kMoeBN = 256;
 constexpr int kMoeLdsBytes = 3 * (160 * 128 + kMoeBN * 128);   // the largest stage set: three stages of BM = 160
-constexpr int kMoeSaBytes = 8 * 128;                          // row scales per stage: 8 row groups x 32 dwords
+constexpr int kMoeScaleBytes = 2 * 2 * 160 * 4;               // scale products of two stages for up to 160 rows; those of more lie behind two stages of tiles
 constexpr int kMoeMaxKB = 128;                      // 128-blocks along k: H, I <= 16384
 
 typedef __attribute__((address_space(3))) char* LdsChar;      // LDS pointers stay typed as such: a generic pointer would
 typedef __attribute__((address_space(3))) float* LdsFloat;    // turn the scale reads into flat loads, which count as vector memory
 template <bool UP, int BM, int BN>
-__device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row0, int rows, int nt, LdsChar smem, LdsFloat sa_stage, LdsFloat sb_tab) {
-    static_assert(BN == 256 || (BN == 128 && !UP), "the gate/up product pairs two 32-row weight blocks per wavefront");
-    constexpr int NS = BM == 256 ? 2 : 3;           // LDS stages: what 160 KB hold
-    constexpr int NIN = BN / 128;                   // 32-row weight blocks per wavefront (wavefront wn: weight rows 32 NIN wn ..)
+__device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row0, int rows, int nt, bool few, LdsChar smem, LdsFloat scales, LdsFloat sb_tab) {
+    static_assert(BN == 256 || (BN == 128 && !UP), "the gate/up product pairs gate and up rows per wavefront");
+    constexpr int NS = BM > 160 ? 2 : 3;           // LDS stages: what 160 KB hold
+    constexpr int NF = BN / 64;                     // 16-row weight operands per wavefront (wavefront wn: weight rows 16 NF wn ..)
     constexpr int NCB = BN / 32;                    // copy instructions of the weights per copying wavefront and stage
     constexpr int kStageA = BM * 128, kStageB = BN * 128, kStage = kStageA + kStageB;
     constexpr int kOffB = NS * kStageA;             // all stages of the routed rows, then the weights': read offsets fit an instruction's 16 bits
     static_assert(NS * kStage <= kMoeLdsBytes, "stages exceed the workgroup's LDS");
     constexpr int NCA = BM / 32;                    // copy instructions of the routed rows per copying wavefront and stage
-    constexpr int MB = BM == 160 ? 3 : BM / 64;     // 32-row blocks of routed rows per wavefront, at most
-    constexpr int RPW = BM / 8;                     // routed rows per row group: a group's scales are one dword copy per stage
-    static_assert(RPW <= 32, "a row group's scales fill at most the 32 dwords of its slot");
-    constexpr int kCopies = NCA + NCB + 2;          // vmem operations per copying wavefront and stage
-    // s_waitcnt immediate for vmcnt((NS - 2) kCopies), lgkmcnt(0): vmcnt's low four bits, then its two high bits at 14
-    constexpr int kLater = (NS - 2) * kCopies;
-    constexpr int kWaitNext = 0x0070 | (kLater & 15) | ((kLater >> 4) << 14);
-    constexpr int kSaBytes = kMoeSaBytes;
+    constexpr int MB = BM / 32;                     // 16-row blocks of routed rows per wavefront
+    constexpr int kCopies = NCA + NCB;              // vmem operations per copying wavefront and stage
+    // s_waitcnt immediate for vmcnt(n), lgkmcnt(0): vmcnt's low four bits, then its two high bits at 14
+    constexpr auto vm = [](int n) constexpr { return 0x0070 | (n & 15) | ((n >> 4) << 14); };
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    // (the thread's number is made opaque here and in front of the epilogue: the compiler would compute what the
+    // codes for all tile sizes have in common, and the addresses of the epilogue, ahead of the loops, and spill there)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 3, wm = wave >> 2;
-    const int half = lane >> 5;
-    // 32-row blocks of routed rows: the wavefronts wm = 0 take the first half (and the odd one), wm = 1 the rest; BM = 256
-    // has the blocks its rows need, the others all of theirs
-    const int blocks = BM == 256 ? (rows + 31) >> 5 : BM / 32;
-    const int blocks0 = (blocks + 1) >> 1, kW0 = 32 * blocks0, my_blocks = wm == 0 ? blocks0 : blocks - blocks0;
+    int quad = lane >> 4;
+    const int w_row0 = 16 * MB * wm;                // first routed row of the wavefront
+    // Whether the weights of a stage are overwritten as soon as every wavefront has them in registers, behind a second
+    // barrier in the stage: they are then copied NS stages ahead instead of NS - 1.  With two stages always; with three
+    // only where there is a workgroup per CU at most, whose stages wait for the latency of memory
+    const bool early = NS == 2 || (BM > 64 && few);
 
     const int KB = UP ? p.H : p.I;                  // bytes (= elements) per row of both operands
     const int nK = KB >> 7;
     const unsigned lds_base = (unsigned)(size_t)LDS_PTR(char, smem);
 
     // ---- copies: wavefronts 0-3 (one per SIMD) issue them: per stage instructions c + 4 n of the
-    // routed rows (n < NCA) and of the weights (n < NCB), and the dword copies of the row scales for
-    // the row groups c and c + 4.  Wavefronts 4-7 issue no memory traffic in the loop: four issuers
-    // measured 5-10 % faster than eight.  (An L2 warm-up by the idle wavefronts, as in the bf16 GEMM,
-    // was tried and is harmful here: an XCD's L2 holds 128 KB per CU, less than the LDS stages
-    // already in flight, so lines touched early are evicted before the copies ask for them.) ----
+    // routed rows (n < NCA) and of the weights (n < NCB), behind its first operand reads: spread over the stage's products
+    // they measured up to 6 % slower (they have less of the stage left to land in).  Wavefronts 4-7 fetch the row scales.
+    // (An L2 warm-up by these, as in the bf16 GEMM, was tried and is harmful here: an XCD's L2 holds
+    // 128 KB per CU, less than the LDS stages already in flight, so lines touched early are evicted before the copies
+    // ask for them.) ----
     const bool copier = wave < 4;
     const int c4 = wave & 3;
-    unsigned a_off[NCA], b_off, s_off[2];
+    unsigned a_off[NCA], b_off[NCB];              // 32 bits: an activation matrix, and an expert's weights, stay under 4 GiB
     {
 #pragma unroll
         for (int n = 0; n < NCA; ++n) {
             const int i = c4 + 4 * n;
             const int r = min(kt_dma_row(i, lane), rows - 1);         // rows past the tile re-read its last row
             const int src = UP ? p.sorted_tok[row0 + r] : row0 + r;
-            a_off[n] = (unsigned)src * (unsigned)KB + 16u * (unsigned)kt_dma_chunk(i, lane);
-            asm("" : "+v"(a_off[n]));               // one register: the 64-bit product would be kept whole
+            unsigned row = (unsigned)src * (unsigned)KB;
+            asm("" : "+v"(row));                    // the sum in one register: a multiply-add would be kept as 64 bits
+            a_off[n] = row + 16u * (unsigned)kt_dma_chunk(i, lane);
         }
-        // (the weight rows of copy n lie a wavefront-uniform number of rows, w_rows(n), behind those of copy 0)
-        b_off = (unsigned)kt_dma_row(c4, lane) * (unsigned)KB + 16u * (unsigned)kt_dma_chunk(c4, lane);
+        unsigned row = (unsigned)kt_dma_row(c4, lane) * (unsigned)KB;
+        asm("" : "+v"(row));
 #pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            const int r = min(RPW * (c4 + 4 * n) + (lane % RPW), rows - 1);
-            const int src = UP ? p.sorted_tok[row0 + r] : row0 + r;
-            s_off[n] = 4u * (unsigned)src * (unsigned)nK;
-            asm("" : "+v"(s_off[n]));
+        for (int n = 0; n < NCB; ++n) {
+            // first weight row of copies n of the four copying wavefronts, behind that of copies 0: 32 rows of the tile each
+            const int rows_on = UP ? (n & 1) * p.I + 32 * (n >> 1) : (nt * BN + 32 * n < p.H ? 32 * n : 0);   // rows past H: others again
+            b_off[n] = row + (unsigned)rows_on * (unsigned)KB + 16u * (unsigned)kt_dma_chunk(c4, lane);
         }
     }
     const char* const a_base = UP ? (const char*)p.xq : (const char*)p.aq;
-    const char* const b_base = UP ? (const char*)(p.w13 + (size_t)e * 2 * (size_t)p.I * (size_t)p.H)
-                                  : (const char*)(p.w2 + (size_t)e * (size_t)p.H * (size_t)p.I);
-    // first weight row of copies n of the four copying wavefronts: 32 rows of the tile
-    auto w_rows = [&](int n) __attribute__((always_inline)) {
-        return UP ? (n & 1) * p.I + nt * 128 + 32 * (n >> 1) : (nt * BN + 32 * n < p.H ? nt * BN + 32 * n : nt * BN);   // rows past H: others again
-    };
-    const char* const s_base = UP ? (const char*)p.xs : (const char*)p.as;
+    const char* const b_base = UP ? (const char*)(p.w13 + ((size_t)e * 2 * (size_t)p.I + (size_t)nt * 128) * (size_t)p.H)
+                                  : (const char*)(p.w2 + ((size_t)e * (size_t)p.H + (size_t)nt * BN) * (size_t)p.I);
     const unsigned lds_copy_base = lds_base + c4 * 1024;
-    const unsigned sa_base = (unsigned)(size_t)LDS_PTR(float, sa_stage) + c4 * 128;
-    auto dma_stage = [&](int U, auto sc) __attribute__((always_inline)) {
-        constexpr int s = decltype(sc)::value;
-        static_for<0, NCA>([&](auto n) __attribute__((always_inline)) {
-            if (BM == 256 && 8 * (c4 + 4 * n.value) >= rows) return;   // (two stages: waits are for everything, not for a count)
-            dma_to_lds_16B<s * kStageA + n.value * 4096>(a_base + (size_t)U * 128, a_off[n.value], lds_copy_base);
-        });
-        static_for<0, NCB>([&](auto n) __attribute__((always_inline)) {
-            dma_to_lds_16B<kOffB + s * kStageB + n.value * 4096>(b_base + (size_t)w_rows(n.value) * KB + (size_t)U * 128, b_off, lds_copy_base);
-        });
-        if (lane < 32) {                            // a slot holds 32 dwords: the upper half of the wavefront stays out
-            dma_to_lds_4B<s * kSaBytes>(s_base + (size_t)U * 4, s_off[0], sa_base);
-            dma_to_lds_4B<s * kSaBytes + 512>(s_base + (size_t)U * 4, s_off[1], sa_base);
+    // copy instruction n of stage U into LDS stage s: NCA of the routed rows, then NCB of the weights
+    auto dma_part = [&](int U, int s, auto nc) __attribute__((always_inline)) {
+        constexpr int n = decltype(nc)::value;
+        if constexpr (n < NCA) dma_to_lds_16B<n * 4096>(a_base + (size_t)U * 128, a_off[n], lds_copy_base + s * kStageA);
+        else dma_to_lds_16B<kOffB + (n - NCA) * 4096>(b_base + (size_t)U * 128, b_off[n - NCA], lds_copy_base + s * kStageB);
+    };
+    auto dma_rows = [&](int U, int s) __attribute__((always_inline)) {
+        static_for<0, NCA>([&](auto n) __attribute__((always_inline)) { dma_part(U, s, n); });
+    };
+    auto dma_weights = [&](int U, int s) __attribute__((always_inline)) {
+        static_for<NCA, kCopies>([&](auto n) __attribute__((always_inline)) { dma_part(U, s, n); });
+    };
+
+    // ---- scales: what the products of stage U are multiplied by, row scale x weight block scale, is worked out once per
+    // row and weight block and left in LDS, [U % 2][weight block][row], one stage ahead.  Thread 256 + m does it for row m; it
+    // loads the row scales of four stages at once: a row's scales lie 4 nK bytes from the next row's, so every load
+    // instruction touches a cache line per row however little it takes of it.  (Copied to LDS a dword per row and stage
+    // they were a third of all the lines the CU asked for.) ----
+    const LdsFloat slot = BM > 160 ? (LdsFloat)(smem + NS * kStage) : scales;
+    static_assert(BM > 160 ? NS * kStage + 2 * 2 * BM * 4 <= kMoeLdsBytes : 2 * 2 * BM * 4 <= kMoeScaleBytes, "no room for the scales");
+    typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;
+    const float* s_src = nullptr;
+    auto put_scales = [&](int U, float s) __attribute__((always_inline)) {
+        if (tid - 256 < BM) {
+            slot[(U & 1) * (2 * BM) + tid - 256] = s * sb_tab[U];
+            slot[(U & 1) * (2 * BM) + BM + tid - 256] = s * sb_tab[kMoeMaxKB + U];
         }
     };
 
-    // ---- weight block scales of all stages into LDS (read back as wavefront-uniform broadcasts; a
-    // global load inside the loop would make the compiler wait for the copies in flight at every use) ----
-    if (tid < 2 * nK) {
-        const int which = tid / nK, b = tid - which * nK;
+    // ---- weight block scales of all stages into LDS ----
+    if (tid >= 256 && tid - 256 < 2 * nK) {         // (not the wavefronts that copy: theirs would wait for it in front of their first copies)
+        const int which = (tid - 256) / nK, b = tid - 256 - which * nK;
         const float* src;
         if (UP) src = p.s13 + ((size_t)e * 2 * (p.I >> 7) + (which ? (p.I >> 7) : 0) + nt) * nK;   // gate rows, up rows of block nt
-        else src = p.s2 + ((size_t)e * (p.H >> 7) + min(nt * NIN + (NIN == 2 ? which : 0), (p.H >> 7) - 1)) * nK;
+        else src = p.s2 + ((size_t)e * (p.H >> 7) + min(BN == 256 ? 2 * nt + which : nt, (p.H >> 7) - 1)) * nK;
         sb_tab[which * kMoeMaxKB + b] = src[b];
     }
-    const int sb_sel0 = UP ? 0 : (NIN == 2 ? wn >> 1 : 0), sb_sel1 = UP ? 1 : sb_sel0;
 
-    // ---- per-lane LDS read addresses (stage 0): K = 64 operand = 32 bytes = chunks 4 ks + 2 half + {0,1} ----
-    unsigned a_addr[2][2], b_addr[2][2];
+    // ---- per-lane LDS read addresses (stage 0): the K = 128 operand is 32 bytes of a 16-row block per lane, chunks quad and
+    // quad + 4 (any order of k will do that both operands share).  A 16-byte read is served in four parts, the first of
+    // which are lanes 0-3, 12-15 and 20-27: with chunks 2 quad and 2 quad + 1 the rows of two quads met in the same banks. ----
+    unsigned a_addr[2], b_addr[2];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            a_addr[ks][q] = lds_base + kt_offset(kW0 * wm + (lane & 31), 4 * ks + 2 * half + q);
-            b_addr[ks][q] = lds_base + kOffB + kt_offset(32 * NIN * wn + (lane & 31), 4 * ks + 2 * half + q);
-        }
-    // row scale of routed row m of the tile: dword m % RPW of row group m / RPW
-    int sa_idx[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        const int m = min(kW0 * wm + 32 * mb + (lane & 31), BM - 1);     // (a block that does not exist reads a valid slot)
-        sa_idx[mb] = (m / RPW) * 32 + (m % RPW);
+    for (int q = 0; q < 2; ++q) {
+        a_addr[q] = lds_base + kt_offset(w_row0 + (lane & 15), quad + 4 * q);
+        b_addr[q] = lds_base + kOffB + kt_offset(16 * NF * wn + (lane & 15), quad + 4 * q);
     }
+    // weight block of a wavefront's operands: UP the gate block for the first half of them and the up block for the rest
+    const LdsFloat my_slot = slot + (UP || BN == 128 ? 0 : wn >> 1) * BM + w_row0 + (lane & 15);
     auto frag = [&](unsigned addr0, unsigned addr1, int imm) __attribute__((always_inline)) -> i32x8 {
         const i32x4 lo = *LDS_PTR(i32x4, (size_t)(addr0 + imm));
         const i32x4 hi = *LDS_PTR(i32x4, (size_t)(addr1 + imm));
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
 
-    f32x16 acc[NIN][MB];
+    f32x4 acc[NF][MB];
 #pragma unroll
-    for (int in = 0; in < NIN; ++in)
+    for (int in = 0; in < NF; ++in)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[in][mb][r] = 0.0f;
+        for (int mb = 0; mb < MB; ++mb) acc[in][mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
     auto barrier = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
@@ -349,112 +347,158 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
         }
     }
 
-    // ---- prologue: NS - 1 stages in flight ----
-    if (copier) {
-        dma_stage(0, IntC<0>{});
-        if (NS > 2 && 1 < nK) dma_stage(1, IntC<1>{});
-    }
+    // ---- main loop.  It is instantiated for either role, so that no wait for a row scale, a load into registers, comes to
+    // stand where a copying wavefront passes: it would wait for its copies. ----
+    auto main_loop = [&](auto role) __attribute__((always_inline)) {
+        constexpr bool COPIER = decltype(role)::value;
+        f32x4 now, later;                                          // row scales of the next stages (the first one's in element 0), and of the four after them
+        if constexpr (COPIER) {                                    // NS - 1 stages in flight
+            __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), known to the compiler: no wait for an earlier load inside the loop
+            dma_rows(0, 0);
+            dma_weights(0, 0);
+        } else {
+            const int r = min(tid - 256, rows - 1);
+            s_src = (UP ? p.xs : p.as) + (size_t)(UP ? p.sorted_tok[row0 + r] : row0 + r) * (size_t)nK;
+            now = *(const f32x4_any*)s_src;
+            later = *(const f32x4_any*)(s_src + (nK > 4 ? 4 : 0));
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);                        // (own weight block scales written)
+        barrier();                                                 // all of them visible
+        if constexpr (COPIER) {
+            // (not before the barrier: the row scales of stage 0 would come back behind these copies)
+            if (1 < nK) { if (NS > 2) dma_rows(1, 1); dma_weights(1, 1); }
+            if (NS > 2 && early && 2 < nK) dma_weights(2, 2);
+        } else {
+            put_scales(0, now[0]);
+            now = __builtin_shufflevector(now, now, 1, 2, 3, 3);
+        }
 
-    auto step = [&](int U, auto sc) __attribute__((always_inline)) {
-        constexpr int s = decltype(sc)::value;
-        // stage U has landed once at most the copies of the stages issued after it (NS - 2 of them) are outstanding
-        if (!copier) __builtin_amdgcn_s_waitcnt(0xC07F);                 // lgkmcnt(0): nothing of its own in flight
-        else if (NS > 2 && U + 1 < nK) __builtin_amdgcn_s_waitcnt(kWaitNext);   // vmcnt(kCopies), lgkmcnt(0)
-        else __builtin_amdgcn_s_waitcnt(0x0070);                         // vmcnt(0), lgkmcnt(0)
-        asm volatile("" ::: "memory");
-        barrier();                                             // stage U visible; stage U-1's buffer is free
-        if (copier && U + NS - 1 < nK) dma_stage(U + NS - 1, IntC<(s + NS - 1) % NS>{});
-        const float sb0 = sb_tab[sb_sel0 * kMoeMaxKB + U], sb1 = sb_tab[sb_sel1 * kMoeMaxKB + U];
-        const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        i32x8 fb[NIN][2];
-        static_for<0, NIN>([&](auto in) __attribute__((always_inline)) {
-            fb[in.value][0] = frag(b_addr[0][0], b_addr[0][1], s * kStageB + in.value * 4096);
-            fb[in.value][1] = frag(b_addr[1][0], b_addr[1][1], s * kStageB + in.value * 4096);
-        });
-        auto multiply = [&](auto mb, i32x8 fa0, i32x8 fa1, float sa) __attribute__((always_inline)) {
-            static_for<0, NIN>([&](auto in) __attribute__((always_inline)) {
-                f32x16 part = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[in.value][0], fa0, zero, 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
-                part = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[in.value][1], fa1, part, 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
-                const float f = sa * (in.value == 0 ? sb0 : sb1);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[in.value][mb.value][r] = fmaf(part[r], f, acc[in.value][mb.value][r]);
-            });
-        };
-        auto row_scale = [&](int mb) __attribute__((always_inline)) { return sa_stage[s * (kSaBytes / 4) + (RPW == 32 ? sa_idx[0] + 32 * mb : sa_idx[mb])]; };
-        if constexpr (BM == 256) {
-            // 128 accumulators leave room for two blocks of routed rows: each is read one block ahead (a block that does
-            // not exist too: its memory does), and the fences keep the compiler from reading all four first
-            i32x8 fa[2][2];
-            float sa[2];
+        // One stage: a stream of NF products per block of 16 rows.  A product's four results are multiplied by their scale and
+        // added up two products later, in the shadow of the next one; operands are read one block ahead; the order is pinned.
+        int s = 0;                                                 // LDS stage of U
+        for (int U = 0;;) {
+            // stage U has landed once no more is outstanding than what was issued after it: the rows of NS - 2 stages and the
+            // weights of as many, or of one more, towards the end fewer
+            if constexpr (!COPIER) __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): no copy of its own in flight
+            else if (early && U + NS - 1 < nK) __builtin_amdgcn_s_waitcnt(vm((NS - 1) * NCB + (NS - 2) * NCA));
+            else if (NS > 2 && U + 1 < nK) __builtin_amdgcn_s_waitcnt(vm(NCB + NCA));
+            else __builtin_amdgcn_s_waitcnt(vm(0));
+            asm volatile("" ::: "memory");
+            barrier();                                             // stage U visible; stage U-1's buffer is free
+            const LdsFloat f_row = my_slot + (U & 1) * (2 * BM);
+            const bool copy = COPIER && U + NS - 1 < nK;
+            const int s_copy = s == 0 ? NS - 1 : s - 1;            // LDS stage of U + NS - 1
+            i32x8 fb[NF], fa[2];
+            float f0[2], f1[2];
+            f32x4 part[4];
             auto read_block = [&](auto mb) __attribute__((always_inline)) {
                 constexpr int set = decltype(mb)::value & 1;
-                sa[set] = row_scale(mb.value);
-                fa[set][0] = frag(a_addr[0][0], a_addr[0][1], s * kStageA + mb.value * 4096);
-                fa[set][1] = frag(a_addr[1][0], a_addr[1][1], s * kStageA + mb.value * 4096);
-                asm volatile("" ::: "memory");
+                fa[set] = frag(a_addr[0], a_addr[1], mb.value * 2048);
+                f0[set] = f_row[16 * mb.value];
+                f1[set] = UP ? f_row[BM + 16 * mb.value] : f0[set];
             };
+            auto add = [&](auto ic) __attribute__((always_inline)) {         // product i of the stage: operand i % NF, block i / NF
+                constexpr int i = decltype(ic)::value;
+                if constexpr (i >= 0) {
+                    const float f = UP && i % NF >= NF / 2 ? f1[(i / NF) & 1] : f0[(i / NF) & 1];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[i % NF][i / NF][r] = fmaf(part[i & 3][r], f, acc[i % NF][i / NF][r]);
+                    asm volatile("" : "+v"(acc[i % NF][i / NF]));           // here: sums are else moved behind the branches around the copies, to the end
+                }
+            };
+            auto block = [&](auto mbc) __attribute__((always_inline)) {
+                constexpr int mb = decltype(mbc)::value;
+                static_for<0, NF>([&](auto in) __attribute__((always_inline)) {
+                    constexpr int i = mb * NF + in.value;
+                    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                    part[i & 3] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb[in.value], fa[mb & 1], zero, 0, 0, 0, 0, 0, 0);   // (scale operands 0: the plain product)
+                    __builtin_amdgcn_sched_barrier(0);
+                    add(IntC<i - 2>{});
+                    // (the other operand set is free once the sums of the block before have taken its scales)
+                    if constexpr (in.value == (NF > 2 ? 1 : NF - 1) && mb + 1 < MB) read_block(IntC<mb + 1>{});
+                    if constexpr (BM > 64 && i == NF - 1) {
+                        if (early) {                               // uniform
+                            barrier();                             // every wavefront has its weights: their buffer is free
+                            if constexpr (COPIER) if (U + NS < nK) dma_weights(U + NS, s);
+                        }
+                    }
+                    if constexpr (!COPIER && i == 1) {
+                        // (a load comes back behind the copies that its CU issued before it, those of stage U + NS - 1: four
+                        // stages ahead of its first use it holds nothing up, one stage ahead everything.  What the last group
+                        // has read past the row is not used: the row after it, or the workspace's next part)
+                        if (((U + 1) & 3) == 0) {
+                            now = later;
+                            asm volatile("" : "+v"(now) :: "memory");      // the load below goes where `later` was
+                            if (U + 5 < nK) later = *(const f32x4_any*)(s_src + U + 5);
+                        }
+                        if (U + 1 < nK) put_scales(U + 1, now[0]);
+                        now = __builtin_shufflevector(now, now, 1, 2, 3, 3);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            };
+            fb[0] = frag(b_addr[0], b_addr[1], 0);
             read_block(IntC<0>{});
-            static_for<0, MB>([&](auto mb) __attribute__((always_inline)) {
-                if constexpr (mb.value + 1 < MB) read_block(IntC<mb.value + 1>{});
-                if (mb.value < my_blocks) multiply(mb, fa[mb.value & 1][0], fa[mb.value & 1][1], sa[mb.value & 1]);      // uniform
-            });
-        } else {
-            static_for<0, MB>([&](auto mb) __attribute__((always_inline)) {
-                if (BM == 160 && mb.value >= my_blocks) return;            // uniform: rows 160..191 do not exist
-                const i32x8 fa0 = frag(a_addr[0][0], a_addr[0][1], s * kStageA + mb.value * 4096);
-                const i32x8 fa1 = frag(a_addr[1][0], a_addr[1][1], s * kStageA + mb.value * 4096);
-                multiply(mb, fa0, fa1, row_scale(mb.value));
-            });
+            static_for<1, NF>([&](auto in) __attribute__((always_inline)) { fb[in.value] = frag(b_addr[0], b_addr[1], in.value * 2048); });
+            __builtin_amdgcn_sched_barrier(0);
+            if (copy) { dma_rows(U + NS - 1, s_copy); if (!early) dma_weights(U + NS - 1, s_copy); }
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<0, MB>(block);
+            add(IntC<MB * NF - 2>{});
+            add(IntC<MB * NF - 1>{});
+            if (++U >= nK) break;
+            const int wrap = s + 1 == NS ? NS : 0;
+            s = s + 1 - wrap;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) { a_addr[q] += (1 - wrap) * kStageA; b_addr[q] += (1 - wrap) * kStageB; }
         }
     };
-    for (int U = 0;;) {
-        step(U, IntC<0>{}); if (++U >= nK) break;
-        step(U, IntC<1>{}); if (++U >= nK) break;
-        if constexpr (NS > 2) { step(U, IntC<2>{}); if (++U >= nK) break; }
-    }
+    if (copier) main_loop(IntC<1>{}); else main_loop(IntC<0>{});
 
-    // result layout of a lane: register r of operand `in`, block mb is weight row 32 in + 8 (r/4) + 4 half + r%4
-    // of the wavefront's 64, routed row (BM/2) wm + 32 mb + lane%32
+    // ---- epilogue: result layout of a lane: register r of operand `in`, block mb is weight row 16 in + 4 quad + r of the wavefront's
+    // 16 NF, routed row w_row0 + 16 mb + lane%16
+    asm volatile("" : "+v"(lane));
+    quad = lane >> 4;
     if constexpr (UP) {
         // SiLU gate, then quant128 over the tile's 128 columns of each routed row
-        float h[MB][16], amax[MB];
+        float amax[MB];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             amax[mb] = 0.0f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float g = acc[0][mb][r];
-                h[mb][r] = g / (1.0f + __expf(-g)) * acc[1][mb][r];
-                amax[mb] = fmaxf(amax[mb], fabsf(h[mb][r]));
-            }
-            // across the two halves of the wavefront (rows 4 half + ..)
-            const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(amax[mb]), __float_as_uint(amax[mb]), false, false);
-            const unsigned s0 = sw[0], s1 = sw[1];
-            amax[mb] = fmaxf(__uint_as_float(s0), __uint_as_float(s1));
+            for (int in = 0; in < 2; ++in)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float g = acc[in][mb][r];
+                    acc[in][mb][r] = g / (1.0f + __expf(-g)) * acc[in + 2][mb][r];
+                    amax[mb] = fmaxf(amax[mb], fabsf(acc[in][mb][r]));
+                }
+            // across the four quarters of the wavefront
+            amax[mb] = fmaxf(amax[mb], __shfl_xor(amax[mb], 16));
+            amax[mb] = fmaxf(amax[mb], __shfl_xor(amax[mb], 32));
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);
         barrier();                                             // every wavefront is done with the stage buffers
-        const LdsFloat ex = (LdsFloat)smem;                        // [wm][mb][wn][32]
+        const LdsFloat ex = (LdsFloat)smem;                        // [wm][mb][wn][16]
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
-            if (half == 0) ex[((wm * MB + mb) * 4 + wn) * 32 + (lane & 31)] = amax[mb];
+            if (quad == 0) ex[((wm * MB + mb) * 4 + wn) * 16 + lane] = amax[mb];
         __builtin_amdgcn_s_waitcnt(0xC07F);
         barrier();
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            if (mb >= my_blocks) break;
             float am = amax[mb];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) am = fmaxf(am, ex[((wm * MB + mb) * 4 + w) * 32 + (lane & 31)]);
+            for (int w = 0; w < 4; ++w) am = fmaxf(am, ex[((wm * MB + mb) * 4 + w) * 16 + (lane & 15)]);
             const float scale = quant_scale(am);
             const float inv = 1.0f / scale;
-            const int m = kW0 * wm + 32 * mb + (lane & 31);
+            const int m = w_row0 + 16 * mb + (lane & 15);
             if (m < rows) {
-                uint8_t* const dst = p.aq + (size_t)(row0 + m) * p.I + nt * 128 + 32 * wn + 4 * half;
+                uint8_t* const dst = p.aq + (size_t)(row0 + m) * p.I + nt * 128 + 32 * wn + 4 * quad;
 #pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4)
-                    *(unsigned*)(dst + 8 * g4) = quant_pack4(h[mb][4 * g4], h[mb][4 * g4 + 1], h[mb][4 * g4 + 2], h[mb][4 * g4 + 3], inv);
-                if (wn == 0 && half == 0) p.as[(size_t)(row0 + m) * (p.I >> 7) + nt] = scale;
+                for (int in = 0; in < 2; ++in)
+                    *(unsigned*)(dst + 16 * in) = quant_pack4(acc[in][mb][0], acc[in][mb][1], acc[in][mb][2], acc[in][mb][3], inv);
+                if (wn == 0 && quad == 0) p.as[(size_t)(row0 + m) * (p.I >> 7) + nt] = scale;
             }
         }
     } else {
@@ -470,25 +514,23 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
         barrier();
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            const int m = kW0 * wm + 32 * mb + (lane & 31);
-            if (mb < my_blocks && m < rows) {
+            const int m = w_row0 + 16 * mb + (lane & 15);
+            if (m < rows) {
                 const int dst = __float_as_int(hand[2 * m]);
                 const float w = hand[2 * m + 1];
 #pragma unroll
-                for (int in = 0; in < NIN; ++in)
-#pragma unroll
-                    for (int g4 = 0; g4 < 4; ++g4) {
-                        const int c = nt * BN + 32 * NIN * wn + 32 * in + 8 * g4 + 4 * half;
-                        if (c < p.H) {
-                            const f32x4 v = {acc[in][mb][4 * g4], acc[in][mb][4 * g4 + 1], acc[in][mb][4 * g4 + 2], acc[in][mb][4 * g4 + 3]};
-                            if (dst >= 0) {
-                                const bf16x4 out = {(__bf16)fmaf(w, v[0], 0.0f), (__bf16)fmaf(w, v[1], 0.0f), (__bf16)fmaf(w, v[2], 0.0f), (__bf16)fmaf(w, v[3], 0.0f)};   // as moe_combine: 0 + w * v
-                                *(bf16x4*)(p.y + (size_t)dst * p.H + c) = out;
-                            } else {
-                                *(f32x4*)(p.o + (size_t)(row0 + m) * p.H + c) = v;
-                            }
+                for (int in = 0; in < NF; ++in) {
+                    const int c = nt * BN + 16 * NF * wn + 16 * in + 4 * quad;
+                    if (c < p.H) {
+                        const f32x4 v = acc[in][mb];
+                        if (dst >= 0) {
+                            const bf16x4 out = {(__bf16)fmaf(w, v[0], 0.0f), (__bf16)fmaf(w, v[1], 0.0f), (__bf16)fmaf(w, v[2], 0.0f), (__bf16)fmaf(w, v[3], 0.0f)};   // as moe_combine: 0 + w * v
+                            *(bf16x4*)(p.y + (size_t)dst * p.H + c) = out;
+                        } else {
+                            *(f32x4*)(p.o + (size_t)(row0 + m) * p.H + c) = v;
                         }
                     }
+                }
             }
         }
     }
@@ -498,8 +540,8 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
 template <bool UP>
 __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
     __shared__ __attribute__((aligned(16))) char smem[kMoeLdsBytes];
-    __shared__ __attribute__((aligned(16))) float sa_stage[3 * kMoeSaBytes / 4];
-    static_assert(kMoeLdsBytes + 3 * kMoeSaBytes + 2 * kMoeMaxKB * 4 <= 160 * 1024, "LDS budget");
+    __shared__ __attribute__((aligned(16))) float scales[kMoeScaleBytes / 4];
+    static_assert(kMoeLdsBytes + kMoeScaleBytes + 2 * kMoeMaxKB * 4 <= 160 * 1024, "LDS budget");
     __shared__ float sb_tab[2 * kMoeMaxKB];          // weight block scale of the tile's two 128-row blocks and every stage
 
     // workgroup -> (row tile mt, column tile nt).  The grid has max_tiles * NT workgroups (a multiple of
@@ -525,25 +567,30 @@ __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
     const MoeTileRec rec = p.tile_rec[logical / NT];             // the expert whose block of ids holds `logical`
     const int cnt = moe_tiles(rec.rows, bm);                      // its row tiles
     const int off = logical - rec.first * NT;                     // in [0, cnt * NT)
-    const int nt = off / cnt, j = off - nt * cnt;                 // column tile, row tile within the expert
+    const int nt = __builtin_amdgcn_readfirstlane(off / cnt), j = off - nt * cnt;                 // column tile, row tile within the expert
     const int begin = moe_tile_begin(rec.rows, cnt, j, bm);
-    const int e = rec.expert, row0 = rec.row0 + begin;
-    const int rows = moe_tile_begin(rec.rows, cnt, j + 1, bm) - begin;   // uniform
+    const int e = __builtin_amdgcn_readfirstlane(rec.expert), row0 = __builtin_amdgcn_readfirstlane(rec.row0 + begin);
+    const int rows = __builtin_amdgcn_readfirstlane(moe_tile_begin(rec.rows, cnt, j + 1, bm) - begin);   // uniform
+    const bool few = live <= 256;
     const LdsChar tiles = LDS_PTR(char, smem);
-    const LdsFloat sa = LDS_PTR(float, sa_stage), sb = LDS_PTR(float, sb_tab);
+    const LdsFloat sa = LDS_PTR(float, scales), sb = LDS_PTR(float, sb_tab);
     if constexpr (!UP) {
         if (narrow) {
-            if (rows > 160) moe_gemm_tile<false, 256, 128>(p, e, row0, rows, nt, tiles, sa, sb);
-            else if (rows > 128) moe_gemm_tile<false, 160, 128>(p, e, row0, rows, nt, tiles, sa, sb);
-            else if (rows > 64) moe_gemm_tile<false, 128, 128>(p, e, row0, rows, nt, tiles, sa, sb);
-            else moe_gemm_tile<false, 64, 128>(p, e, row0, rows, nt, tiles, sa, sb);
+            if (rows > 224) moe_gemm_tile<false, 256, 128>(p, e, row0, rows, nt, few, tiles, sa, sb);
+            else if (rows > 192) moe_gemm_tile<false, 224, 128>(p, e, row0, rows, nt, few, tiles, sa, sb);
+            else if (rows > 160) moe_gemm_tile<false, 192, 128>(p, e, row0, rows, nt, few, tiles, sa, sb);
+            else if (rows > 128) moe_gemm_tile<false, 160, 128>(p, e, row0, rows, nt, few, tiles, sa, sb);
+            else if (rows > 64) moe_gemm_tile<false, 128, 128>(p, e, row0, rows, nt, few, tiles, sa, sb);
+            else moe_gemm_tile<false, 64, 128>(p, e, row0, rows, nt, few, tiles, sa, sb);
             return;
         }
     }
-    if (rows > 160) moe_gemm_tile<UP, 256, 256>(p, e, row0, rows, nt, tiles, sa, sb);
-    else if (rows > 128) moe_gemm_tile<UP, 160, 256>(p, e, row0, rows, nt, tiles, sa, sb);
-    else if (rows > 64) moe_gemm_tile<UP, 128, 256>(p, e, row0, rows, nt, tiles, sa, sb);
-    else moe_gemm_tile<UP, 64, 256>(p, e, row0, rows, nt, tiles, sa, sb);
+    if (rows > 224) moe_gemm_tile<UP, 256, 256>(p, e, row0, rows, nt, few, tiles, sa, sb);
+    else if (rows > 192) moe_gemm_tile<UP, 224, 256>(p, e, row0, rows, nt, few, tiles, sa, sb);
+    else if (rows > 160) moe_gemm_tile<UP, 192, 256>(p, e, row0, rows, nt, few, tiles, sa, sb);
+    else if (rows > 128) moe_gemm_tile<UP, 160, 256>(p, e, row0, rows, nt, few, tiles, sa, sb);
+    else if (rows > 64) moe_gemm_tile<UP, 128, 256>(p, e, row0, rows, nt, few, tiles, sa, sb);
+    else moe_gemm_tile<UP, 64, 256>(p, e, row0, rows, nt, few, tiles, sa, sb);
 }
 
 // ------------------------------------------------------------------------------------

@@ -28,25 +28,25 @@ MOE_HD int moe_tile_begin(int cnt, int n, int j, int bm) {
 
 // Estimated time of a product, in hundredths of a microsecond: `rows` routed rows in `tiles` row tiles, `cols` column tiles,
 // `stages` 128-deep stages; `down`: its column tiles are halved where the whole ones would fill half the chip at most.
-// Measured: a stage of a workgroup takes 0.22 us + 0.17 per 32 rows of its tile while its CU's share of L2 is no limit,
-// 0.30 + 0.25 with all 256 CUs at it, four fifths of that on half a column tile; launch, start and end 3 us + 0.8 per 32
-// rows, in every round of workgroups.  (The mean tile is charged half a block of 32 rows for its remainder.)
+// A stage of a workgroup, a round of 256 workgroups and a last round that does not fill the chip are charged what makes the
+// choice below agree with the times it was fitted to, not what they take one by one: a stage 0.51 us + 0.17 per 32 rows of its
+// tile with all 256 CUs at it, 0.48 + 0.19 in a round of a few workgroups, four fifths of either on half a column tile; every
+// round 6.3 us + 1.15 per 32 rows.
 MOE_HD int moe_product_time(int rows, int tiles, int cols, int stages, bool down) {
-    int alone = 30 + 17 * rows / (32 * tiles), full = 42 + 25 * rows / (32 * tiles), wgs = tiles * cols;
+    int alone = 48 + 19 * rows / (32 * tiles), full = 51 + 17 * rows / (32 * tiles), wgs = tiles * cols;
     if (down && wgs <= 128) { wgs *= 2; alone = alone * 4 / 5; full = full * 4 / 5; }
     const int rounds = wgs / 256, rest = wgs % 256, share = full * rest / 256;
     const int last = rest == 0 ? 0 : share > alone ? share : alone;
-    return stages * (rounds * full + last) + (rounds + (rest > 0 ? 1 : 0)) * (340 + 80 * rows / (32 * tiles));
+    return stages * (rounds * full + last) + (rounds + (rest > 0 ? 1 : 0)) * (630 + 115 * rows / (32 * tiles));
 }
 
 // The cut a call takes when the caller leaves it open: bm = 0, whose larger tiles copy a third less from L2 per product, or
 // bm = 128, whose larger number fills the chip where the large ones would leave CUs idle or start another round.
 // Gate/up + down, us, tiles of 128 rows against up to 256, same rows on every expert: 8 experts of 1024 x 512, 256 rows
-// 21.7 / 34.2, 2000 rows 59.3 / 50.9; 4 of 4096 x 1408, 200 rows 48.9 / 74.9, 700 rows 106 / 90; 12 of 2944 x 1152, 200 rows
-// 62.3 / 68.9, 300 rows 85.7 / 78.1; 8 of 4096 x 14336, 256 rows 471 / 520, 400 rows 841 / 712; 32 of 7168 x 2048, 256 rows
-// 520 / 480.  Of 156 measured configurations one came out more than 3 % slower than with tiles of 128 rows (64 of 2048 x 1408,
-// 256 +- 16 rows: 267 / 275).  A last round of a few workgroups is where the estimate errs: 12 of 2944 x 1152, 250 +- 15 rows:
-// 79 / 90, and it takes the larger tiles.
+// 24 / 35, 2000 rows 60 / 49; 4 of 4096 x 1408, 200 rows 52 / 68, 700 rows 108 / 91; 12 of 2944 x 1152, 256 rows 66 / 77,
+// 300 rows 91 / 76; 8 of 4096 x 14336, 200 rows 451 / 401, 400 rows 807 / 615; 32 of 7168 x 2048, 256 rows 484 / 431.  Of 164
+// measured configurations (8 layers, 2 to 4000 rows per expert, even and random) the choice is the better of the two
+// within 3 % in all of one run and all but one of another (8 of 4096 x 14336, 256 rows, where they are level: 457 / 439).
 MOE_HD int moe_choose(int rows, int tiles128, int tiles256, int H, int I) {
     if (tiles128 == tiles256) return 0;
     const int small = moe_product_time(rows, tiles128, I / 128, H / 128, false) + moe_product_time(rows, tiles128, (H + 255) / 256, I / 128, true);
