@@ -76,9 +76,14 @@ extern "C" int moe_ffn_fp8_ex(const void* x, const int* ids, const float* wts,
     p.w13 = (const uint8_t*)w13; p.s13 = s13; p.w2 = (const uint8_t*)w2; p.s2 = s2;
     p.y = (__bf16*)y;
     p.T = T; p.H = H; p.I = I; p.E = E; p.KTOP = KTOP;
-    // how an expert's rows are cut into tiles (moe_layout.h); each tile runs the 64-, 128-, 160- or 256-row code that fits
-    // the rows it really has.  `bm_override` is for tests
-    p.bm = bm_override;
+    // how an expert's rows are cut into tiles (moe_layout.h); each tile runs the 64- to 256-row code that fits the rows
+    // it really has.  `bm_override` is for tests
+    // Few rows per expert on average, also if every slot were local: the kernel whose workgroups share a CU by twos.  Its tiles
+    // have 32 rows; an expert with more reads its weights again.  Gate/up + down, us, against the 64-row code: 170 tokens
+    // x 6 on 64 experts of 2048 x 1408 (16 slots per expert, 7 to 25 rows) 104 -> 94, 300 x 6 (28 slots, 16 to 38 rows) 107 -> 124;
+    // up to 12 slots per expert leave room for one that is favoured almost threefold.
+    p.few = bm_override == 0 && (long long)T * KTOP <= 12LL * E ? 1 : 0;
+    p.bm = p.few ? 64 : bm_override;
     const int bound = p.bm ? p.bm : 128;                 // (neither of the library's two cuts makes more tiles than that)
     p.max_tiles = (int)(((size_t)T * KTOP + bound - 1) / bound + E);
     // narrow column tiles of the down product are for problems whose wide tiles would not fill the chip: the grid is

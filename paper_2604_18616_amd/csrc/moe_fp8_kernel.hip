@@ -189,6 +189,7 @@ __global__ __launch_bounds__(1024) void moe_prepare(MoeParams p, int stages) {
 // ------------------------------------------------------------------------------------
 constexpr int kMoeBN = 256;
 constexpr int kMoeLdsBytes = 3 * (160 * 128 + kMoeBN * 128);   // the largest stage set: three stages of BM = 160
+constexpr int kMoeFewLdsBytes = 3 * 32 * 128 + 2 * kMoeBN * 128;   // of a workgroup with BM = 32
 constexpr int kMoeScaleBytes = 2 * 2 * 160 * 4;               // scale products of two stages for up to 160 rows; those of more lie behind two stages of tiles
 constexpr int kMoeMaxKB = 128;                      // 128-blocks along k: H, I <= 16384
 
@@ -197,12 +198,14 @@ typedef __attribute__((address_space(3))) float* LdsFloat;    // turn the scale 
 template <bool UP, int BM, int BN>
 __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row0, int rows, int nt, bool few, LdsChar smem, LdsFloat scales, LdsFloat sb_tab) {
     static_assert(BN == 256 || (BN == 128 && !UP), "the gate/up product pairs gate and up rows per wavefront");
-    constexpr int NS = BM > 160 ? 2 : 3;           // LDS stages: what 160 KB hold
+    // LDS stages of the weights and of the routed rows: what 160 KB hold, with BM = 32 twice (a third of the rows of 192 or
+    // 224, which would fit, measured no difference)
+    constexpr int NB = BM > 160 || (BM == 32 && BN == 256) ? 2 : 3, NA = BM > 160 ? 2 : 3;
     constexpr int NF = BN / 64;                     // 16-row weight operands per wavefront (wavefront wn: weight rows 16 NF wn ..)
     constexpr int NCB = BN / 32;                    // copy instructions of the weights per copying wavefront and stage
-    constexpr int kStageA = BM * 128, kStageB = BN * 128, kStage = kStageA + kStageB;
-    constexpr int kOffB = NS * kStageA;             // all stages of the routed rows, then the weights': read offsets fit an instruction's 16 bits
-    static_assert(NS * kStage <= kMoeLdsBytes, "stages exceed the workgroup's LDS");
+    constexpr int kStageA = BM * 128, kStageB = BN * 128, kStages = NA * kStageA + NB * kStageB;
+    constexpr int kOffB = NA * kStageA;             // all stages of the routed rows, then the weights': read offsets fit an instruction's 16 bits
+    static_assert(kStages <= (BM == 32 ? kMoeFewLdsBytes : kMoeLdsBytes), "stages exceed the workgroup's LDS");
     constexpr int NCA = BM / 32;                    // copy instructions of the routed rows per copying wavefront and stage
     constexpr int MB = BM / 32;                     // 16-row blocks of routed rows per wavefront
     constexpr int kCopies = NCA + NCB;              // vmem operations per copying wavefront and stage
@@ -219,9 +222,10 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     int quad = lane >> 4;
     const int w_row0 = 16 * MB * wm;                // first routed row of the wavefront
     // Whether the weights of a stage are overwritten as soon as every wavefront has them in registers, behind a second
-    // barrier in the stage: they are then copied NS stages ahead instead of NS - 1.  With two stages always; with three
+    // barrier in the stage: they are then copied NB stages ahead instead of NB - 1.  With two stages always; with three
     // only where there is a workgroup per CU at most, whose stages wait for the latency of memory
-    const bool early = NS == 2 || (BM > 64 && few);
+    constexpr bool kCanBeEarly = BM != 64;
+    const bool early = NB == 2 || (kCanBeEarly && few);
 
     const int KB = UP ? p.H : p.I;                  // bytes (= elements) per row of both operands
     const int nK = KB >> 7;
@@ -277,8 +281,8 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     // loads the row scales of four stages at once: a row's scales lie 4 nK bytes from the next row's, so every load
     // instruction touches a cache line per row however little it takes of it.  (Copied to LDS a dword per row and stage
     // they were a third of all the lines the CU asked for.) ----
-    const LdsFloat slot = BM > 160 ? (LdsFloat)(smem + NS * kStage) : scales;
-    static_assert(BM > 160 ? NS * kStage + 2 * 2 * BM * 4 <= kMoeLdsBytes : 2 * 2 * BM * 4 <= kMoeScaleBytes, "no room for the scales");
+    const LdsFloat slot = BM > 160 ? (LdsFloat)(smem + kStages) : scales;
+    static_assert(BM > 160 ? kStages + 2 * 2 * BM * 4 <= kMoeLdsBytes : 2 * 2 * BM * 4 <= kMoeScaleBytes, "no room for the scales");
     typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;
     const float* s_src = nullptr;
     auto put_scales = [&](int U, float s) __attribute__((always_inline)) {
@@ -352,7 +356,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     auto main_loop = [&](auto role) __attribute__((always_inline)) {
         constexpr bool COPIER = decltype(role)::value;
         f32x4 now, later;                                          // row scales of the next stages (the first one's in element 0), and of the four after them
-        if constexpr (COPIER) {                                    // NS - 1 stages in flight
+        if constexpr (COPIER) {                                    // one to three stages in flight
             __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), known to the compiler: no wait for an earlier load inside the loop
             dma_rows(0, 0);
             dma_weights(0, 0);
@@ -366,8 +370,8 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
         barrier();                                                 // all of them visible
         if constexpr (COPIER) {
             // (not before the barrier: the row scales of stage 0 would come back behind these copies)
-            if (1 < nK) { if (NS > 2) dma_rows(1, 1); dma_weights(1, 1); }
-            if (NS > 2 && early && 2 < nK) dma_weights(2, 2);
+            if (1 < nK) { if (NA > 2) dma_rows(1, 1); dma_weights(1, 1); }
+            if (NB > 2 && early && 2 < nK) dma_weights(2, 2);
         } else {
             put_scales(0, now[0]);
             now = __builtin_shufflevector(now, now, 1, 2, 3, 3);
@@ -375,19 +379,17 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
 
         // One stage: a stream of NF products per block of 16 rows.  A product's four results are multiplied by their scale and
         // added up two products later, in the shadow of the next one; operands are read one block ahead; the order is pinned.
-        int s = 0;                                                 // LDS stage of U
+        int sa = 0, sb = 0;                                        // LDS stages of U
         for (int U = 0;;) {
-            // stage U has landed once no more is outstanding than what was issued after it: the rows of NS - 2 stages and the
-            // weights of as many, or of one more, towards the end fewer
+            // stage U has landed once no more is outstanding than what was issued after it: NB - 1 stages of weights if they are
+            // copied early, else one less, and the rows issued with them, towards the end fewer
             if constexpr (!COPIER) __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): no copy of its own in flight
-            else if (early && U + NS - 1 < nK) __builtin_amdgcn_s_waitcnt(vm((NS - 1) * NCB + (NS - 2) * NCA));
-            else if (NS > 2 && U + 1 < nK) __builtin_amdgcn_s_waitcnt(vm(NCB + NCA));
+            else if (NA == NB && early && U + NB - 1 < nK) __builtin_amdgcn_s_waitcnt(vm((NB - 1) * NCB + (NB - 2) * NCA));
+            else if (NA > 2 && U + 1 < nK) __builtin_amdgcn_s_waitcnt(vm(NCB + NCA));
             else __builtin_amdgcn_s_waitcnt(vm(0));
             asm volatile("" ::: "memory");
             barrier();                                             // stage U visible; stage U-1's buffer is free
             const LdsFloat f_row = my_slot + (U & 1) * (2 * BM);
-            const bool copy = COPIER && U + NS - 1 < nK;
-            const int s_copy = s == 0 ? NS - 1 : s - 1;            // LDS stage of U + NS - 1
             i32x8 fb[NF], fa[2];
             float f0[2], f1[2];
             f32x4 part[4];
@@ -416,14 +418,14 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
                     add(IntC<i - 2>{});
                     // (the other operand set is free once the sums of the block before have taken its scales)
                     if constexpr (in.value == (NF > 2 ? 1 : NF - 1) && mb + 1 < MB) read_block(IntC<mb + 1>{});
-                    if constexpr (BM > 64 && i == NF - 1) {
+                    if constexpr (kCanBeEarly && i == NF - 1) {
                         if (early) {                               // uniform
                             barrier();                             // every wavefront has its weights: their buffer is free
-                            if constexpr (COPIER) if (U + NS < nK) dma_weights(U + NS, s);
+                            if constexpr (COPIER) if (U + NB < nK) dma_weights(U + NB, sb);
                         }
                     }
                     if constexpr (!COPIER && i == 1) {
-                        // (a load comes back behind the copies that its CU issued before it, those of stage U + NS - 1: four
+                        // (a load comes back behind the copies that its CU issued before it, those of the next stages: four
                         // stages ahead of its first use it holds nothing up, one stage ahead everything.  What the last group
                         // has read past the row is not used: the row after it, or the workspace's next part)
                         if (((U + 1) & 3) == 0) {
@@ -441,16 +443,20 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
             read_block(IntC<0>{});
             static_for<1, NF>([&](auto in) __attribute__((always_inline)) { fb[in.value] = frag(b_addr[0], b_addr[1], in.value * 2048); });
             __builtin_amdgcn_sched_barrier(0);
-            if (copy) { dma_rows(U + NS - 1, s_copy); if (!early) dma_weights(U + NS - 1, s_copy); }
+            if constexpr (COPIER) {
+                if (U + NA - 1 < nK) dma_rows(U + NA - 1, sa == 0 ? NA - 1 : sa - 1);
+                if (!early && U + NB - 1 < nK) dma_weights(U + NB - 1, sb == 0 ? NB - 1 : sb - 1);
+            }
             __builtin_amdgcn_sched_barrier(0);
             static_for<0, MB>(block);
             add(IntC<MB * NF - 2>{});
             add(IntC<MB * NF - 1>{});
             if (++U >= nK) break;
-            const int wrap = s + 1 == NS ? NS : 0;
-            s = s + 1 - wrap;
+            const int wrap_a = sa + 1 == NA ? NA : 0, wrap_b = sb + 1 == NB ? NB : 0;
+            sa += 1 - wrap_a;
+            sb += 1 - wrap_b;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) { a_addr[q] += (1 - wrap) * kStageA; b_addr[q] += (1 - wrap) * kStageB; }
+            for (int q = 0; q < 2; ++q) { a_addr[q] += (1 - wrap_a) * kStageA; b_addr[q] += (1 - wrap_b) * kStageB; }
         }
     };
     if (copier) main_loop(IntC<1>{}); else main_loop(IntC<0>{});
@@ -536,6 +542,55 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     }
 }
 
+// Workgroup -> row tile and column tile; false if there is none for it (uniform, before any barrier).  The grid has
+// max_tiles * NT workgroups (a multiple of 8), of which ntiles * NT are live; XCD x (= blockIdx % 8) takes the x-th eighth
+// of the live logical ids in order, so the workgroups resident on an XCD are neighbours.  Logical order: expert by expert;
+// inside an expert column tile by column tile, the expert's row tiles innermost: neighbours share their weight tile (same
+// nt) or their routed rows (same row tile), which the XCD's L2 then fetches once.
+struct MoeTile { int e, row0, rows, nt; };
+__device__ __forceinline__ bool moe_tile_of(const MoeParams& p, int NT, int live, int bm, MoeTile& t) {
+    const int per_xcd = (live + 7) >> 3, bid = blockIdx.x, logical = (bid & 7) * per_xcd + (bid >> 3);
+    if ((bid >> 3) >= per_xcd || logical >= live) return false;
+    const MoeTileRec rec = p.tile_rec[logical / NT];             // the expert whose block of ids holds `logical`
+    const int cnt = moe_tiles(rec.rows, bm);                      // its row tiles
+    const int off = logical - rec.first * NT;                     // in [0, cnt * NT)
+    const int nt = off / cnt, j = off - nt * cnt;                 // column tile, row tile within the expert
+    const int begin = moe_tile_begin(rec.rows, cnt, j, bm);
+    t.e = __builtin_amdgcn_readfirstlane(rec.expert);
+    t.row0 = __builtin_amdgcn_readfirstlane(rec.row0 + begin);
+    t.rows = __builtin_amdgcn_readfirstlane(moe_tile_begin(rec.rows, cnt, j + 1, bm) - begin);
+    t.nt = __builtin_amdgcn_readfirstlane(nt);
+    return true;
+}
+
+// Kernel for few rows per expert (MoeParams::few): tiles of 32 rows in two stages of weights and three of rows (three of either
+// where the column tiles are halved), so that two workgroups share a CU and one starts and ends while the other streams.  Reading the weights bounds it:
+// gate/up / down, us, against the 64-row code with one workgroup per CU: 40 tokens of (2048 x 1408, 64 experts) 68.7 / 32.2
+// -> 63.1 / 28.7, 60 of (2048 x 768, 128 experts) 71.3 / 40.0 -> 66.4 / 31.8, 64 of (7168 x 2048, 32 experts) 129 / 66 -> 126 / 62.
+template <bool UP>
+__global__ __launch_bounds__(512, 4) void moe_gemm_few(MoeParams p) {
+    constexpr int BM = 32;
+    __shared__ __attribute__((aligned(16))) char smem[kMoeFewLdsBytes];
+    __shared__ __attribute__((aligned(16))) float scales[2 * 2 * BM];
+    static_assert(2 * (kMoeFewLdsBytes + 2 * 2 * BM * 4 + 2 * kMoeMaxKB * 4) <= 160 * 1024, "LDS budget");
+    __shared__ float sb_tab[2 * kMoeMaxKB];
+    const int ntl = p.ntiles[0], bm = p.ntiles[1];
+    const bool narrow = !UP && p.dn_narrow_ok && ntl * ((p.H + kMoeBN - 1) / kMoeBN) <= 128;       // as in moe_gemm
+    const int NT = UP ? (p.I >> 7) : narrow ? (p.H >> 7) : (p.H + kMoeBN - 1) / kMoeBN;
+    MoeTile t;
+    if (!moe_tile_of(p, NT, ntl * NT, bm, t)) return;
+    const LdsChar tiles = LDS_PTR(char, smem);
+    const LdsFloat sa = LDS_PTR(float, scales), sb = LDS_PTR(float, sb_tab);
+    for (int r = 0; r < t.rows; r += BM) {           // (a favoured expert's tile has up to 96 rows)
+        if (r > 0) __syncthreads();                  // the epilogue's reads of what the next copies overwrite
+        const int rows = min(BM, t.rows - r);
+        if constexpr (!UP) {
+            if (narrow) { moe_gemm_tile<false, BM, 128>(p, t.e, t.row0 + r, rows, t.nt, true, tiles, sa, sb); continue; }
+        }
+        moe_gemm_tile<UP, BM, 256>(p, t.e, t.row0 + r, rows, t.nt, true, tiles, sa, sb);
+    }
+}
+
 // Kernel: maps the workgroup to its (row tile, column tile) and runs the tile code that fits the tile's rows.
 template <bool UP>
 __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
@@ -544,12 +599,6 @@ __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
     static_assert(kMoeLdsBytes + kMoeScaleBytes + 2 * kMoeMaxKB * 4 <= 160 * 1024, "LDS budget");
     __shared__ float sb_tab[2 * kMoeMaxKB];          // weight block scale of the tile's two 128-row blocks and every stage
 
-    // workgroup -> (row tile mt, column tile nt).  The grid has max_tiles * NT workgroups (a multiple of
-    // 8), of which ntiles * NT are live; XCD x (= blockIdx % 8) takes the x-th eighth of the live logical
-    // ids in order, so the ~32 workgroups resident on an XCD are neighbours.  Logical order: expert by
-    // expert; inside an expert column tile by column tile, the expert's row tiles innermost: neighbours
-    // share their weight tile (same nt) or their routed rows (same mt), which the XCD's L2 then
-    // fetches once.
     // Down product: column tiles of 256 weight rows, or of 128 when the wide ones would fill half the chip at most (few
     // experts in use, or a small H: 8 experts of 4096 x 14336 make 128 wide tiles).  The host sizes the grid for the
     // narrow tiles when the problem is small enough for that to happen (p.dn_narrow_ok); the choice itself needs the
@@ -560,17 +609,10 @@ __global__ __launch_bounds__(512, 1) void moe_gemm(MoeParams p) {
     const int ntl = p.ntiles[0], bm = p.ntiles[1];
     const bool narrow = !UP && p.dn_narrow_ok && ntl * ((p.H + kMoeBN - 1) / kMoeBN) <= 128;
     const int NT = UP ? (p.I >> 7) : narrow ? (p.H >> 7) : (p.H + kMoeBN - 1) / kMoeBN;
-    const int live = ntl * NT, per_xcd = (live + 7) >> 3;
-    const int bid = blockIdx.x;
-    const int logical = (bid & 7) * per_xcd + (bid >> 3);
-    if ((bid >> 3) >= per_xcd || logical >= live) return;   // uniform: before any barrier
-    const MoeTileRec rec = p.tile_rec[logical / NT];             // the expert whose block of ids holds `logical`
-    const int cnt = moe_tiles(rec.rows, bm);                      // its row tiles
-    const int off = logical - rec.first * NT;                     // in [0, cnt * NT)
-    const int nt = __builtin_amdgcn_readfirstlane(off / cnt), j = off - nt * cnt;                 // column tile, row tile within the expert
-    const int begin = moe_tile_begin(rec.rows, cnt, j, bm);
-    const int e = __builtin_amdgcn_readfirstlane(rec.expert), row0 = __builtin_amdgcn_readfirstlane(rec.row0 + begin);
-    const int rows = __builtin_amdgcn_readfirstlane(moe_tile_begin(rec.rows, cnt, j + 1, bm) - begin);   // uniform
+    const int live = ntl * NT;
+    MoeTile t;
+    if (!moe_tile_of(p, NT, live, bm, t)) return;
+    const int e = t.e, row0 = t.row0, rows = t.rows, nt = t.nt;
     const bool few = live <= 256;
     const LdsChar tiles = LDS_PTR(char, smem);
     const LdsFloat sa = LDS_PTR(float, scales), sb = LDS_PTR(float, sb_tab);
@@ -680,8 +722,13 @@ int moe_launch(const MoeParams& p, int first, int last, hipStream_t stream) {
     auto grid8 = [](long long n) { return dim3((unsigned)((n + 7) / 8 * 8)); };   // the tile order wants a multiple of 8
     const dim3 g_up = grid8((long long)p.max_tiles * (p.I / 128)),
                g_dn = grid8((long long)p.max_tiles * (p.dn_narrow_ok ? p.H / 128 : (p.H + kMoeBN - 1) / kMoeBN));
-    if (on(2)) hipLaunchKernelGGL((moe_gemm<true>), g_up, dim3(512), 0, stream, p);
-    if (on(3)) hipLaunchKernelGGL((moe_gemm<false>), g_dn, dim3(512), 0, stream, p);
+    if (p.few) {
+        if (on(2)) hipLaunchKernelGGL((moe_gemm_few<true>), g_up, dim3(512), 0, stream, p);
+        if (on(3)) hipLaunchKernelGGL((moe_gemm_few<false>), g_dn, dim3(512), 0, stream, p);
+    } else {
+        if (on(2)) hipLaunchKernelGGL((moe_gemm<true>), g_up, dim3(512), 0, stream, p);
+        if (on(3)) hipLaunchKernelGGL((moe_gemm<false>), g_dn, dim3(512), 0, stream, p);
+    }
     if (on(4)) {
         // parts of a token's columns: enough wavefronts for the chip (8192 slots) down to one pass of 512 columns each
         const int most = (p.H + 511) / 512, want = (8192 + p.T - 1) / p.T, segs = want < most ? want : most;

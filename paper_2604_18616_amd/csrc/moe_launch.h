@@ -26,6 +26,7 @@ struct MoeParams {
     __bf16* y;
     int T, H, I, E, KTOP;
     int bm;                   // rows per tile for this call: 64, 128, or 0 for the library's choice (moe_choose, by the routing stage)
+    int few;                  // the products run on the kernel for few rows per expert, with bm = 64
     int max_tiles;            // upper bound on the number of row tiles: ceil(T*KTOP / (bm or 128)) + E
     int dn_narrow_ok;         // the grid of the down product is sized for 128-row column tiles (the kernel decides whether to use them)
     // workspace carve-up (all device pointers into the caller's workspace)
