@@ -86,6 +86,29 @@ def load_library(build_if_missing: bool = True):
     return _lib
 
 
+_native = None
+
+
+def _load_native():
+    """The extension module that makes the plain calls (csrc/native_calls.cpp), with the library's addresses; False where it
+    has not been built: the calls then take the longer way through this file, to the same kernels."""
+    global _native
+    import importlib
+
+    import torch  # noqa: F401  (its libraries are what the module refers to)
+    lib = load_library()
+    try:
+        module = importlib.import_module(__package__ + "._native")
+    except ModuleNotFoundError:
+        module = False
+    if module:
+        module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.attn_fwd, lib.attn_fwd_strided, lib.attn_fwd_workspace_bytes, lib.attn_fwd_workspace,
+            lib.gemm_bf16_workspace_bytes, lib.gemm_bf16_tile, lib.gemm_bf16_workspace)))
+    _native = module
+    return module
+
+
 def strerror(code: int) -> str:
     return load_library().attn_strerror(int(code)).decode()
 
@@ -154,6 +177,13 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     with torch if not given.  The kernel is enqueued on `stream` (default: torch's current
     stream); no sync.
     """
+    if o is None and lse is None and stream is None:
+        native = _load_native() if _native is None else _native
+        done = native.attn(q, k, v, causal, scale) if native else None         # None: not a plain call
+        if done is not None:
+            if type(done) is int:
+                raise AttnError(done, strerror(done))
+            return done
     import torch
 
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
@@ -216,6 +246,13 @@ def gemm_bf16(a, b, c=None, b_is_nk=False, stream=None, tile=0):
     """C = A B for bf16 CUDA tensors a [M,K] and b [K,N] (or [N,K] if b_is_nk); rows contiguous,
     row pitch free.  c (bf16 [M,N]) is allocated with torch if not given.  Enqueued on `stream`
     (default: torch's current stream); no sync.  tile: 0 (by size) or a shape code of gemm.h: 64, 128, 1284, 256, 2564, those with 16 appended, or 19216 (gemm_bf16_tile)."""
+    if c is None and stream is None and tile == 0:
+        native = _load_native() if _native is None else _native
+        done = native.gemm(a, b, b_is_nk) if native else None
+        if done is not None:
+            if type(done) is int:
+                raise AttnError(done, strerror(done))
+            return done
     import torch
 
     if not (a.is_cuda and b.is_cuda):

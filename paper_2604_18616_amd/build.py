@@ -10,6 +10,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 OBJ_DIR = os.path.join(_HERE, "_build")
 LIB_PATH = os.path.join(_HERE, "libattn_mi355x.so")
+NATIVE_SRC = "native_calls.cpp"                      # the Python binding's plain calls, against torch's C++ interface
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 SOURCES = ["attn_api.cpp", "attn_fwd_kernel.hip", "attn_split_kernel.hip", "gemm_api.cpp", "gemm_bf16_kernel.hip",
            "gemm_unaligned_kernel.hip", "moe_api.cpp", "moe_fp8_kernel.hip"]
 HIPCC_FLAGS = [
@@ -53,6 +55,19 @@ def stale_sources() -> list:
     return sorted(f for d in dirs for f in os.listdir(d) if os.path.getmtime(os.path.join(d, f)) > t)
 
 
+def _native_command(out):
+    """One command compiles and links the extension module; torch's libraries are the ones the process has loaded."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    includes = [*include_paths(), sysconfig.get_paths()["include"]]
+    return [hipcc_path(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wno-unused-command-line-argument", "-DUSE_ROCM",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *("-isystem" + p for p in includes),
+            "-o", out, os.path.join(CSRC, NATIVE_SRC), "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+
+
 def build_library(verbose: bool = False, incremental: bool = False) -> str:
     """Compile every source under csrc/ (one hipcc per file, in parallel) and link libattn_mi355x.so.
     Always recompiles unless `incremental`, which keeps the objects that are newer than their source
@@ -66,6 +81,11 @@ def build_library(verbose: bool = False, incremental: bool = False) -> str:
         if incremental and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(src), hdr):
             continue
         jobs.append([hipcc, *HIPCC_FLAGS, "-c", "-o", obj, src])
+    native_tmp = NATIVE_PATH + ".tmp.%d" % os.getpid()
+    src = os.path.join(CSRC, NATIVE_SRC)
+    native = not (incremental and os.path.exists(NATIVE_PATH) and os.path.getmtime(NATIVE_PATH) > os.path.getmtime(src))
+    if native:
+        jobs.append(_native_command(native_tmp))
     with ThreadPoolExecutor(max(1, min(len(jobs), os.cpu_count() or 1))) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     tmp = LIB_PATH + ".tmp.%d" % os.getpid()
@@ -76,6 +96,8 @@ def build_library(verbose: bool = False, incremental: bool = False) -> str:
             os.remove(tmp)
         raise
     os.replace(tmp, LIB_PATH)
+    if native:
+        os.replace(native_tmp, NATIVE_PATH)
     return LIB_PATH
 
 

@@ -1,0 +1,128 @@
+"""The extension module's plain calls against the same calls through the Python code: same results on the same memory formats,
+and everything that is not plain is left to the Python code, whose errors stay what they were."""
+import pytest
+import torch
+
+from paper_2604_18616_amd import binding
+
+
+def modes():
+    """The binding with the module and without it."""
+    for native in (None, False):
+        binding._native = native
+        yield native
+    binding._native = None
+
+
+@pytest.fixture(autouse=True)
+def restore():
+    yield
+    binding._native = None
+
+
+def test_module_is_built_and_leaves_cpu_tensors_to_python():
+    module = binding._load_native()
+    assert module, "the extension module is missing: build() makes it"
+    t, m = torch.zeros(1, 2, 3, 64, dtype=torch.bfloat16), torch.zeros(8, 8, dtype=torch.bfloat16)
+    assert module.attn(t, t, t, False, None) is None
+    assert module.attn(t, t, None, False, None) is None and module.attn(t, t) is None
+    assert module.gemm(m, m, True) is None and module.gemm(m, "b", True) is None and module.gemm() is None
+    for _ in modes():
+        with pytest.raises(ValueError, match="no CPU path"):
+            binding.attn_fwd(t, t, t)
+        with pytest.raises(ValueError, match="no CPU path"):
+            binding.gemm_bf16(m, m)
+
+
+def rnd(*shape):
+    return torch.randn(shape, device="cuda", dtype=torch.bfloat16)
+
+
+LAYOUTS = {
+    "contiguous": lambda B, H, S, D: rnd(B, H, S, D),
+    "bshd": lambda B, H, S, D: rnd(B, S, H, D).transpose(1, 2),
+    "cache": lambda B, H, S, D: rnd(B, H, S + 37, D)[:, :, :S],
+    "wide rows": lambda B, H, S, D: rnd(B, H, S, D + 8)[..., :D],
+    "one for all": lambda B, H, S, D: rnd(1, H, S, D).expand(B, H, S, D),
+    "parameter": lambda B, H, S, D: torch.nn.Parameter(rnd(B, H, S, D)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", list(LAYOUTS))
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,causal,scale", [(2, 8, 2, 1, 700, 128, False, None), (1, 4, 4, 5, 100, 64, True, 0.3),
+                                                           (2, 4, 1, 200, 600, 128, True, None), (1, 2, 2, 129, 64, 64, False, 1.0)])
+def test_attention_both_ways(layout, B, Hq, Hkv, Sq, Sk, D, causal, scale):
+    torch.manual_seed(Sk)
+    make = LAYOUTS[layout]
+    q, k, v = make(B, Hq, Sq, D), make(B, Hkv, Sk, D), make(B, Hkv, Sk, D)
+    print("native attn", layout, B, Hq, Hkv, Sq, Sk, D, causal, flush=True)
+    got = [binding.attn_fwd(q, k, v, causal=causal, scale=scale) for _ in modes()]
+    (o, lse), (o2, lse2) = got
+    assert o.stride() == o2.stride() and lse.stride() == lse2.stride() and o.dtype == o2.dtype and lse.dtype == lse2.dtype
+    assert not o.requires_grad and torch.equal(o, o2) and torch.equal(lse, lse2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(1, 1024, 4096), (64, 64, 64), (33, 70, 129), (300, 512, 96)])
+@pytest.mark.parametrize("nk", [False, True])
+@pytest.mark.parametrize("pad,offset", [(0, 0), (8, 0), (3, 1)])
+def test_products_both_ways(M, N, K, nk, pad, offset):
+    torch.manual_seed(M)
+
+    def matrix(r, c):
+        return rnd(r * (c + pad) + offset)[offset:].view(r, c + pad)[:, :c]
+    a, b = matrix(M, K), matrix(N, K) if nk else matrix(K, N)
+    print("native gemm", M, N, K, nk, pad, offset, flush=True)
+    got = [binding.gemm_bf16(a, b, b_is_nk=nk) for _ in modes()]
+    assert got[0].stride() == got[1].stride() and torch.equal(*got)
+
+
+@pytest.mark.gpu
+def test_refusals_stay_the_same():
+    t, m = rnd(1, 2, 100, 64), rnd(64, 64)
+
+    class Sub(torch.Tensor):
+        pass
+    calls = [
+        lambda: binding.attn_fwd(t.half(), t, t), lambda: binding.attn_fwd(t[..., ::2], t, t), lambda: binding.attn_fwd(t[0], t, t),
+        lambda: binding.attn_fwd(t, t, t[:, :, :50]), lambda: binding.attn_fwd(t, t[:, :1], t), lambda: binding.attn_fwd(t[:, :0], t, t),
+        lambda: binding.attn_fwd(t[..., :32], t[..., :32], t[..., :32]), lambda: binding.attn_fwd(t, t, t, scale=-1.0),
+        lambda: binding.attn_fwd(t, t, t, scale=float("nan")), lambda: binding.attn_fwd(t.cpu(), t, t), lambda: binding.attn_fwd(t, t, t, scale="x"),
+        lambda: binding.attn_fwd(rnd(1, 2, 100, 66)[..., 1:65], t, t),
+        lambda: binding.attn_fwd(rnd(1, 3, 100, 64), t, t), lambda: binding.gemm_bf16(m, m[:32]), lambda: binding.gemm_bf16(m.float(), m),
+        lambda: binding.gemm_bf16(m.t(), m), lambda: binding.gemm_bf16(m[:0], m), lambda: binding.gemm_bf16(m, m.cpu()), lambda: binding.gemm_bf16(m[None], m),
+    ]
+    for i, call in enumerate(calls):
+        said = []
+        for _ in modes():
+            with pytest.raises(Exception) as e:
+                call()
+            said.append((type(e.value), str(e.value)))
+        assert said[0] == said[1], (i, said)
+    # taken, if not as plain calls: a subclass, an integer scale, a number for a truth value
+    o, _ = binding.attn_fwd(t, t, t, scale=0.125)
+    for q, causal, scale in ((t.as_subclass(Sub), False, 0.125), (t, 0, 0.125)):
+        assert torch.equal(binding.attn_fwd(q, t, t, causal=causal, scale=scale)[0].as_subclass(torch.Tensor), o)
+    assert torch.equal(binding.attn_fwd(t, t, t, scale=1)[0], binding.attn_fwd(t, t, t, scale=1.0)[0])
+
+
+@pytest.mark.gpu
+def test_other_streams_and_capture():
+    q, k, v = rnd(2, 8, 1, 128), rnd(2, 2, 900, 128), rnd(2, 2, 900, 128)
+    a, b = rnd(4, 4096), rnd(512, 4096)
+    want = binding.attn_fwd(q, k, v)[0], binding.gemm_bf16(a, b, b_is_nk=True)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        got = binding.attn_fwd(q, k, v)[0], binding.gemm_bf16(a, b, b_is_nk=True)
+    side.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        o, c = binding.attn_fwd(q, k, v)[0], binding.gemm_bf16(a, b, b_is_nk=True)
+    for _ in range(3):
+        o.zero_(), c.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, want[0]) and torch.equal(c, want[1])
