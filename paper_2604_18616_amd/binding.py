@@ -168,6 +168,17 @@ def _scratch(need, device):
         return None
 
 
+_torch_scratch = _scratch
+
+
+def _plain_calls():
+    """The extension module; False without it, and where a program has put its own source of memory for the parts in place of
+    _scratch, which only the code below asks."""
+    if _scratch is not _torch_scratch:
+        return False
+    return _load_native() if _native is None else _native
+
+
 def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     """O, LSE = attention forward of bf16 CUDA tensors q [B,Hq,Sq,D], k/v [B,Hkv,Sk,D].
 
@@ -178,7 +189,7 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     stream); no sync.
     """
     if o is None and lse is None and stream is None:
-        native = _load_native() if _native is None else _native
+        native = _plain_calls()
         done = native.attn(q, k, v, causal, scale) if native else None         # None: not a plain call
         if done is not None:
             if type(done) is int:
@@ -247,7 +258,7 @@ def gemm_bf16(a, b, c=None, b_is_nk=False, stream=None, tile=0):
     row pitch free.  c (bf16 [M,N]) is allocated with torch if not given.  Enqueued on `stream`
     (default: torch's current stream); no sync.  tile: 0 (by size) or a shape code of gemm.h: 64, 128, 1284, 256, 2564, those with 16 appended, or 19216 (gemm_bf16_tile)."""
     if c is None and stream is None and tile == 0:
-        native = _load_native() if _native is None else _native
+        native = _plain_calls()
         done = native.gemm(a, b, b_is_nk) if native else None
         if done is not None:
             if type(done) is int:

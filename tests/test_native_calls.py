@@ -126,3 +126,29 @@ def test_other_streams_and_capture():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(o, want[0]) and torch.equal(c, want[1])
+
+
+@pytest.mark.gpu
+def test_no_memory_for_the_parts_means_no_cut():
+    q, k, v = rnd(1, 32, 64, 128), rnd(1, 8, 20000, 128), rnd(1, 8, 20000, 128)
+    a, b = rnd(100, 14336), rnd(4096, 14336)
+    lib = binding.load_library()
+    assert lib.attn_fwd_workspace_bytes(1, 32, 8, 64, 20000, 128) > 4 << 20 and lib.gemm_bf16_workspace_bytes(100, 4096, 14336) > 4 << 20
+    o, lse = torch.empty_like(q), torch.empty(1, 32, 64, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    assert binding.attn_fwd_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), 1, 32, 8, 64, 20000, 128, False, 128 ** -0.5, stream) == 0
+    c = binding.gemm_bf16(a, b, b_is_nk=True, tile=lib.gemm_bf16_auto_tile(100, 4096))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    spare = [torch.empty_like(x) for x in (o, c)]            # small blocks for the results below
+    del spare
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + 1) / torch.cuda.get_device_properties(0).total_memory)
+        full = []
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            while True:                                      # what is left of large blocks
+                full.append(torch.empty(2 << 20, dtype=torch.uint8, device="cuda"))
+        uncut = binding.attn_fwd(q, k, v)[0], binding.gemm_bf16(a, b, b_is_nk=True)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(uncut[0], o) and torch.equal(uncut[1], c)
