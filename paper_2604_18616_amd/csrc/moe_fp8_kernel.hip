@@ -332,24 +332,27 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
 
     // ---- down product: where each row goes.  A row that is the only local slot of its token is that token's
     // whole sum and is written to y directly.  The lookup (row -> token -> its slots -> weight: three dependent
-    // loads) is done here, before the loop, by the wavefronts that do not copy (a copying wavefront would have
-    // to wait for it before it may issue its first copies): thread 256 + m takes row m and hands token and
-    // weight over through LDS once the stage buffers are free, after the loop ----
+    // loads) is done by the wavefronts that do not copy, thread 256 + m for row m, while stage 0 is on its way; token and
+    // weight are handed over through LDS once the stage buffers are free, after the loop ----
     int look_tok = -1;
     float look_w = 0.0f;
-    if constexpr (!UP) {
+    auto look_up = [&]() __attribute__((always_inline)) {
         const int m = tid - 256;
-        if (m >= 0 && m < rows) {
+        if (m < rows) {
             const int t = p.sorted_tok[row0 + m];
+            const int* const pos = p.pos + t * p.KTOP;
+            int at[16];                                            // (all slots' loads at once: one by one they are a chain of KTOP round trips)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) at[k] = k < p.KTOP ? pos[k] : -1;
             int nlocal = 0, slot = 0;
-            for (int k = 0; k < p.KTOP; ++k) {
-                const int rk = p.pos[t * p.KTOP + k];
-                nlocal += rk >= 0 ? 1 : 0;
-                if (rk == row0 + m) slot = k;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                nlocal += at[k] >= 0 ? 1 : 0;
+                if (at[k] == row0 + m) slot = k;
             }
             if (nlocal == 1) { look_tok = t; look_w = p.wts[t * p.KTOP + slot]; }
         }
-    }
+    };
 
     // ---- main loop.  It is instantiated for either role, so that no wait for a row scale, a load into registers, comes to
     // stand where a copying wavefront passes: it would wait for its copies. ----
@@ -375,6 +378,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
         } else {
             put_scales(0, now[0]);
             now = __builtin_shufflevector(now, now, 1, 2, 3, 3);
+            if constexpr (!UP) look_up();
         }
 
         // One stage: a stream of NF products per block of 16 rows.  A product's four results are multiplied by their scale and
