@@ -78,11 +78,14 @@ extern "C" int moe_ffn_fp8_ex(const void* x, const int* ids, const float* wts,
     p.T = T; p.H = H; p.I = I; p.E = E; p.KTOP = KTOP;
     // how an expert's rows are cut into tiles (moe_layout.h); each tile runs the 64- to 256-row code that fits the rows
     // it really has.  `bm_override` is for tests
-    // Few rows per expert on average, also if every slot were local: the kernel whose workgroups share a CU by twos.  Its tiles
-    // have 32 rows; an expert with more reads its weights again.  Gate/up + down, us, against the 64-row code: 170 tokens
-    // x 6 on 64 experts of 2048 x 1408 (16 slots per expert, 7 to 25 rows) 104 -> 94, 300 x 6 (28 slots, 16 to 38 rows) 107 -> 124;
-    // up to 12 slots per expert leave room for one that is favoured almost threefold.
-    p.few = bm_override == 0 && (long long)T * KTOP <= 12LL * E ? 1 : 0;
+    // Few rows per expert, also if every slot were local: the kernel whose workgroups share a CU by twos.  Its tiles have 32
+    // rows; an expert with more reads its weights again, which costs more than the kernel gives, and the host does not know the
+    // routing.  With up to 32 tokens no expert has more (a token's choices differ); with up to 64 a favoured one is read twice at
+    // most, and with 4 slots per expert few are.  Whole call, us, against the 64-row code: 16 tokens x 2 on 8 experts of
+    // 4096 x 14336 260 -> 254, 42 x 6 on 64 of 2048 x 1408 117 -> 110, 64 x 8 on 128 of 2048 x 768 128 -> 118, or 108 -> 109 with
+    // three experts above 32 rows.  Beyond: 48 x 2 on the 8 experts 258 -> 254, but 263 -> 401 with two above 32 rows.
+    const long long few_slots = T <= 32 ? 12 : T <= 64 ? 4 : 0;
+    p.few = bm_override == 0 && (long long)T * KTOP <= few_slots * E ? 1 : 0;
     p.bm = p.few ? 64 : bm_override;
     const int bound = p.bm ? p.bm : 128;                 // (neither of the library's two cuts makes more tiles than that)
     p.max_tiles = (int)(((size_t)T * KTOP + bound - 1) / bound + E);

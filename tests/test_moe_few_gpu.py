@@ -1,5 +1,5 @@
-"""moe_ffn_fp8 with few rows per expert (at most 12 slots each on average): two workgroups per CU with tiles of 32 rows, and
-experts that are favoured beyond one such tile."""
+"""moe_ffn_fp8 with few rows per expert: two workgroups per CU with tiles of 32 rows.  Taken with up to 32 tokens and 12 slots per
+expert, or up to 64 tokens and 4 slots per expert; on either side of both lines, and with an expert favoured beyond one tile."""
 import pytest
 
 from tests.test_moe_tiles_gpu import check_rows_per_expert
@@ -7,14 +7,24 @@ from tests.test_moe_tiles_gpu import check_rows_per_expert
 pytestmark = pytest.mark.gpu
 
 
-# one to three tiles of 32 rows inside a row tile, a second row tile; 128 wide column tiles of the down product and fewer
-# (halved, three stages), and more
-@pytest.mark.parametrize("counts", [(1,), (12, 3), (31, 33, 2), (64, 65, 96, 97), (130, 1)])
-@pytest.mark.parametrize("H,Isz,empty", [(128, 128, 16), (640, 384, 40), (2944, 256, 60)])
-def test_favoured_experts(counts, H, Isz, empty):
-    filler = (0,) * max(0, -(-sum(counts) // 12) - len(counts)) + (1,) * empty
+# one and two tiles of 32 rows, 32 and 64 tokens; 128 wide column tiles of the down product and fewer (halved, three
+# stages), and more
+@pytest.mark.parametrize("counts", [(1,), (12, 3), (31, 1), (32,), (33, 2), (31, 33), (64,)])
+@pytest.mark.parametrize("H,Isz,ones", [(128, 128, 0), (640, 384, 16), (2944, 256, 60)])
+def test_favoured_experts(counts, H, Isz, ones):
+    ones = min(ones, (32 if sum(counts) <= 32 and ones < 60 else 64) - sum(counts))
+    tokens = sum(counts) + ones
+    per = 12 if tokens <= 32 else 4
+    filler = (1,) * ones + (0,) * max(0, -(-tokens // per) - len(counts) - ones)
     check_rows_per_expert(counts, H, Isz, filler=filler)
 
 
-def test_two_local_slots():
-    check_rows_per_expert((20, 40), 256, 256, twice=True, filler=(1,) * 30)
+# one token or one expert to the other side of each line: the general kernel, whose tiles a favoured expert does not outgrow
+@pytest.mark.parametrize("counts,filler", [((33,), (0,) * 7), ((64,), (0,) * 14), ((64,), (1,) + (0,) * 20), ((20, 12), ())])
+def test_beyond_the_lines(counts, filler):
+    check_rows_per_expert(counts, 640, 384, filler=filler)
+
+
+@pytest.mark.parametrize("counts,filler", [((10, 12), (1,) * 8), ((33,), (1,) * 10 + (0,) * 12)])
+def test_two_local_slots(counts, filler):
+    check_rows_per_expert(counts, 256, 256, twice=True, filler=filler)
