@@ -570,7 +570,7 @@ __device__ __forceinline__ bool moe_tile_of(const MoeParams& p, int NT, int live
 // Kernel for few rows per expert (MoeParams::few): tiles of 32 rows in two stages of weights and three of rows (three of either
 // where the column tiles are halved), so that two workgroups share a CU and one starts and ends while the other streams.  Reading the weights bounds it:
 // gate/up / down, us, against the 64-row code with one workgroup per CU: 40 tokens of (2048 x 1408, 64 experts) 68.7 / 32.2
-// -> 63.1 / 28.7, 60 of (2048 x 768, 128 experts) 71.3 / 40.0 -> 66.4 / 31.8, 64 of (7168 x 2048, 32 experts) 129 / 66 -> 126 / 62.
+// -> 63.1 / 28.7, 60 of (2048 x 768, 128 experts) 71.3 / 40.0 -> 66.4 / 31.8.
 template <bool UP>
 __global__ __launch_bounds__(512, 4) void moe_gemm_few(MoeParams p) {
     constexpr int BM = 32;
