@@ -223,8 +223,10 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     const int w_row0 = 16 * MB * wm;                // first routed row of the wavefront
     // Whether the weights of a stage are overwritten as soon as every wavefront has them in registers, behind a second
     // barrier in the stage: they are then copied NB stages ahead instead of NB - 1.  With two stages always; with three
-    // only where there is a workgroup per CU at most, whose stages wait for the latency of memory
-    constexpr bool kCanBeEarly = BM != 64;
+    // only where there is a workgroup per CU at most, whose stages wait for the latency of memory, and not with 64 or 128
+    // rows (128: whole call, us, with and without, 12 experts of 2944 x 1152, 67 rows each 52.1 / 50.3, 4 of 4096 x 1408, 100 rows
+    // 56.0 / 54.3, 200 rows in two tiles 59.4 / 60.6)
+    constexpr bool kCanBeEarly = NB == 2 || BM == 160 || BM == 32;
     const bool early = NB == 2 || (kCanBeEarly && few);
 
     const int KB = UP ? p.H : p.I;                  // bytes (= elements) per row of both operands
@@ -240,7 +242,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     const bool copier = wave < 4;
     const int c4 = wave & 3;
     unsigned a_off[NCA], b_off[NCB];              // 32 bits: an activation matrix, and an expert's weights, stay under 4 GiB
-    {
+    auto copy_offsets = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int n = 0; n < NCA; ++n) {
             const int i = c4 + 4 * n;
@@ -258,7 +260,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
             const int rows_on = UP ? (n & 1) * p.I + 32 * (n >> 1) : (nt * BN + 32 * n < p.H ? 32 * n : 0);   // rows past H: others again
             b_off[n] = row + (unsigned)rows_on * (unsigned)KB + 16u * (unsigned)kt_dma_chunk(c4, lane);
         }
-    }
+    };
     const char* const a_base = UP ? (const char*)p.xq : (const char*)p.aq;
     const char* const b_base = UP ? (const char*)(p.w13 + ((size_t)e * 2 * (size_t)p.I + (size_t)nt * 128) * (size_t)p.H)
                                   : (const char*)(p.w2 + ((size_t)e * (size_t)p.H + (size_t)nt * BN) * (size_t)p.I);
@@ -280,26 +282,25 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     // row and weight block and left in LDS, [U % 2][weight block][row], one stage ahead.  Thread 256 + m does it for row m; it
     // loads the row scales of four stages at once: a row's scales lie 4 nK bytes from the next row's, so every load
     // instruction touches a cache line per row however little it takes of it.  (Copied to LDS a dword per row and stage
-    // they were a third of all the lines the CU asked for.) ----
+    // they were a third of all the lines the CU asked for.)  The weight block scales of all stages go to a table in LDS, which
+    // the barrier of stage 0 makes visible; stage 0 takes its own two from memory. ----
     const LdsFloat slot = BM > 160 ? (LdsFloat)(smem + kStages) : scales;
     static_assert(BM > 160 ? kStages + 2 * 2 * BM * 4 <= kMoeLdsBytes : 2 * 2 * BM * 4 <= kMoeScaleBytes, "no room for the scales");
     typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;
     const float* s_src = nullptr;
-    auto put_scales = [&](int U, float s) __attribute__((always_inline)) {
+    unsigned slot_at = 0;                           // LDS address of this thread's row in slot
+    auto put_scales = [&](int U, float s, float sb0, float sb1) __attribute__((always_inline)) {
         if (tid - 256 < BM) {
-            slot[(U & 1) * (2 * BM) + tid - 256] = s * sb_tab[U];
-            slot[(U & 1) * (2 * BM) + BM + tid - 256] = s * sb_tab[kMoeMaxKB + U];
+            unsigned at = slot_at + (U & 1) * (8 * BM);
+            asm("" : "+v"(at));                     // (one address, and one store of both)
+            *LDS_PTR(float, (size_t)at) = s * sb0;
+            *LDS_PTR(float, (size_t)(at + 4 * BM)) = s * sb1;
         }
     };
-
-    // ---- weight block scales of all stages into LDS ----
-    if (tid >= 256 && tid - 256 < 2 * nK) {         // (not the wavefronts that copy: theirs would wait for it in front of their first copies)
-        const int which = (tid - 256) / nK, b = tid - 256 - which * nK;
-        const float* src;
-        if (UP) src = p.s13 + ((size_t)e * 2 * (p.I >> 7) + (which ? (p.I >> 7) : 0) + nt) * nK;   // gate rows, up rows of block nt
-        else src = p.s2 + ((size_t)e * (p.H >> 7) + min(BN == 256 ? 2 * nt + which : nt, (p.H >> 7) - 1)) * nK;
-        sb_tab[which * kMoeMaxKB + b] = src[b];
-    }
+    auto sb_src = [&](int which) __attribute__((always_inline)) -> const float* {         // weight block 0 or 1 of the tile
+        if (UP) return p.s13 + ((size_t)e * 2 * (p.I >> 7) + (which ? (p.I >> 7) : 0) + nt) * nK;   // gate rows, up rows of block nt
+        return p.s2 + ((size_t)e * (p.H >> 7) + min(BN == 256 ? 2 * nt + which : nt, (p.H >> 7) - 1)) * nK;
+    };
 
     // ---- per-lane LDS read addresses (stage 0): the K = 128 operand is 32 bytes of a 16-row block per lane, chunks quad and
     // quad + 4 (any order of k will do that both operands share).  A 16-byte read is served in four parts, the first of
@@ -333,22 +334,27 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
     // ---- down product: where each row goes.  A row that is the only local slot of its token is that token's
     // whole sum and is written to y directly.  The lookup (row -> token -> its slots -> weight: three dependent
     // loads) is done by the wavefronts that do not copy, thread 256 + m for row m, while stage 0 is on its way; token and
-    // weight are handed over through LDS once the stage buffers are free, after the loop ----
+    // weight are handed over through LDS once the stage buffers are free, after the loop.  Slots are loaded by eights, as one
+    // by one they are a chain of KTOP round trips, and looped over, as 16 of them unrolled are 1.4 KB of code, whose
+    // fetching took 0.4 us of a down product of 5.  (What an eight reads past the token's slots is the next token's, or the
+    // workspace's next part, and not looked at.) ----
     int look_tok = -1;
     float look_w = 0.0f;
-    auto look_up = [&]() __attribute__((always_inline)) {
+    auto look_up = [&](int t) __attribute__((always_inline)) {
         const int m = tid - 256;
         if (m < rows) {
-            const int t = p.sorted_tok[row0 + m];
+            typedef __attribute__((ext_vector_type(4), aligned(4))) int i32x4_any;
             const int* const pos = p.pos + t * p.KTOP;
-            int at[16];                                            // (all slots' loads at once: one by one they are a chain of KTOP round trips)
-#pragma unroll
-            for (int k = 0; k < 16; ++k) at[k] = k < p.KTOP ? pos[k] : -1;
             int nlocal = 0, slot = 0;
+            for (int k0 = 0; k0 < p.KTOP; k0 += 8) {
+                const i32x4_any lo = *(const i32x4_any*)(pos + k0), hi = *(const i32x4_any*)(pos + k0 + 4);
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                nlocal += at[k] >= 0 ? 1 : 0;
-                if (at[k] == row0 + m) slot = k;
+                for (int k = 0; k < 8; ++k) {
+                    if (k0 + k >= p.KTOP) break;
+                    const int at = k < 4 ? lo[k & 3] : hi[k & 3];
+                    nlocal += at >= 0 ? 1 : 0;
+                    if (at == row0 + m) slot = k0 + k;
+                }
             }
             if (nlocal == 1) { look_tok = t; look_w = p.wts[t * p.KTOP + slot]; }
         }
@@ -360,26 +366,34 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
         constexpr bool COPIER = decltype(role)::value;
         f32x4 now, later;                                          // row scales of the next stages (the first one's in element 0), and of the four after them
         if constexpr (COPIER) {                                    // one to three stages in flight
+            copy_offsets();
             __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), known to the compiler: no wait for an earlier load inside the loop
             dma_rows(0, 0);
             dma_weights(0, 0);
-        } else {
-            const int r = min(tid - 256, rows - 1);
-            s_src = (UP ? p.xs : p.as) + (size_t)(UP ? p.sorted_tok[row0 + r] : row0 + r) * (size_t)nK;
-            now = *(const f32x4_any*)s_src;
-            later = *(const f32x4_any*)(s_src + (nK > 4 ? 4 : 0));
-        }
-        __builtin_amdgcn_s_waitcnt(0xC07F);                        // (own weight block scales written)
-        barrier();                                                 // all of them visible
-        if constexpr (COPIER) {
-            // (not before the barrier: the row scales of stage 0 would come back behind these copies)
             if (1 < nK) { if (NA > 2) dma_rows(1, 1); dma_weights(1, 1); }
             if (NB > 2 && early && 2 < nK) dma_weights(2, 2);
         } else {
-            put_scales(0, now[0]);
+            // Two round trips to memory, what depends on no other load and then what depends on the row's token: this chain, and
+            // not the copies, is what stage 0 waits for.  (Four round trips, with the offsets of copies they do not issue and the
+            // table ahead of the row scales, and a barrier in front of the copies of stage 1, took 0.3 us more.)
+            slot_at = (unsigned)(size_t)slot + 4 * (tid - 256);
+            const int r = min(tid - 256, rows - 1), i = min(tid - 256, 2 * nK - 1), which = i >= nK ? 1 : 0;
+            const int t = p.sorted_tok[row0 + r];
+            const float sb = sb_src(which)[i - which * nK], sb0 = *sb_src(0), sb1 = *sb_src(1);
+            s_src = (UP ? p.xs : p.as) + (size_t)(UP ? t : row0 + r) * (size_t)nK;
+            now = *(const f32x4_any*)s_src;
+            later = *(const f32x4_any*)(s_src + (nK > 4 ? 4 : 0));
+            if (tid - 256 < 2 * nK) sb_tab[which * kMoeMaxKB + i - which * nK] = sb;             // (2 nK <= 256)
+            if constexpr (!UP) look_up(t);
+            put_scales(0, now[0], sb0, sb1);
             now = __builtin_shufflevector(now, now, 1, 2, 3, 3);
-            if constexpr (!UP) look_up();
         }
+
+        // Behind which product of a stage the next stage's scales are stored: as operand reads come back in order, a store among
+        // them holds up the products behind it, which a stage of few products cannot hide (BM = 64, gate/up of 8 experts of
+        // 1024 x 512: 9.7 us behind the second product, 9.1 in front of the last); larger ones have the time, and the barrier
+        // would wait for a late store (BM = 128, 12 of 2944 x 1152: 26.4 / 27.3)
+        constexpr int kPutAt = MB <= 2 && MB * NF >= 4 ? MB * NF - 2 : 1;
 
         // One stage: a stream of NF products per block of 16 rows.  A product's four results are multiplied by their scale and
         // added up two products later, in the shadow of the next one; operands are read one block ahead; the order is pinned.
@@ -397,6 +411,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
             i32x8 fb[NF], fa[2];
             float f0[2], f1[2];
             f32x4 part[4];
+            float sb0 = 0.0f, sb1 = 0.0f;                          // weight block scales of stage U + 1 (after the last stage, ones that nobody reads)
             auto read_block = [&](auto mb) __attribute__((always_inline)) {
                 constexpr int set = decltype(mb)::value & 1;
                 fa[set] = frag(a_addr[0], a_addr[1], mb.value * 2048);
@@ -428,7 +443,7 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
                             if constexpr (COPIER) if (U + NB < nK) dma_weights(U + NB, sb);
                         }
                     }
-                    if constexpr (!COPIER && i == 1) {
+                    if constexpr (!COPIER && i == kPutAt) {
                         // (a load comes back behind the copies that its CU issued before it, those of the next stages: four
                         // stages ahead of its first use it holds nothing up, one stage ahead everything.  What the last group
                         // has read past the row is not used: the row after it, or the workspace's next part)
@@ -437,12 +452,13 @@ __device__ __forceinline__ void moe_gemm_tile(const MoeParams& p, int e, int row
                             asm volatile("" : "+v"(now) :: "memory");      // the load below goes where `later` was
                             if (U + 5 < nK) later = *(const f32x4_any*)(s_src + U + 5);
                         }
-                        if (U + 1 < nK) put_scales(U + 1, now[0]);
+                        put_scales(U + 1, now[0], sb0, sb1);
                         now = __builtin_shufflevector(now, now, 1, 2, 3, 3);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 });
             };
+            if constexpr (!COPIER) { const int next = min(U + 1, nK - 1); sb0 = sb_tab[next]; sb1 = sb_tab[kMoeMaxKB + next]; }
             fb[0] = frag(b_addr[0], b_addr[1], 0);
             read_block(IntC<0>{});
             static_for<1, NF>([&](auto in) __attribute__((always_inline)) { fb[in.value] = frag(b_addr[0], b_addr[1], in.value * 2048); });

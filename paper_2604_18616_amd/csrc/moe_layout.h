@@ -22,7 +22,7 @@ MOE_HD int moe_tiles(int cnt, int bm) {
 }
 // First row of tile j of the n = moe_tiles(cnt, bm) of an expert; j = n gives its number of rows.
 MOE_HD int moe_tile_begin(int cnt, int n, int j, int bm) {
-    const int at = bm != 0 ? j * bm : (int)((long long)j * ((cnt + 31) / 32) / n) * 32;
+    const int at = bm != 0 ? j * bm : (int)((unsigned)j * ((unsigned)(cnt + 31) / 32) / (unsigned)n) * 32;
     return j >= n || at > cnt ? cnt : at;
 }
 

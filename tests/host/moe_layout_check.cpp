@@ -12,7 +12,7 @@ static int failures = 0;
 static void check_cuts() {
     const int bms[] = {0, 64, 128};
     for (int bm : bms)
-        for (int cnt = 0; cnt <= 20000; ++cnt) {
+        for (int cnt = 0; cnt <= 1 << 20; cnt += cnt < 20000 ? 1 : 4093) {
             const int n = moe_tiles(cnt, bm), most = bm ? bm + 32 : 256;
             CHECK((n == 0) == (cnt == 0), "bm %d, %d rows: %d tiles", bm, cnt, n);
             CHECK(bm != 0 || n <= moe_tiles(cnt, 128), "%d rows: %d tiles, more than of 128 rows", cnt, n);
