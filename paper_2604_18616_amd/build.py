@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -69,9 +70,9 @@ def _native_command(out):
 
 
 def build_library(verbose: bool = False, incremental: bool = False) -> str:
-    """Compile every source under csrc/ (one hipcc per file, in parallel) and link libattn_mi355x.so.
-    Always recompiles unless `incremental`, which keeps the objects that are newer than their source
-    and than every header."""
+    """Compile every source of the library under csrc/ (one hipcc per file, in parallel), link libattn_mi355x.so, then
+    build the extension module, which C programs do without.  Always recompiles unless `incremental`, which keeps the
+    objects that are newer than their source and than every header."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     hipcc, hdr = hipcc_path(), _newest_header()
     objs, jobs = [], []
@@ -81,11 +82,6 @@ def build_library(verbose: bool = False, incremental: bool = False) -> str:
         if incremental and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(src), hdr):
             continue
         jobs.append([hipcc, *HIPCC_FLAGS, "-c", "-o", obj, src])
-    native_tmp = NATIVE_PATH + ".tmp.%d" % os.getpid()
-    src = os.path.join(CSRC, NATIVE_SRC)
-    native = not (incremental and os.path.exists(NATIVE_PATH) and os.path.getmtime(NATIVE_PATH) > os.path.getmtime(src))
-    if native:
-        jobs.append(_native_command(native_tmp))
     with ThreadPoolExecutor(max(1, min(len(jobs), os.cpu_count() or 1))) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     tmp = LIB_PATH + ".tmp.%d" % os.getpid()
@@ -96,9 +92,27 @@ def build_library(verbose: bool = False, incremental: bool = False) -> str:
             os.remove(tmp)
         raise
     os.replace(tmp, LIB_PATH)
-    if native:
-        os.replace(native_tmp, NATIVE_PATH)
+    try:
+        build_native(verbose, incremental)
+    except (ImportError, RuntimeError) as why:           # (without torch, or without its headers: a C program needs neither)
+        warnings.warn("the extension module was not built, Python calls take longer: %s" % why)
     return LIB_PATH
+
+
+def build_native(verbose: bool = False, incremental: bool = False) -> None:
+    """Compile and link the extension module, which is optional: without it the binding's calls take the longer way."""
+    src = os.path.join(CSRC, NATIVE_SRC)
+    if incremental and os.path.exists(NATIVE_PATH) and os.path.getmtime(NATIVE_PATH) > os.path.getmtime(src):
+        return
+    if os.path.exists(NATIVE_PATH):
+        os.remove(NATIVE_PATH)                           # (made for an older library)
+    tmp = NATIVE_PATH + ".tmp.%d" % os.getpid()
+    try:
+        _run(_native_command(tmp), verbose)
+        os.replace(tmp, NATIVE_PATH)
+    finally:
+        if os.path.exists(tmp):
+            os.remove(tmp)
 
 
 if __name__ == "__main__":
