@@ -10,7 +10,7 @@ from __future__ import annotations
 import ctypes
 import os
 
-from .build import LIB_PATH, build_library, stale_sources
+from .build import LIB_PATH, NATIVE_PATH, build_library, stale_sources
 
 _lib = None
 
@@ -90,16 +90,25 @@ _native = None
 
 
 def _load_native():
-    """The extension module that makes the plain calls (csrc/native_calls.cpp), with the library's addresses; False where it
-    has not been built: the calls then take the longer way through this file, to the same kernels."""
+    """The extension module that makes the plain calls (csrc/native_calls.cpp), with the library's addresses; False, with a
+    warning, where it has not been built or not for this torch: the calls then take the longer way through this file, to the
+    same kernels."""
     global _native
-    import importlib
+    import importlib.util
+    import warnings
 
-    import torch  # noqa: F401  (its libraries are what the module refers to)
+    import torch
     lib = load_library()
     try:
-        module = importlib.import_module(__package__ + "._native")
-    except ModuleNotFoundError:
+        if not os.path.exists(NATIVE_PATH):
+            raise ImportError("it has not been built")
+        spec = importlib.util.spec_from_file_location(__package__ + "._native", NATIVE_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        if module.torch_version != torch.__version__:
+            raise ImportError("it was built for torch %s" % module.torch_version)
+    except ImportError as why:
+        warnings.warn("calls take longer without the extension module (python -m paper_2604_18616_amd.build builds it): %s" % why)
         module = False
     if module:
         module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 import warnings
 from concurrent.futures import ThreadPoolExecutor
 
@@ -12,7 +13,7 @@ CSRC = os.path.join(_HERE, "csrc")
 OBJ_DIR = os.path.join(_HERE, "_build")
 LIB_PATH = os.path.join(_HERE, "libattn_mi355x.so")
 NATIVE_SRC = "native_calls.cpp"                      # the Python binding's plain calls, against torch's C++ interface
-NATIVE_PATH = os.path.join(_HERE, "_native.so")
+NATIVE_PATH = os.path.join(_HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))     # (for this Python only)
 SOURCES = ["attn_api.cpp", "attn_fwd_kernel.hip", "attn_split_kernel.hip", "gemm_api.cpp", "gemm_bf16_kernel.hip",
            "gemm_unaligned_kernel.hip", "moe_api.cpp", "moe_fp8_kernel.hip"]
 HIPCC_FLAGS = [
@@ -53,18 +54,16 @@ def stale_sources() -> list:
         return []
     t = os.path.getmtime(LIB_PATH)
     dirs = (CSRC, os.path.join(os.path.dirname(_HERE), "include"))
-    return sorted(f for d in dirs for f in os.listdir(d) if os.path.getmtime(os.path.join(d, f)) > t)
+    return sorted(f for d in dirs for f in os.listdir(d) if f != NATIVE_SRC and os.path.getmtime(os.path.join(d, f)) > t)
 
 
 def _native_command(out):
     """One command compiles and links the extension module; torch's libraries are the ones the process has loaded."""
-    import sysconfig
-
     import torch
     from torch.utils.cpp_extension import include_paths
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     includes = [*include_paths(), sysconfig.get_paths()["include"]]
-    return [hipcc_path(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wno-unused-command-line-argument", "-DUSE_ROCM",
+    return [hipcc_path(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wno-unused-command-line-argument", "-DUSE_ROCM", '-DNATIVE_TORCH="%s"' % torch.__version__,
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *("-isystem" + p for p in includes),
             "-o", out, os.path.join(CSRC, NATIVE_SRC), "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
 
@@ -101,15 +100,22 @@ def build_library(verbose: bool = False, incremental: bool = False) -> str:
 
 def build_native(verbose: bool = False, incremental: bool = False) -> None:
     """Compile and link the extension module, which is optional: without it the binding's calls take the longer way."""
-    src = os.path.join(CSRC, NATIVE_SRC)
-    if incremental and os.path.exists(NATIVE_PATH) and os.path.getmtime(NATIVE_PATH) > os.path.getmtime(src):
-        return
-    if os.path.exists(NATIVE_PATH):
-        os.remove(NATIVE_PATH)                           # (made for an older library)
+    src, record = os.path.join(CSRC, NATIVE_SRC), os.path.join(OBJ_DIR, NATIVE_SRC + ".command")
     tmp = NATIVE_PATH + ".tmp.%d" % os.getpid()
     try:
-        _run(_native_command(tmp), verbose)
+        command = "\n".join(_native_command(NATIVE_PATH))           # (torch's version and Python's folders among its words)
+        if incremental and os.path.exists(NATIVE_PATH) and os.path.getmtime(NATIVE_PATH) > os.path.getmtime(src) and os.path.exists(record):
+            with open(record) as f:
+                if f.read() == command:
+                    return
+        _run([tmp if word == NATIVE_PATH else word for word in command.split("\n")], verbose)
         os.replace(tmp, NATIVE_PATH)
+        with open(record, "w") as f:
+            f.write(command)
+    except (ImportError, RuntimeError):
+        if os.path.exists(NATIVE_PATH):
+            os.remove(NATIVE_PATH)                       # (made for an older library, or another torch)
+        raise
     finally:
         if os.path.exists(tmp):
             os.remove(tmp)

@@ -156,4 +156,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__native() {
+    PyObject* const m = PyModule_Create(&module);
+    // the torch it was compiled for, which the binding compares with the one in use
+    if (m && PyModule_AddStringConstant(m, "torch_version", NATIVE_TORCH) != 0) { Py_DECREF(m); return nullptr; }
+    return m;
+}

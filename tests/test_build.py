@@ -26,7 +26,7 @@ def fake(tmp_path, monkeypatch):
     return tmp_path, commands
 
 
-def test_library_and_module_are_built(fake):
+def test_library_and_module_are_built(fake, monkeypatch):
     folder, commands = fake
     assert build.build_library() == str(folder / "lib.so")
     assert sorted(os.listdir(folder)) == ["lib.so", "module.so", "obj"]
@@ -36,6 +36,11 @@ def test_library_and_module_are_built(fake):
     assert len(commands) == 1                            # the link
     build.build_library()
     assert len(commands) == 1 + len(build.SOURCES) + 2
+    import torch
+    del commands[:]
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + ".1")
+    build.build_library(incremental=True)
+    assert len(commands) == 2                            # the link, and the module for the other torch
 
 
 @pytest.mark.parametrize("why", [ImportError("no torch"), RuntimeError("hipcc failed")])

@@ -34,6 +34,23 @@ def test_module_is_built_and_leaves_cpu_tensors_to_python():
             binding.gemm_bf16(m, m)
 
 
+@pytest.mark.parametrize("fault", ["missing", "no library", "other torch"])
+def test_a_module_that_does_not_fit_is_passed_by(tmp_path, monkeypatch, fault):
+    if fault == "other torch":
+        monkeypatch.setattr(torch, "__version__", "0.0.0")
+    else:
+        monkeypatch.setattr(binding, "NATIVE_PATH", str(tmp_path / "_native.so"))
+        if fault == "no library":
+            (tmp_path / "_native.so").write_bytes(b"not one")
+    t = torch.zeros(1, 2, 3, 64, dtype=torch.bfloat16)
+    binding._native = None
+    with pytest.warns(UserWarning, match="extension module"):
+        assert binding._plain_calls() is False
+    with pytest.raises(ValueError, match="no CPU path"):     # by the Python code, and no second warning
+        binding.attn_fwd(t, t, t)
+    assert binding._native is False
+
+
 def rnd(*shape):
     return torch.randn(shape, device="cuda", dtype=torch.bfloat16)
 
