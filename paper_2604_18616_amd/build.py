@@ -104,7 +104,7 @@ def build_native(verbose: bool = False, incremental: bool = False) -> None:
     tmp = NATIVE_PATH + ".tmp.%d" % os.getpid()
     try:
         command = "\n".join(_native_command(NATIVE_PATH))           # (torch's version and Python's folders among its words)
-        if incremental and os.path.exists(NATIVE_PATH) and os.path.getmtime(NATIVE_PATH) > os.path.getmtime(src) and os.path.exists(record):
+        if incremental and os.path.exists(NATIVE_PATH) and os.path.exists(record) and os.path.getmtime(NATIVE_PATH) > max(os.path.getmtime(src), _newest_header()):
             with open(record) as f:
                 if f.read() == command:
                     return

@@ -15,27 +15,21 @@
 
 #include <cmath>
 
+#include "../../include/attn_workspace.h"
+#include "../../include/gemm_workspace.h"
+
 namespace {
 
 using At = at::Tensor;
-typedef int (*AttnFwd)(const void*, const void*, const void*, void*, float*, int, int, int, int, int, int, int, float, void*);
-typedef int (*AttnStrided)(const void*, const void*, const void*, void*, float*, int, int, int, int, int, int, const long long*, const long long*,
-                           const long long*, const long long*, int, float, void*);
-typedef size_t (*AttnBytes)(int, int, int, int, int, int);
-typedef int (*AttnWorkspace)(const void*, const void*, const void*, void*, float*, int, int, int, int, int, int, const long long*, const long long*,
-                             const long long*, const long long*, int, float, void*, size_t, int, void*);
-typedef size_t (*GemmBytes)(int, int, int);
-typedef int (*GemmTile)(const void*, const void*, void*, int, int, int, long long, long long, long long, int, int, void*);
-typedef int (*GemmWorkspace)(const void*, const void*, void*, int, int, int, long long, long long, long long, int, int, int, void*, size_t, void*);
-
+// The library's entry points, with the headers' own types.
 struct Entries {
-    AttnFwd attn_fwd;
-    AttnStrided attn_fwd_strided;
-    AttnBytes attn_fwd_workspace_bytes;
-    AttnWorkspace attn_fwd_workspace;
-    GemmBytes gemm_bf16_workspace_bytes;
-    GemmTile gemm_bf16_tile;
-    GemmWorkspace gemm_bf16_workspace;
+    decltype(&::attn_fwd) attn_fwd;
+    decltype(&::attn_fwd_strided) attn_fwd_strided;
+    decltype(&::attn_fwd_workspace_bytes) attn_fwd_workspace_bytes;
+    decltype(&::attn_fwd_workspace) attn_fwd_workspace;
+    decltype(&::gemm_bf16_workspace_bytes) gemm_bf16_workspace_bytes;
+    decltype(&::gemm_bf16_tile) gemm_bf16_tile;
+    decltype(&::gemm_bf16_workspace) gemm_bf16_workspace;
 } entry = {};
 
 // A torch.Tensor or Parameter proper whose memory is its values: bf16 on a GPU, no subclass, no tensor of a transform.
@@ -143,7 +137,10 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
         p[i] = PyLong_AsVoidPtr(args[i]);
         if (!p[i]) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an address is null"); return nullptr; }
     }
-    entry = {(AttnFwd)p[0], (AttnStrided)p[1], (AttnBytes)p[2], (AttnWorkspace)p[3], (GemmBytes)p[4], (GemmTile)p[5], (GemmWorkspace)p[6]};
+    int at = 0;
+    auto next = [&](auto& f) { f = reinterpret_cast<std::remove_reference_t<decltype(f)>>(p[at++]); };
+    next(entry.attn_fwd), next(entry.attn_fwd_strided), next(entry.attn_fwd_workspace_bytes), next(entry.attn_fwd_workspace);
+    next(entry.gemm_bf16_workspace_bytes), next(entry.gemm_bf16_tile), next(entry.gemm_bf16_workspace);
     Py_RETURN_NONE;
 }
 

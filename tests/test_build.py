@@ -36,7 +36,18 @@ def test_library_and_module_are_built(fake, monkeypatch):
     assert len(commands) == 1                            # the link
     build.build_library()
     assert len(commands) == 1 + len(build.SOURCES) + 2
+    del commands[:]
+    newer = os.path.getmtime(folder / "module.so") + 10
+    monkeypatch.setattr(build, "_newest_header", lambda: newer)
+    build.build_library(incremental=True)
+    assert len(commands) == len(build.SOURCES) + 2       # a header is newer
+    monkeypatch.undo()
+
+
+def test_the_module_is_made_again_for_another_torch(fake, monkeypatch):
     import torch
+    folder, commands = fake
+    build.build_library()
     del commands[:]
     monkeypatch.setattr(torch, "__version__", torch.__version__ + ".1")
     build.build_library(incremental=True)
