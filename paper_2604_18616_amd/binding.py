@@ -180,12 +180,14 @@ def _scratch(need, device):
 _torch_scratch = _scratch
 
 
-def _plain_calls():
-    """The extension module; False without it, and where a program has put its own source of memory for the parts in place of
-    _scratch, which only the code below asks."""
+def _plain_calls(t):
+    """The extension module for a call whose first tensor is t; False without it, and where a program has put its own source
+    of memory for the parts in place of _scratch, which only the code below asks.  Tensors on the CPU are refused without loading anything."""
     if _scratch is not _torch_scratch:
         return False
-    return _load_native() if _native is None else _native
+    if _native is None:
+        return _load_native() if getattr(t, "is_cuda", False) else False
+    return _native
 
 
 def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
@@ -198,7 +200,7 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     stream); no sync.
     """
     if o is None and lse is None and stream is None:
-        native = _plain_calls()
+        native = _plain_calls(q)
         done = native.attn(q, k, v, causal, scale) if native else None         # None: not a plain call
         if done is not None:
             if type(done) is int:
@@ -267,7 +269,7 @@ def gemm_bf16(a, b, c=None, b_is_nk=False, stream=None, tile=0):
     row pitch free.  c (bf16 [M,N]) is allocated with torch if not given.  Enqueued on `stream`
     (default: torch's current stream); no sync.  tile: 0 (by size) or a shape code of gemm.h: 64, 128, 1284, 256, 2564, those with 16 appended, or 19216 (gemm_bf16_tile)."""
     if c is None and stream is None and tile == 0:
-        native = _plain_calls()
+        native = _plain_calls(a)
         done = native.gemm(a, b, b_is_nk) if native else None
         if done is not None:
             if type(done) is int:

@@ -45,10 +45,24 @@ def test_a_module_that_does_not_fit_is_passed_by(tmp_path, monkeypatch, fault):
     t = torch.zeros(1, 2, 3, 64, dtype=torch.bfloat16)
     binding._native = None
     with pytest.warns(UserWarning, match="extension module"):
-        assert binding._plain_calls() is False
+        assert binding._load_native() is False
     with pytest.raises(ValueError, match="no CPU path"):     # by the Python code, and no second warning
         binding.attn_fwd(t, t, t)
     assert binding._native is False
+
+
+def test_cpu_tensors_are_refused_without_the_library(tmp_path, monkeypatch):
+    def build(*_):
+        raise AssertionError("a library for a call that cannot be made")
+    monkeypatch.setattr(binding, "LIB_PATH", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(binding, "build_library", build)
+    monkeypatch.setattr(binding, "_lib", None)
+    binding._native = None
+    t, m = torch.zeros(1, 2, 3, 64, dtype=torch.bfloat16), torch.zeros(8, 8, dtype=torch.bfloat16)
+    with pytest.raises(ValueError, match="no CPU path"):
+        binding.attn_fwd(t, t, t)
+    with pytest.raises(ValueError, match="no CPU path"):
+        binding.gemm_bf16(m, m)
 
 
 def rnd(*shape):
