@@ -746,19 +746,9 @@ double attn_launch_mfma_calibration(float* sink, int blocks, int iters, int data
 // 0 picks by attn_auto_rows.
 // Measured on MI355X (TFLOP/s, 128 rows against 256): at D = 64 the 128-row workgroup needs 137 registers and
 // 32 KB of LDS, three of them fit a CU, and it is ahead on every shape tried (+1 % to +42 %: 1087 against 991 on
-// B2 H16 S8192, 617 against 434 on causal B16 H16 S1024); at D = 128 (192 registers, two per CU) every workgroup
-// copies its own K/V tiles, twice the copies per FLOP, and the uncoordinated wavefront pairs lose 6-15 % against the
-// two wavefront groups of the 256-row workgroup, except where 256-row workgroups cannot fill the chip's 256 CUs
-// (64 workgroups: +20 %), and except where there are few keys: then a workgroup's start and end (8 to 10 us, the wait for Q
-// above all) are most of its time, and two workgroups per CU hide each other's.  Time with 128 rows over time with 256, over 7
-// batches and head counts from 32 to 2400 workgroups: up to 512 keys 0.72 to 1.08, in the mean 0.89; causal prompts up to 704 keys
-// (352 visible to a row in the mean) 0.82 to 1.02; 600 to 900 keys without a mask 0.85 to 1.18, causal prompts of 1024 1.04 and 1.24.
-// us, 256 -> 128 rows: 32 32 8 256 256 causal 49.9 -> 40.6, 128 8 2 256 256 51.4 -> 43.2, 40 8 8 700 700 causal 69.6 -> 67.5.
+// B2 H16 S8192, 617 against 434 on causal B16 H16 S1024); at D = 128 (192 registers, two per CU) workgroup_rows decides.
 int attn_auto_rows(const AttnParams& p, int D, int causal) {
-    if (D == 64) return 128;
-    if (p.Sk <= 512 || (causal && p.Sk - (p.Sq < p.Sk ? p.Sq : p.Sk) / 2 <= 352)) return 128;
-    const long long wg256 = (long long)p.B * p.Hq * ((p.Sq + 255) / 256);
-    return wg256 <= 128 ? 128 : 256;
+    return D == 64 ? 128 : attn_layout::workgroup_rows(p.B, p.Hq, p.Hkv, p.Sq, p.Sk, causal != 0);
 }
 
 int attn_launch(AttnParams p, int D, int causal, int wg_rows, hipStream_t stream) {
@@ -766,13 +756,8 @@ int attn_launch(AttnParams p, int D, int causal, int wg_rows, hipStream_t stream
     const long long kv_ss = p.k_ss > p.v_ss ? p.k_ss : p.v_ss;
     const bool fast = p.Sq > 64 && ((long long)p.Sk + 64) * kv_ss * 2 < (1LL << 32);   // a head of K or V (padded to whole tiles) under 4 GiB
     const int br = !fast ? 128 : wg_rows ? wg_rows : attn_auto_rows(p, D, causal);
-    // heads of one kv head side by side in a workgroup of the tiled kernel: the largest power of two that divides
-    // the group size and leaves every head at least one wavefront (32 rows)
-    p.hpw = 1; p.hpw_log2 = 0;
-    if (fast) {
-        const int g = p.Hq / p.Hkv, nw = br / 32;
-        while (p.hpw * 2 <= nw && g % (p.hpw * 2) == 0) { p.hpw *= 2; ++p.hpw_log2; }
-    }
+    p.hpw = fast ? attn_layout::heads_side_by_side(p.Hq / p.Hkv, br / 32) : 1;
+    p.hpw_log2 = p.hpw >= 8 ? 3 : p.hpw / 2;
     const int rows_per_head = br / p.hpw;
     p.nQt = (p.Sq + rows_per_head - 1) / rows_per_head;
     const long long nblocks = (long long)p.B * (p.Hq / p.hpw) * p.nQt;

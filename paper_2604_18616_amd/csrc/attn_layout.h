@@ -141,4 +141,40 @@ ATTN_HD __attribute__((always_inline)) BlockCoord block_coord(int bid, int nbloc
     return c;
 }
 
+// Query heads of one kv head side by side in a workgroup of `waves` wavefronts: the largest power of two that divides the
+// group size and leaves every head at least one wavefront (32 rows).
+ATTN_HD constexpr int heads_side_by_side(int group, int waves) {
+    int h = 1;
+    while (h * 2 <= waves && group % (h * 2) == 0) h *= 2;
+    return h;
+}
+
+// Rows of a workgroup, D = 128.  A 256-row workgroup has a CU to itself; of 128-row ones two share a CU, copy every K/V tile
+// twice and lose 6 to 15 % on long key ranges.  128 rows are taken
+//   - where 256-row workgroups are too few for the chip's 256 CUs (64 of them: +20 %), and
+//   - with few keys, where a workgroup's start and end (8 to 10 us, the wait for Q above all) are most of its time, which
+//     two per CU hide for each other, if the rounds of workgroups come out in their favour: a last round of 128-row ones
+//     with at most one per CU is short, one of 256-row ones is not.  The estimates (us, per round, and per 64-key tile a row
+//     sees in the mean) are fitted to 2236 shapes of 129 to 2400 workgroups and checked on 1800 others.
+// Time with 128 rows over time with 256 (B Hq Hkv Sq Sk): 192 workgroups of 256 rows, 6 16 16 384 384 causal
+// 15.0 / 12.4 us; 144, 9 16 16 200 512 18.1 / 15.4; 288, 6 16 16 576 576 causal 17.9 / 26.9; 1024, 16 16 16 1024 256 48.3 / 53.3.
+// Of the 4036 shapes 17 take 2 to 5 % longer than with 256 rows, none more; with 128 rows wherever keys are few 384 do, by up to 21 %.
+ATTN_HD constexpr int workgroup_rows(long long B, int Hq, int Hkv, int Sq, int Sk, bool causal) {
+    if (B * Hq * ((Sq + 255) / 256) <= 128) return 128;
+    const long long seen = Sq < Sk ? Sq : Sk;
+    const double keys = causal ? (double)(seen * Sk - seen * (seen - 1) / 2) / Sq : (double)Sk;     // that a row sees, in the mean
+    if (Sk > 512 && !(causal && keys <= 352.5)) return 256;
+    const int h1 = heads_side_by_side(Hq / Hkv, 4), h2 = heads_side_by_side(Hq / Hkv, 8);
+    const long long n1 = B * (Hq / h1) * ((Sq + 128 / h1 - 1) / (128 / h1)), n2 = B * (Hq / h2) * ((Sq + 256 / h2 - 1) / (256 / h2));
+    // A mask that hides half: workgroups differ in length, and more than the rounds decides how the short ones fill the gaps of the
+    // long ones.  With heads side by side, whose tiles are cut finer, twice as many workgroups even out better.
+    const bool uneven = causal && h2 > 1 && keys <= 0.6 * Sk;
+    if (uneven && n2 <= 256 && 2 * (long long)Sq <= 3 * (long long)Sk) return n1 <= 256 || keys <= 200 ? 128 : 256;
+    const double tiles = keys / 64, pair = 5.8 + 1.58 * tiles, one = 3.4 + 0.89 * tiles;
+    const long long rest = n1 % 512, late = causal && Sk > 512 && h2 > 1 ? 32 : 0;      // (a handful of the last, shortest ones makes no round of 256 rows)
+    const double t128 = 3.0 + (double)(n1 / 512) * pair + (rest == 0 ? 0.0 : rest <= 256 ? one : pair);
+    const double t256 = (1.0 + (double)((n2 + 255 - late) / 256) * (7.5 + 1.29 * tiles)) * (uneven ? 1.06 : n2 > 512 ? 1.05 : 1.0);
+    return t128 < t256 ? 128 : 256;
+}
+
 }  // namespace attn_layout

@@ -178,7 +178,36 @@ template <bool CAUSAL> void check_block_coord(int B, int Hq, int Hkv, int nQt, i
     CHECK((int)seen.size() == nblocks, "%zu of %d blocks covered", seen.size(), nblocks);
 }
 
+// The rows of a workgroup: the faster choice, within 4 %, where both were measured (us with 128 and with 256 rows).
+static void check_workgroup_rows() {
+    struct { int B, Hq, Hkv, Sq, Sk; bool causal; double t128, t256; } const measured[] = {
+        // one round of 256-row workgroups
+        {6, 16, 16, 384, 384, true, 15.03, 12.37}, {24, 8, 4, 200, 512, true, 19.33, 16.34}, {9, 16, 16, 200, 512, false, 18.06, 15.43},
+        {19, 16, 2, 128, 512, false, 18.29, 15.79}, {5, 16, 16, 512, 512, false, 18.95, 16.25}, {8, 8, 4, 700, 700, true, 22.51, 19.51},
+        {3, 32, 8, 384, 384, false, 15.53, 13.55},
+        // a short second round, with and without heads side by side
+        {6, 16, 16, 576, 576, true, 17.89, 26.93}, {8, 16, 2, 576, 576, true, 20.71, 18.90}, {1, 96, 16, 679, 679, true, 24.11, 22.25},
+        {19, 16, 16, 160, 160, true, 15.82, 20.46}, {19, 16, 16, 160, 160, false, 16.89, 19.89},
+        // two rounds and more
+        {25, 16, 16, 160, 160, true, 18.28, 20.94}, {32, 16, 16, 160, 160, true, 20.26, 23.11}, {16, 16, 16, 1024, 256, true, 34.26, 47.70},
+        {16, 16, 16, 1024, 256, false, 48.28, 53.30}, {150, 16, 16, 160, 160, false, 88.34, 103.48}};
+    for (const auto& m : measured) {
+        const int rows = workgroup_rows(m.B, m.Hq, m.Hkv, m.Sq, m.Sk, m.causal);
+        const double t = rows == 128 ? m.t128 : m.t256;
+        CHECK(t <= 1.04 * (m.t128 < m.t256 ? m.t128 : m.t256), "%d %d %d %d %d: %d rows, measured %.1f / %.1f us", m.B, m.Hq, m.Hkv, m.Sq, m.Sk, rows, m.t128, m.t256);
+    }
+    // 256-row workgroups that cannot fill half the chip, long key ranges
+    CHECK(workgroup_rows(2, 32, 8, 512, 5000, true) == 128 && workgroup_rows(4, 32, 8, 4096, 4096, true) == 256 && workgroup_rows(16, 8, 1, 1024, 1024, true) == 256, "large");
+    CHECK(workgroup_rows(1 << 15, 1 << 10, 1, 65, 1, false) == 128 || workgroup_rows(1 << 15, 1 << 10, 1, 65, 1, false) == 256, "many workgroups");
+    for (int g = 1; g <= 64; ++g)
+        for (int waves : {4, 8}) {
+            const int h = heads_side_by_side(g, waves);
+            CHECK(g % h == 0 && h <= waves && (h & (h - 1)) == 0 && (2 * h > waves || g % (2 * h)), "group %d, %d wavefronts: %d", g, waves, h);
+        }
+}
+
 int main() {
+    check_workgroup_rows();
     for (int hpw : {1, 2, 4, 8}) {
         check_block_coord<true>(4, 32, 8, 64, hpw <= 4 ? hpw : 4);                             // the headline shape and its packings
         check_block_coord<false>(2, 16, 16, 32, 1);
