@@ -63,7 +63,8 @@ int moe_ffn_fp8(const void *x, const int *ids, const float *wts,
  *       on the same arguments, workspace and row_tile.  moe_ffn_fp8 is 0..4.
  *   row_tile  rows of one expert per workgroup of the two products: 64, 128, or 0 = what moe_ffn_fp8 does, which is
  *       128, or tiles of up to 256 rows where their smaller number fills the GPU as well (one tile for up to 160 rows, more
- *       rows evenly into the fewest tiles): the faster one by an estimate from the routed rows of the whole call.
+ *       rows evenly into the fewest tiles): the faster one by an estimate from the routed rows of the whole call; or 32 for
+ *       few tokens (T <= 32 and at most 12 slots per expert, T * KTOP <= 12 E, or T <= 64 and at most 4).
  *       For 64 and 128 an expert's rows are cut into tiles of row_tile rows and a remainder (an expert with row_tile + 1 ..
  *       row_tile + 32 rows gets a single tile); every tile runs the code that fits its rows.
  * A stage range outside 0..4 or another row_tile: ATTN_ERR_UNSUPPORTED.
@@ -110,8 +111,8 @@ long long moe_ffn_fp8_workspace_offset(int T, int H, int I, int E, int KTOP, int
 
 /* Row tiles (workgroups per column tile) an expert with `rows` routed rows is cut into for row_tile = 64 or
  * 128 as in moe_ffn_fp8_ex: tiles of row_tile rows and a remainder, except that an expert with row_tile + 1 ..
- * row_tile + 32 rows gets a single tile.  For 0 the most it is cut into, the answer for 128: tiles of up to 256 rows,
- * which a call takes or not by all its routed rows, are never more; workspace part 2 holds the number of row tiles that a
+ * row_tile + 32 rows gets a single tile.  For 0 the answer for 128, the most an expert is cut into except in the calls of
+ * few tokens that take tiles of 32 rows; workspace part 2 holds the number of row tiles that a
  * call made.  -1 for a negative count or another row_tile.  Host-only helper. */
 int moe_ffn_fp8_row_tiles(int rows, int row_tile);
 

@@ -21,7 +21,7 @@ static bool sizes_ok(int T, int H, int I, int E, int KTOP) {
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 size_t moe_workspace_layout(int T, int H, int I, int E, int KTOP, size_t off[13]) {
-    const size_t slots = (size_t)T * KTOP, max_tiles = (slots + kMoeBM - 1) / kMoeBM + E;
+    const size_t slots = (size_t)T * KTOP, bm = moe_few(T, E, KTOP) ? 32 : kMoeBM, max_tiles = (slots + bm - 1) / bm + E;
     size_t cur = 0;
     auto take = [&](int idx, size_t bytes) { off[idx] = cur; cur = align256(cur + bytes); };
     take(0, sizeof(int) * (E + 1));          // offsets
@@ -78,15 +78,13 @@ extern "C" int moe_ffn_fp8_ex(const void* x, const int* ids, const float* wts,
     p.T = T; p.H = H; p.I = I; p.E = E; p.KTOP = KTOP;
     // how an expert's rows are cut into tiles (moe_layout.h); each tile runs the 64- to 256-row code that fits the rows
     // it really has.  `bm_override` is for tests
-    // Few rows per expert, also if every slot were local: the kernel whose workgroups share a CU by twos.  Its tiles have 32
-    // rows; an expert with more reads its weights again, which costs more than the kernel gives, and the host does not know the
-    // routing.  With up to 32 tokens no expert has more (a token's choices differ); with up to 64 a favoured one is read twice at
-    // most, and with 4 slots per expert few are.  Whole call, us, against the 64-row code: 16 tokens x 2 on 8 experts of
-    // 4096 x 14336 260 -> 254, 42 x 6 on 64 of 2048 x 1408 117 -> 110, 64 x 8 on 128 of 2048 x 768 128 -> 118, or 108 -> 109 with
-    // three experts above 32 rows.  Beyond: 48 x 2 on the 8 experts 258 -> 254, but 263 -> 401 with two above 32 rows.
-    const long long few_slots = T <= 32 ? 12 : T <= 64 ? 4 : 0;
-    p.few = bm_override == 0 && (long long)T * KTOP <= few_slots * E ? 1 : 0;
-    p.bm = p.few ? 64 : bm_override;
+    // Few rows per expert: tiles of 32 rows on the kernel whose workgroups share a CU by twos.  Whole call, us, against the 64-row
+    // code, even routing: 16 tokens x 2 on 8 experts of 4096 x 14336 260 -> 254, 42 x 6 on 64 of 2048 x 1408 116 -> 109, 64 x 8 on
+    // 128 of 2048 x 768 130 -> 120; uneven: the same 109 -> 100 and 119 -> 107, 64 x 1 on 16 of 6144 x 2048 with most tokens on
+    // one expert 57 -> 55.  Beyond the two lines experts of more than 32 rows are common: 48 x 2 on the 8 experts 258 -> 254, but
+    // 263 -> 401 with two of them (as a tile of 64 rows in two passes of one workgroup).
+    p.few = bm_override == 0 && moe_few(T, E, KTOP) ? 1 : 0;
+    p.bm = p.few ? 32 : bm_override;
     const int bound = p.bm ? p.bm : 128;                 // (neither of the library's two cuts makes more tiles than that)
     p.max_tiles = (int)(((size_t)T * KTOP + bound - 1) / bound + E);
     // narrow column tiles of the down product are for problems whose wide tiles would not fill the chip: the grid is

@@ -586,7 +586,9 @@ __device__ __forceinline__ bool moe_tile_of(const MoeParams& p, int NT, int live
 // Kernel for few rows per expert (MoeParams::few): tiles of 32 rows in two stages of weights and three of rows (three of either
 // where the column tiles are halved), so that two workgroups share a CU and one starts and ends while the other streams.  Reading the weights bounds it:
 // gate/up / down, us, against the 64-row code with one workgroup per CU: 40 tokens of (2048 x 1408, 64 experts) 68.7 / 32.2
-// -> 63.1 / 28.7, 60 of (2048 x 768, 128 experts) 71.3 / 40.0 -> 66.4 / 31.8.
+// -> 63.1 / 28.7, 60 of (2048 x 768, 128 experts) 71.3 / 40.0 -> 66.4 / 31.8.  An expert with more than 32 rows is several
+// tiles, neighbours in the order of workgroups, so that its weights come from HBM once.  (As one tile of two passes it was the last to
+// end: 64 tokens on 16 experts of 6144 x 2048, most of them on one, 96 us for the call against 55.)
 template <bool UP>
 __global__ __launch_bounds__(512, 4) void moe_gemm_few(MoeParams p) {
     constexpr int BM = 32;
@@ -595,20 +597,18 @@ __global__ __launch_bounds__(512, 4) void moe_gemm_few(MoeParams p) {
     static_assert(2 * (kMoeFewLdsBytes + 2 * 2 * BM * 4 + 2 * kMoeMaxKB * 4) <= 160 * 1024, "LDS budget");
     __shared__ float sb_tab[2 * kMoeMaxKB];
     const int ntl = p.ntiles[0], bm = p.ntiles[1];
-    const bool narrow = !UP && p.dn_narrow_ok && ntl * ((p.H + kMoeBN - 1) / kMoeBN) <= 128;       // as in moe_gemm
+    // half column tiles as in moe_gemm, although a CU holds two workgroups here.  Down product, us, at other limits: 64 tiles, 84 wide
+    // ones of (7168 x 2048) 10.5 -> 14.2, 112 of (4096 x 14336) 70 -> 97; 256, 140 of the former 14.7 -> 17.2, 224 20.2 -> 19.4
+    const bool narrow = !UP && p.dn_narrow_ok && ntl * ((p.H + kMoeBN - 1) / kMoeBN) <= 128;
     const int NT = UP ? (p.I >> 7) : narrow ? (p.H >> 7) : (p.H + kMoeBN - 1) / kMoeBN;
     MoeTile t;
     if (!moe_tile_of(p, NT, ntl * NT, bm, t)) return;
     const LdsChar tiles = LDS_PTR(char, smem);
     const LdsFloat sa = LDS_PTR(float, scales), sb = LDS_PTR(float, sb_tab);
-    for (int r = 0; r < t.rows; r += BM) {           // (a favoured expert's tile has up to 96 rows)
-        if (r > 0) __syncthreads();                  // the epilogue's reads of what the next copies overwrite
-        const int rows = min(BM, t.rows - r);
-        if constexpr (!UP) {
-            if (narrow) { moe_gemm_tile<false, BM, 128>(p, t.e, t.row0 + r, rows, t.nt, true, tiles, sa, sb); continue; }
-        }
-        moe_gemm_tile<UP, BM, 256>(p, t.e, t.row0 + r, rows, t.nt, true, tiles, sa, sb);
+    if constexpr (!UP) {
+        if (narrow) { moe_gemm_tile<false, BM, 128>(p, t.e, t.row0, t.rows, t.nt, true, tiles, sa, sb); return; }
     }
+    moe_gemm_tile<UP, BM, 256>(p, t.e, t.row0, t.rows, t.nt, true, tiles, sa, sb);
 }
 
 // Kernel: maps the workgroup to its (row tile, column tile) and runs the tile code that fits the tile's rows.

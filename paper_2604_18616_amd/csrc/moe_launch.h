@@ -7,7 +7,7 @@
 
 #include "moe_layout.h"
 
-constexpr int kMoeBM = 64;   // smallest row tile (routed token slots of one expert) of the grouped products: sizes the tile tables
+constexpr int kMoeBM = 64;   // smallest row tile (routed token slots of one expert) of the grouped products but for the few-rows kernel's: sizes the tile tables
 
 // What a workgroup of the grouped products needs to know about the expert its row tile belongs to, in one
 // 16-byte load: the tile's own first row and row count follow from these by arithmetic (moe_tile_begin), so the
@@ -25,8 +25,8 @@ struct MoeParams {
     const uint8_t* w13; const float* s13; const uint8_t* w2; const float* s2;
     __bf16* y;
     int T, H, I, E, KTOP;
-    int bm;                   // rows per tile for this call: 64, 128, or 0 for the library's choice (moe_choose, by the routing stage)
-    int few;                  // the products run on the kernel for few rows per expert, with bm = 64
+    int bm;                   // rows per tile for this call: 32 (few), 64, 128, or 0 for the library's choice (moe_choose, by the routing stage)
+    int few;                  // the products run on the kernel for few rows per expert (moe_few), with bm = 32
     int max_tiles;            // upper bound on the number of row tiles: ceil(T*KTOP / (bm or 128)) + E
     int dn_narrow_ok;         // the grid of the down product is sized for 128-row column tiles (the kernel decides whether to use them)
     // workspace carve-up (all device pointers into the caller's workspace)

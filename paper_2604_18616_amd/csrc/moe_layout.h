@@ -14,9 +14,18 @@ MOE_HD int moe_row_tiles(int cnt, int bm) {
     return (n == 1 && r <= 32) ? 1 : n + (r > 0 ? 1 : 0);
 }
 
+// Few rows per expert, also if every slot were local: the call runs on the kernel whose workgroups share a CU by twos, with bm = 32:
+// every tile has up to 32 rows.  The host chooses and does not know the routing: a favoured expert's weights are copied once for
+// every 32 of its rows, by neighbouring workgroups, the second time from L2.
+MOE_HD bool moe_few(int T, int E, int KTOP) {
+    const long long slots = T <= 32 ? 12 : T <= 64 ? 4 : 0;      // per expert
+    return (long long)T * KTOP <= slots * E;
+}
+
 // bm = 0: an expert with up to 160 rows gets one tile, more rows the fewest tiles of at most 256, cut evenly at multiples of
 // 32.  Never more tiles than bm = 128 makes.
 MOE_HD int moe_tiles(int cnt, int bm) {
+    if (bm == 32) return (cnt + 31) / 32;
     if (bm != 0) return moe_row_tiles(cnt, bm);
     return cnt <= 160 ? (cnt > 0 ? 1 : 0) : (cnt + 255) / 256;
 }

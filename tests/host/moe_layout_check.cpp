@@ -10,10 +10,10 @@ static int failures = 0;
 #define CHECK(cond, ...) do { if (!(cond) && ++failures < 20) { printf(__VA_ARGS__); printf("\n"); } } while (0)
 
 static void check_cuts() {
-    const int bms[] = {0, 64, 128};
+    const int bms[] = {0, 32, 64, 128};
     for (int bm : bms)
         for (int cnt = 0; cnt <= 1 << 20; cnt += cnt < 20000 ? 1 : 4093) {
-            const int n = moe_tiles(cnt, bm), most = bm ? bm + 32 : 256;
+            const int n = moe_tiles(cnt, bm), most = bm == 32 ? 32 : bm ? bm + 32 : 256;
             CHECK((n == 0) == (cnt == 0), "bm %d, %d rows: %d tiles", bm, cnt, n);
             CHECK(bm != 0 || n <= moe_tiles(cnt, 128), "%d rows: %d tiles, more than of 128 rows", cnt, n);
             for (int j = 0; j < n; ++j) {
@@ -24,6 +24,28 @@ static void check_cuts() {
             CHECK(n == 0 || moe_tile_begin(cnt, n, n, bm) == cnt, "bm %d, %d rows: ends at %d", bm, cnt, moe_tile_begin(cnt, n, n, bm));
         }
     CHECK((1 << 20) / 128 + 256 < 1 << 15, "two tile counts share an int");
+}
+
+// Calls of few tokens: however the slots fall on the experts, even all on one, the tiles fit the table for slots / 32 + E.
+static void check_few() {
+    CHECK(moe_few(32, 8, 3) && !moe_few(33, 8, 3) && !moe_few(32, 8, 4) && moe_few(64, 64, 4) && !moe_few(65, 64, 4) && !moe_few(64, 63, 4), "lines");
+    unsigned seed = 1;
+    for (int T = 1; T <= 64; ++T)
+        for (int k = 1; k <= 16; ++k)
+            for (int E = 1; E <= 256; E += E < 16 ? 1 : 24) {
+                if (!moe_few(T, E, k)) continue;
+                for (int form = 0; form < 4; ++form) {                 // all on one; 33 each as far as they go; 1 each; random
+                    int left = T * k, tiles = 0;
+                    for (int e = 0; e < E && left > 0; ++e) {
+                        seed = seed * 1664525u + 1013904223u;
+                        int n = form == 0 ? left : form == 1 ? 33 : form == 2 ? 1 : (int)((seed >> 16) % 70);
+                        if (n > left || (form != 2 && e == E - 1)) n = left;
+                        left -= n;
+                        tiles += moe_tiles(n, 32);
+                    }
+                    CHECK(tiles <= (T * k + 31) / 32 + E, "%d tokens x %d on %d experts: %d tiles", T, k, E, tiles);
+                }
+            }
 }
 
 static void check_choice() {
@@ -45,6 +67,7 @@ static void check_choice() {
 
 int main() {
     check_cuts();
+    check_few();
     check_choice();
     if (failures) { printf("%d moe layout check(s) FAILED\n", failures); return 1; }
     printf("moe layout checks passed\n");

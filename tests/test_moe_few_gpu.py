@@ -1,8 +1,16 @@
 """moe_ffn_fp8 with few rows per expert: two workgroups per CU with tiles of 32 rows.  Taken with up to 32 tokens and 12 slots per
 expert, or up to 64 tokens and 4 slots per expert; on either side of both lines, and with an expert favoured beyond one tile."""
+import numpy as np
 import pytest
 
+import oracle
+from paper_2604_18616_amd import inputs as I
+from tests.test_moe_parity_gpu import check_routing, check_stage1, check_y, run, sanity_net
 from tests.test_moe_tiles_gpu import check_rows_per_expert
+
+
+def tiles_32(counts):
+    return sum(-(-n // 32) for n in counts)
 
 pytestmark = pytest.mark.gpu
 
@@ -16,7 +24,7 @@ def test_favoured_experts(counts, H, Isz, ones):
     tokens = sum(counts) + ones
     per = 12 if tokens <= 32 else 4
     filler = (1,) * ones + (0,) * max(0, -(-tokens // per) - len(counts) - ones)
-    check_rows_per_expert(counts, H, Isz, filler=filler)
+    check_rows_per_expert(counts, H, Isz, filler=filler, tiles=tiles_32(counts + filler))
 
 
 # one token or one expert to the other side of each line: the general kernel, whose tiles a favoured expert does not outgrow
@@ -28,3 +36,20 @@ def test_beyond_the_lines(counts, filler):
 @pytest.mark.parametrize("counts,filler", [((10, 12), (1,) * 8), ((33,), (1,) * 10 + (0,) * 12)])
 def test_two_local_slots(counts, filler):
     check_rows_per_expert(counts, 256, 256, twice=True, filler=filler)
+
+
+# nothing says that a token's choices differ: all slots on one expert, or all but one
+@pytest.mark.parametrize("T,KTOP,E,others", [(64, 4, 64, 0), (32, 16, 43, 0), (64, 4, 64, 1), (1, 12, 1, 0)])
+def test_repeated_choices(T, KTOP, E, others):
+    w = I.MoeWorkload("t", T, 77 + T + others, H=384, I=640, E=E, KTOP=KTOP, EP=1)
+    d = I.make_moe(w)
+    ids = np.full((T, KTOP), E - 1, np.int32)
+    ids[:, :others] = 0
+    d["ids"] = ids
+    print("repeated choices", T, KTOP, E, others, flush=True)
+    g = run(d)
+    assert g["ntiles"] == tiles_32((T * others, T * (KTOP - others)))
+    check_routing(w, d, g)
+    check_stage1(w, d, g, [0, T - 1])
+    check_y(w, d, g, sorted({0, T // 2, T - 1}))
+    sanity_net(g["y"], oracle.moe_ref(**d), "repeated")
