@@ -521,14 +521,15 @@ static void launch_tiled(GemmParams p, int b_is_nk, hipStream_t stream) {
 // every CU has its fill of workgroups) x (how full the last round of workgroups leaves the chip) x (the share of
 // the tiles' area that lies inside the result).  The first factor is measured on large squares (TFLOP/s: 256 x 256
 // tiles on the 16x16x32 instruction 1420, 192 x 256 tiles on it 1300, 128 x 128 in two stages with two
-// workgroups per CU 1150, in four stages with one per CU 880, 64 x 64 with two per CU 700); the second is
-// tiles / (slots x rounds) with 256 CUs x workgroups per CU slots.  Checked against measurements on squares from
-// 1024 to 6144 and on rectangles from 1024 x 4096 to 1024 x 16384 and 3000 x 5000: it picks the fastest of the
-// five everywhere (a half-filled chip runs somewhat faster than the estimate, which never changed the order).
+// workgroups per CU 1150, in four stages with one per CU 1000, where 880 would choose alike, 64 x 64 with two per CU 700);
+// the second is tiles / (slots x rounds) with 256 CUs x workgroups per CU slots.  Checked against measurements on
+// squares from 1024 to 6144 and on rectangles from 1024 x 4096 to 1024 x 16384 and 3000 x 5000: it picks the fastest of
+// the five (a half-filled chip runs somewhat faster than the estimate), but for 1024 x 2048, 2048 x 1024 and 512 x 4096 with B
+// stored [K,N] and 2048 of k or more: 64 x 64 tiles, which take 4 to 9 % longer than 128 x 128 in four stages (K 4096: 28.5 / 26.2 us).
 int gemm_auto_tile(int M, int N) {
     struct Shape { int tile, edge_m, edge_n, slots; double peak; };
     static const Shape shapes[5] = {{25616, 256, 256, 256, 1420.0}, {19216, 192, 256, 256, 1300.0}, {128, 128, 128, 512, 1150.0},
-                                    {1284, 128, 128, 256, 880.0}, {64, 64, 64, 512, 700.0}};
+                                    {1284, 128, 128, 256, 1000.0}, {64, 64, 64, 512, 700.0}};
     int best = 25616;
     double best_rate = -1.0;
     for (const Shape& sh : shapes) {
@@ -544,12 +545,14 @@ int gemm_auto_tile(int M, int N) {
 // Whether to cut k over workgroups, and how: the least estimated time in microseconds, against the uncut product in
 // gemm_auto_tile's shape, which stays unless the cut promises an eighth less.  Measured (B stored [N,K], its memory cold):
 // a workgroup's 64-deep stage takes, with one workgroup per CU and with every slot taken, 0.28 / 0.42 us on 64 x 64
-// tiles, 0.50 / 0.57 on 128 x 128 tiles in four stages, 0.88 / 1.06 on them in two, 1.5 on 256 x 256 tiles; start and
+// tiles, 0.88 / 1.06 on 128 x 128 tiles in two stages, 1.5 on 256 x 256 tiles; on 128 x 128 tiles in four stages it takes 0.38 /
+// 0.49 and is charged the 0.50 / 0.57 of four wavefronts instead of eight, since with its own figures 296 products whose cut
+// changed took 1.04 times as long in the mean and up to 1.6 (1000 2152 15616: uncut, 90 -> 142 us); start and
 // end 3 us; the operands arrive at 5.1 TB/s at most (3.6 where two rows of 64 x 64 tiles read each weight); the sum of
 // the parts costs 2.5 us and its traffic at 6 TB/s.
 // Uncut against cut, M N K: 1 1024 14336: 63.9 -> 11.2 us; 16 4096 4096: 21.4 -> 10.5; 128 4096 14336: 71.4 -> 34.0;
 // 256 256 10240: 45.2 -> 10.7; 1024 1024 8192: 40.6 -> 29.2.  Where the uncut product has its fill of workgroups or is
-// bound by its operands the parts only cost: 16 14336 4096: 27.1 against 30.2 in two; 2048 2048 2048: 21.3 against 32.2.
+// bound by its operands the parts only cost: 16 14336 4096: 27.1 against 30.8 in two; 2048 2048 2048: 21.0 against 39.0.
 GemmPlan gemm_plan(int M, int N, int K, int tile, int splits) {
     GemmPlan best{tile ? tile : gemm_auto_tile(M, N), 1};
     if (splits) { best.splits = splits; return best; }
