@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 
 
 # one and two tiles of 32 rows, 32 and 64 tokens; 128 wide column tiles of the down product and fewer (halved, three
-# stages), and more
+# stages of weights), and more; one to nine 128-deep stages
 @pytest.mark.parametrize("counts", [(1,), (12, 3), (31, 1), (32,), (33, 2), (31, 33), (64,)])
-@pytest.mark.parametrize("H,Isz,ones", [(128, 128, 0), (640, 384, 16), (2944, 256, 60)])
+@pytest.mark.parametrize("H,Isz,ones", [(128, 128, 0), (640, 384, 16), (384, 1152, 16), (2944, 256, 60), (1152, 640, 60)])
 def test_favoured_experts(counts, H, Isz, ones):
     ones = min(ones, (32 if sum(counts) <= 32 and ones < 60 else 64) - sum(counts))
     tokens = sum(counts) + ones
