@@ -52,10 +52,11 @@ MOE_HD int moe_product_time(int rows, int tiles, int cols, int stages, bool down
 // The cut a call takes when the caller leaves it open: bm = 0, whose larger tiles copy a third less from L2 per product, or
 // bm = 128, whose larger number fills the chip where the large ones would leave CUs idle or start another round.
 // Gate/up + down, us, tiles of 128 rows against up to 256, same rows on every expert: 8 experts of 1024 x 512, 256 rows
-// 24 / 35, 2000 rows 60 / 49; 4 of 4096 x 1408, 200 rows 52 / 68, 700 rows 108 / 91; 12 of 2944 x 1152, 256 rows 66 / 77,
-// 300 rows 91 / 76; 8 of 4096 x 14336, 200 rows 451 / 401, 400 rows 807 / 615; 32 of 7168 x 2048, 256 rows 484 / 431.  Of 164
-// measured configurations (8 layers, 2 to 4000 rows per expert, even and random) the choice is the better of the two
-// within 3 % in all of one run and all but one of another (8 of 4096 x 14336, 256 rows, where they are level: 457 / 439).
+// 23 / 33, 2000 rows 57 / 51; 4 of 4096 x 1408, 200 rows 50 / 63, 700 rows 105 / 87; 12 of 2944 x 1152, 256 rows 64 / 74,
+// 300 rows 88 / 73; 8 of 4096 x 14336, 200 rows 454 / 400, 400 rows 832 / 616; 32 of 7168 x 2048, 256 rows 493 / 434.  With the
+// same rows on every expert, 36 configurations of 8 layers, the choice is the better one within 3 %.  It sees the mean of the rows
+// only: over 176 even and uneven routings of the layers it cost 0.6 % in the mean, most where a few experts have many times the
+// rows of the others (8688 tokens on 32 of 7168 x 2048: 696, against 611 with 128 rows).
 MOE_HD int moe_choose(int rows, int tiles128, int tiles256, int H, int I) {
     if (tiles128 == tiles256) return 0;
     const int small = moe_product_time(rows, tiles128, I / 128, H / 128, false) + moe_product_time(rows, tiles128, (H + 255) / 256, I / 128, true);

@@ -49,15 +49,24 @@ static void check_few() {
 }
 
 static void check_choice() {
-    // E experts with `rows` rows each; us of the two products with tiles of 128 rows and of up to 256
+    // E experts with `rows` rows each; us of the two products with tiles of 128 rows and of up to 256, as the kernels are now.
+    // Either cut will do where the times are within 3 %, what two runs may differ by
     struct { int H, I, E, rows; double t128, t256; } const measured[] = {
-        {1024, 512, 8, 175, 21.3, 28.9}, {1024, 512, 8, 256, 21.7, 34.2}, {1024, 512, 8, 512, 23.5, 35.4}, {1024, 512, 8, 1000, 31.2, 38.5},
-        {1024, 512, 8, 2000, 59.3, 50.9}, {4096, 1408, 4, 200, 48.9, 74.9}, {4096, 1408, 4, 500, 58.4, 84.0}, {4096, 1408, 4, 700, 106.4, 90.5},
-        {2944, 1152, 12, 200, 62.3, 68.9}, {2944, 1152, 12, 300, 85.7, 78.1}, {4096, 14336, 8, 256, 471.4, 520.4}, {4096, 14336, 8, 400, 841.1, 711.5},
-        {2048, 1408, 64, 200, 242.9, 207.2}, {2048, 768, 128, 256, 314.1, 277.3}, {5120, 1536, 16, 256, 156.5, 149.0}, {7168, 2048, 32, 256, 520.0, 479.8}};
+        {1024, 512, 8, 175, 22.8, 26.5}, {1024, 512, 8, 256, 22.8, 33.1}, {1024, 512, 8, 400, 23.8, 30.3}, {1024, 512, 8, 512, 24.0, 34.1},
+        {1024, 512, 8, 700, 27.3, 34.4}, {1024, 512, 8, 1000, 29.5, 36.8}, {1024, 512, 8, 1400, 49.7, 43.4}, {1024, 512, 8, 2000, 57.4, 50.8},
+        {4096, 1408, 4, 200, 49.7, 63.3}, {4096, 1408, 4, 300, 54.3, 55.2}, {4096, 1408, 4, 500, 59.6, 77.3}, {4096, 1408, 4, 700, 104.8, 87.2},
+        {4096, 1408, 4, 1000, 116.8, 99.1}, {2944, 1152, 12, 200, 63.5, 64.6}, {2944, 1152, 12, 256, 63.5, 73.7}, {2944, 1152, 12, 300, 87.6, 72.7},
+        {2944, 1152, 12, 400, 107.0, 91.3}, {2944, 1152, 12, 600, 135.6, 127.3}, {4096, 14336, 8, 200, 454.1, 399.7},
+        {4096, 14336, 8, 256, 443.8, 451.6}, {4096, 14336, 8, 400, 832.2, 615.5}, {4096, 14336, 8, 600, 1062.5, 931.9},
+        {2048, 1408, 64, 170, 232.7, 183.6}, {2048, 1408, 64, 200, 240.9, 198.1}, {2048, 1408, 64, 256, 245.6, 215.7},
+        {2048, 1408, 64, 400, 435.1, 330.3}, {2048, 768, 128, 200, 292.3, 239.6}, {2048, 768, 128, 256, 299.7, 265.8},
+        {2048, 768, 128, 400, 530.1, 398.1}, {5120, 1536, 16, 200, 165.1, 139.3}, {5120, 1536, 16, 256, 171.3, 154.6},
+        {5120, 1536, 16, 400, 258.8, 227.8}, {7168, 2048, 32, 180, 470.9, 367.9}, {7168, 2048, 32, 256, 493.4, 433.6},
+        {7168, 2048, 32, 300, 647.3, 558.7}, {7168, 2048, 32, 400, 877.5, 660.4}};
     for (const auto& m : measured) {
         const int bm = moe_choose(m.E * m.rows, m.E * moe_tiles(m.rows, 128), m.E * moe_tiles(m.rows, 0), m.H, m.I);
-        CHECK(bm == (m.t128 < m.t256 ? 128 : 0), "%d experts of %d x %d, %d rows: bm %d, measured %.1f / %.1f us", m.E, m.H, m.I, m.rows, bm, m.t128, m.t256);
+        CHECK((bm ? m.t128 : m.t256) <= 1.03 * (m.t128 < m.t256 ? m.t128 : m.t256), "%d experts of %d x %d, %d rows: bm %d, measured %.1f / %.1f us",
+              m.E, m.H, m.I, m.rows, bm, m.t128, m.t256);
     }
     // the largest sums that the estimate can meet stay inside an int and positive
     const int tiles = (1 << 20) / 128 + 256;
