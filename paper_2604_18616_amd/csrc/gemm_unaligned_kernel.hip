@@ -11,9 +11,10 @@
 // seen before is zeroed on its way to LDS in both operands (0 x inf would be NaN), and columns a neighbouring tile owns
 // are not stored.  That needs K >= 64 and, for B stored [K,N], N >= BN.
 //
-// What bounds it: the copies L2 -> registers, 36 to 40 bytes per ns and CU: M999 N2001 K1501 [K,N] on 64 x 64 tiles, two
-// workgroups per CU, reads 786 KB per CU in 20.5 us; on 256 tiles of 128 x 64 it is 590 KB and 18.6 us.  The fp32 FMA kernel
-// that served these sizes needed 252 us.  M2001 N2001 K2001 on 128 x 128 tiles: 35.6 us (450 TFLOP/s).
+// What bounds it: a workgroup has one wavefront per SIMD, which waits for its loads, writes LDS, meets the barrier and multiplies in
+// turn.  M999 N2001 K1501 [K,N] on 64 x 64 tiles, two workgroups per CU, reads 786 KB per CU in 20.5 us; on 256 tiles of 128 x 64 it
+// is 590 KB and 18.6 us, 32 bytes per ns and CU, where copies alone reach 60 to 118 from L2.  The fp32 FMA kernel that served these
+// sizes needed 252 us.  M2001 N2001 K2001 on 128 x 128 tiles: 35.6 us (450 TFLOP/s).
 #include <stdint.h>
 
 #include "gemm_layout.h"
