@@ -1,5 +1,5 @@
-"""attn_fwd where the number of keys decides between workgroups of 128 and 256 rows (D = 128): up to 512 keys, causal up to 352
-visible to a row in the mean."""
+"""attn_fwd with few keys, where workgroups have 128 or 256 rows by an estimate (D = 128; up to 512 keys, causal up to 352 visible
+to a row in the mean), and just beyond: both are taken here."""
 import pytest
 import torch
 
