@@ -21,15 +21,15 @@ static bool sizes_ok(int T, int H, int I, int E, int KTOP) {
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 size_t moe_workspace_layout(int T, int H, int I, int E, int KTOP, size_t off[13]) {
-    const size_t slots = (size_t)T * KTOP, bm = moe_few(T, E, KTOP) ? 32 : kMoeBM, max_tiles = (slots + bm - 1) / bm + E;
+    const size_t slots = (size_t)T * KTOP, max_tiles = (slots + kMoeBM - 1) / kMoeBM + E;
     size_t cur = 0;
     auto take = [&](int idx, size_t bytes) { off[idx] = cur; cur = align256(cur + bytes); };
     take(0, sizeof(int) * (E + 1));          // offsets
     take(1, sizeof(int) * E);                // cursor
     take(2, 2 * sizeof(int));                // ntiles
     take(3, 4 * sizeof(int) * max_tiles);    // tile_rec
-    take(4, sizeof(int));                    // (not in use)
-    take(5, sizeof(int));                    // (not in use)
+    take(4, sizeof(int));                    // with part 5 512 bytes behind the table, for the further records of a call with
+    take(5, sizeof(int));                    // tiles of 32 rows (moe_few: at most 16 of 16 bytes)
     take(6, sizeof(int) * slots);            // sorted_tok
     take(7, sizeof(int) * slots);            // pos
     take(8, (size_t)T * H);                  // xq

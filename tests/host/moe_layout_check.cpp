@@ -26,7 +26,8 @@ static void check_cuts() {
     CHECK((1 << 20) / 128 + 256 < 1 << 15, "two tile counts share an int");
 }
 
-// Calls of few tokens: however the slots fall on the experts, even all on one, the tiles fit the table for slots / 32 + E.
+// Calls of few tokens: however the slots fall on the experts, even all on one, there are at most slots / 32 + E tiles, whose
+// records fit the table for slots / 64 + E and the 512 bytes behind it.
 static void check_few() {
     CHECK(moe_few(32, 8, 3) && !moe_few(33, 8, 3) && !moe_few(32, 8, 4) && moe_few(64, 64, 4) && !moe_few(65, 64, 4) && !moe_few(64, 63, 4), "lines");
     unsigned seed = 1;
@@ -34,6 +35,7 @@ static void check_few() {
         for (int k = 1; k <= 16; ++k)
             for (int E = 1; E <= 256; E += E < 16 ? 1 : 24) {
                 if (!moe_few(T, E, k)) continue;
+                CHECK(((T * k + 31) / 32 - (T * k + 63) / 64) * 16 <= 512, "%d tokens x %d on %d experts: records", T, k, E);
                 for (int form = 0; form < 4; ++form) {                 // all on one; 33 each as far as they go; 1 each; random
                     int left = T * k, tiles = 0;
                     for (int e = 0; e < E && left > 0; ++e) {

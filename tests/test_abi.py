@@ -243,3 +243,16 @@ def test_headers_are_plain_c_and_link(tmp_path):
     res = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert res.returncode == 0, res.stdout
     assert "entry points" in res.stdout and "success" in res.stdout
+
+
+def test_moe_workspace_of_calls_with_few_tokens(lib):
+    """Their tiles of 32 rows are up to slots / 32 + E, in the same workspace as ever: the records fit in front of part 6."""
+    pinned = {(64, 2048, 768, 128, 8): 4743424, (32, 384, 640, 43, 16): 1143552, (64, 384, 640, 256, 16): 2289664, (1, 128, 128, 1, 12): 10496, (65, 2048, 768, 128, 8): 4818176}
+    for sizes, size in pinned.items():
+        assert lib.moe_ffn_fp8_workspace_bytes(*sizes) == size, sizes
+    for T in range(1, 65):
+        for KTOP in range(1, 17):
+            E = -(-T * KTOP // (12 if T <= 32 else 4))
+            for e in (E, 256):
+                room = lib.moe_ffn_fp8_workspace_offset(T, 256, 128, e, KTOP, 6) - lib.moe_ffn_fp8_workspace_offset(T, 256, 128, e, KTOP, 3)
+                assert 16 * (-(-T * KTOP // 32) + e) <= room, (T, KTOP, e)
